@@ -8,12 +8,13 @@
 //
 // GPU design: nodes are binned into a uniform grid of cells about one mean
 // spacing wide (count, scan, scatter). One 64-lane wavefront handles one
-// centre: it gathers the (d^2, j) keys of all nodes in a square block of
-// cells into LDS, bitonic-sorts them, and accepts the first n_c when the
-// n_c-th distance is provably inside the searched block (every unsearched
-// node is at least r cell widths away); otherwise it widens the block. A
-// centre whose block holds more candidates than LDS (a dense cluster) is
-// finished by an exact selection kernel over the same blocks instead.
+// centre: it takes the (d^2, j) keys of all nodes in a square block of cells
+// and accepts the n_c smallest when the n_c-th distance is provably inside
+// the searched block (every unsearched node is at least r cell widths away);
+// otherwise it widens the block. Blocks of up to 256 candidates are ranked by
+// counting, larger ones (uneven node sets) sorted in LDS, and a centre whose
+// block holds more than LDS does (a dense cluster) is finished by an exact
+// selection kernel over the same blocks.
 #pragma clang fp contract(off)
 
 #include <algorithm>
@@ -273,17 +274,150 @@ __device__ __forceinline__ int block_cell(const Grid &g, const CellBlock &b, int
   return (b.z_lo + t / b.nxc) * g.ncx + ix;
 }
 
-__global__ __launch_bounds__(KNN_BLOCK) void query_kernel(
+// The usual query: one wavefront per centre, four per block, no barriers. The
+// block's candidates are held in registers (at most KNN_REG per lane); those
+// inside the radius that the block provably covers are compacted into LDS,
+// and each takes its place in the result by counting the smaller keys among
+// them (broadcast reads), so nothing is sorted and only about n / 0.75 keys
+// are compared. Bound by vector issue (the count loop) and the three
+// dependent loads cell start -> node number -> coordinates, which 32
+// wavefronts per compute unit hide: 4 KB of LDS per wavefront, where the
+// LDS sort below needs 25 KB and runs six. The whole search of the 524,288
+// centres of the 2048 x 256 channel (n = 37) takes 1.03 ms, against 6.06 ms
+// with every centre sorted in LDS. A centre whose block holds more
+// than KNN_KEYS candidates (denser than about 2.5 nodes per cell there) or more
+// than KNN_ROWS rows (a sparse one) goes to `over`, for query_list_kernel.
+constexpr int KNN_WAVES = 4;
+constexpr int KNN_REG = 4;
+constexpr int KNN_KEYS = 64 * KNN_REG;
+constexpr int KNN_ROWS = 32;
+
+struct __align__(16) Key {
+  double d;
+  int j, pad;
+};
+
+__device__ __forceinline__ void knn_wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__global__ __launch_bounds__(64 * KNN_WAVES) void query_kernel(
+    const double *__restrict__ xy, Grid g, const int *__restrict__ start, const int *__restrict__ cell_nodes,
+    const int *__restrict__ centers, int n_centers, const int *__restrict__ n_per, int n_max, int *__restrict__ idx,
+    int *__restrict__ over, int *__restrict__ n_over) {
+  __shared__ Key s_keys[KNN_WAVES][KNN_KEYS];
+  // block ids go round-robin over the 8 XCDs: each XCD takes a contiguous
+  // range of centres, whose candidates then stay in its L2
+  const int nb = gridDim.x, full = (nb / 8) * 8, bid = blockIdx.x;
+  const int lb = bid >= full ? bid : (bid % 8) * (nb / 8) + bid / 8;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int lane = threadIdx.x & 63;
+  const int q = lb * KNN_WAVES + wave;
+  if (q >= n_centers) return;
+  Key *keys = s_keys[wave];
+  const int c = centers ? centers[q] : q;
+  const int nq = n_per ? n_per[q] : n_max;
+  const double2 *pt = reinterpret_cast<const double2 *>(xy);
+  const double xc = xy[2 * static_cast<int64_t>(c)], zc = xy[2 * static_cast<int64_t>(c) + 1];
+  const int cx = cell_x(g, xc), cz = cell_z(g, zc);
+  const double smin = fmin(g.sx, g.sz);
+  int r = max(1, static_cast<int>(ceil(sqrt(nq / 3.14159))));
+  for (;; ++r) {
+    const CellBlock b = cell_block(g, cx, cz, r);
+    // lane t: the node ranges of the block's row t
+    int a0 = 0, b0 = 0, a1 = 0, b1 = 0;
+    if (b.nzc <= KNN_ROWS && lane < b.nzc) block_row(g, b, b.z_lo + lane, start, a0, b0, a1, b1);
+    const int len0 = b0 - a0, len = len0 + (b1 - a1);
+    int incl = len;
+    for (int off = 1; off < KNN_ROWS; off <<= 1) {
+      const int v = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += v;
+    }
+    const int total = __builtin_amdgcn_readlane(incl, KNN_ROWS - 1);
+    if (b.nzc > KNN_ROWS || total > KNN_KEYS) {
+      if (lane == 0) over[atomicAdd(n_over, 1)] = q;
+      return;
+    }
+    // candidate lane + 64 u: its place in cell_nodes, row by row
+    const bool wraps = __ballot(b1 > a1) != 0;
+    const int first = incl - len;
+    int p[KNN_REG];
+#pragma unroll
+    for (int u = 0; u < KNN_REG; ++u) p[u] = -1;
+    for (int t = 0; t < b.nzc; ++t) {
+      const int f = __builtin_amdgcn_readlane(first, t), e = __builtin_amdgcn_readlane(incl, t);
+      const int s0 = __builtin_amdgcn_readlane(a0, t) - f;
+      const int n0 = f + __builtin_amdgcn_readlane(len0, t);
+      const int s1 = wraps ? __builtin_amdgcn_readlane(a1, t) - n0 : 0;
+#pragma unroll
+      for (int u = 0; u < KNN_REG; ++u) {
+        const int k = lane + 64 * u;
+        if (64 * u < total && k >= f && k < e) p[u] = k + (k < n0 ? s0 : s1);
+      }
+    }
+    int j[KNN_REG];
+    double d[KNN_REG];
+#pragma unroll
+    for (int u = 0; u < KNN_REG; ++u) j[u] = p[u] >= 0 ? cell_nodes[p[u]] : -1;
+#pragma unroll
+    for (int u = 0; u < KNN_REG; ++u) {
+      d[u] = INFINITY;
+      if (j[u] >= 0) {
+        const double2 v = pt[j[u]];
+        d[u] = key_d2(v.x, v.y, xc, zc, g.period);
+      }
+    }
+    // keys below the covered radius (all of them when the block is the whole
+    // grid): with at least nq of them, the nq smallest are among them
+    const double reach = r * smin, lim = reach * reach * (1.0 - 1e-12);
+    int cnt = 0;
+    knn_wave_sync();
+#pragma unroll
+    for (int u = 0; u < KNN_REG; ++u) {
+      const bool in = j[u] >= 0 && (b.covered || d[u] < lim);
+      const uint64_t m = __ballot(in);
+      if (in) {
+        const int at = cnt + __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(m >> 32),
+                                                       __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(m), 0));
+        keys[at] = Key{d[u], j[u], 0};
+      }
+      cnt += __popcll(m);
+    }
+    if (cnt < nq) {
+      if (b.covered) return;  // fewer nodes than nq: ruled out by the argument checks
+      continue;
+    }
+    knn_wave_sync();
+    int *out = idx + static_cast<int64_t>(q) * n_max;
+    for (int at = lane; at < cnt; at += 64) {
+      const Key own = keys[at];
+      int rank = 0;
+#pragma unroll 4
+      for (int k = 0; k < cnt; ++k) rank += key_less(keys[k].d, keys[k].j, own.d, own.j) ? 1 : 0;
+      if (rank < nq) out[rank] = own.j;
+    }
+    for (int k = nq + lane; k < n_max; k += 64) out[k] = -1;
+    return;
+  }
+}
+
+// The centres query_kernel leaves over (uneven node sets): the same widening
+// blocks with up to KNN_CAP candidates sorted in LDS, one wavefront per
+// block. A centre of a still denser block is marked (KNN_DENSE in its first
+// entry) for query_wide_kernel, which runs over the same list.
+constexpr int KNN_DENSE = -2;
+__global__ __launch_bounds__(KNN_BLOCK) void query_list_kernel(
     const double *__restrict__ xy, int n_nodes, Grid g, const int *__restrict__ start,
     const int *__restrict__ cell_nodes, const int *__restrict__ centers, int n_centers,
-    const int *__restrict__ n_per, int n_max, int *__restrict__ idx, int *__restrict__ over,
-    int *__restrict__ n_over) {
+    const int *__restrict__ n_per, int n_max, int *__restrict__ idx,
+    const int *__restrict__ over) {
   __shared__ double sd[KNN_CAP];
   __shared__ int sj[KNN_CAP];
   __shared__ int s_scan[KNN_BLOCK];
-  const int q = blockIdx.x;
+  const int q = over[blockIdx.x];
   const int lane = threadIdx.x;
-  if (q >= n_centers) return;
   const int c = centers ? centers[q] : q;
   const int nq = n_per ? n_per[q] : n_max;
   int *out = idx + static_cast<int64_t>(q) * n_max;
@@ -314,8 +448,8 @@ __global__ __launch_bounds__(KNN_BLOCK) void query_kernel(
     const int total = s_scan[KNN_BLOCK - 1];
     int pos = s_scan[lane] - my;
     __syncthreads();
-    if (total > KNN_CAP) {  // a dense cluster: the exact fallback kernel takes this centre
-      if (lane == 0) over[atomicAdd(n_over, 1)] = q;
+    if (total > KNN_CAP) {  // a dense cluster: the selection kernel takes this centre
+      if (lane == 0) out[0] = KNN_DENSE;
       return;
     }
     // pass 2: keys into LDS
@@ -379,6 +513,7 @@ __global__ __launch_bounds__(KNN_BLOCK) void query_wide_kernel(
   __shared__ int s_out[128];
   const int q = list[blockIdx.x];
   const int lane = threadIdx.x;
+  if (idx[static_cast<int64_t>(q) * n_max] != KNN_DENSE) return;  // the list kernel finished it
   const int c = centers ? centers[q] : q;
   const int nq = n_per ? n_per[q] : n_max;
   const double xc = xy[2 * c], zc = xy[2 * c + 1];
@@ -507,13 +642,15 @@ int knn_run(rbffd_ctx *ctx, const rbffd_stencils *st, int32_t *idx, Workspace &w
   scan_tiles_kernel<<<1, SCAN_THREADS, 0, s>>>(d_tiles, tiles, d_start, ncell);
   scan_write_kernel<<<tiles, SCAN_THREADS, 0, s>>>(d_count, ncell, d_tiles, d_start);
   scatter_kernel<<<grid_for(n, 256), 256, 0, s>>>(st->xy, n, g, d_start, d_count, d_nodes);
-  query_kernel<<<nc, KNN_BLOCK, 0, s>>>(st->xy, n, g, d_start, d_nodes, st->centers, nc, st->n_per, st->n_max, idx,
-                                        d_over, d_nover);
+  query_kernel<<<grid_for(nc, KNN_WAVES), 64 * KNN_WAVES, 0, s>>>(st->xy, g, d_start, d_nodes, st->centers, nc,
+                                                                  st->n_per, st->n_max, idx, d_over, d_nover);
   RBFFD_HIP(ctx, hipGetLastError());
   int n_over = 0;
   RBFFD_HIP(ctx, hipMemcpyAsync(&n_over, d_nover, sizeof(int), hipMemcpyDeviceToHost, s));
   RBFFD_HIP(ctx, hipStreamSynchronize(s));
   if (n_over > 0) {
+    query_list_kernel<<<n_over, KNN_BLOCK, 0, s>>>(st->xy, n, g, d_start, d_nodes, st->centers, nc, st->n_per, st->n_max,
+                                                   idx, d_over);
     query_wide_kernel<<<n_over, KNN_BLOCK, 0, s>>>(st->xy, g, d_start, d_nodes, st->centers, st->n_per, st->n_max,
                                                    d_over, idx);
     RBFFD_HIP(ctx, hipGetLastError());

@@ -463,6 +463,26 @@ def test_knn_dense_cluster(R, ctx):
     _knn_case(R, ctx, xy, 60, 0.0, centers=samp, n_per=n_per)
 
 
+@pytest.mark.parametrize("n", [13, 37, 61, 120])
+def test_knn_uneven_sets(R, ctx, n):
+    """Sets whose search blocks hold around the 64, 128 and 256 candidates at
+    which the search changes its way (one to four keys per lane, then the
+    sorting kernel), isolated nodes whose blocks span more than 32 rows, and
+    tied distances in a dense lattice patch; bit-exact against the oracle."""
+    say(f"knn: uneven node sets, n = {n}")
+    rng = np.random.default_rng(29)
+    sparse = rng.uniform(0.0, 1.0, (1500, 2))
+    patches = [np.array([x, 0.5]) + rng.uniform(-0.05, 0.05, (k, 2))
+               for x, k in ((0.1, 40), (0.3, 90), (0.5, 180), (0.7, 400), (0.9, 900))]
+    g = np.arange(16) * 2.0 ** -9
+    lattice = np.stack(np.meshgrid(0.25 + g, 0.75 + g), -1).reshape(-1, 2)
+    far = np.array([[3.0, 0.5], [3.0, 2.5], [0.5, 2.9]])
+    xy = np.concatenate([sparse, *patches, lattice, far])
+    for period in (0.0, 4.0):
+        cen = np.concatenate([np.arange(0, len(xy) - 3, 17), len(xy) - 1 - np.arange(3)]).astype(np.int32)
+        _knn_case(R, ctx, xy, n, period, centers=cen)
+
+
 def test_weights_tuner_shapes_are_bit_identical(R, ctx):
     """Every launch shape of every size bucket (persistent grids of 8-24
     workgroups per compute unit or one per system; two systems per wavefront
