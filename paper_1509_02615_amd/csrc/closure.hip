@@ -7,13 +7,9 @@
 // (4, padded to 16). BF16 weights and activations, FP32 accumulation on the
 // matrix cores (v_mfma_f32_16x16x32_bf16).
 //
-// Every product is one kernel, C = A . B^T with both operands contiguous
-// along the contraction index (samples x features, or features x samples
-// for the weight gradients), and an epilogue per use:
-//   bias + activation -> BF16  (hidden layers)
-//   bias -> FP32               (output layer)
-//   x a'(h) -> BF16            (back-propagation through the activation)
-//   atomic FP32 accumulation   (weight gradients, split over sample chunks)
+// Two kernels, both from the state to their result in one launch: the forward
+// pass, and a training pass that keeps the activations of a tile of samples in
+// LDS and the parameter gradient in registers.
 // Lane layout of the 16x16x32 instruction: lane l holds A[l%16][8(l/16)..+7],
 // B[8(l/16)..+7][l%16] (so row l%16 of B^T) and D[4(l/16)..+3][l%16].
 #include <algorithm>
@@ -32,65 +28,6 @@ static_assert(NPARAM == RBFFD_CLOSURE_NPARAMS, "parameter layout");
 
 typedef __attribute__((ext_vector_type(4))) float f4v;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf8v;
-
-enum { EPI_ACT = 0, EPI_BIAS = 1, EPI_DACT = 2, EPI_ATOMIC = 3 };
-
-// C[m][n] (epilogue) = sum_k A[m][k] B[n][k]; A: M x K (lda), B: 16*NT x K
-// (ldb); K a multiple of 32 within [kbeg, kend) = blockIdx.y's chunk. Four
-// wavefronts, each 16 rows x 16*NT columns.
-template <int EPI, int NT>
-__global__ __launch_bounds__(256) void gemm_nt_kernel(const __bf16 *__restrict__ A, int lda,
-                                                      const __bf16 *__restrict__ B, int ldb, int M, int K,
-                                                      int k_chunk, const float *__restrict__ bias,
-                                                      const __bf16 *__restrict__ H, int ldh, void *C, int ldc,
-                                                      int act) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int m0 = blockIdx.x * 64 + wave * 16;
-  const int kbeg = blockIdx.y * k_chunk, kend = min(K, kbeg + k_chunk);
-  f4v acc[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) acc[t] = f4v{0.f, 0.f, 0.f, 0.f};
-  const int row = m0 + (lane & 15), koff = 8 * (lane >> 4);
-  const bool rowok = row < M;
-  for (int k0 = kbeg; k0 < kend; k0 += 32) {
-    bf8v a;
-    if (rowok) {
-      a = *reinterpret_cast<const bf8v *>(A + static_cast<int64_t>(row) * lda + k0 + koff);
-    } else {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) a[q] = static_cast<__bf16>(0.0f);
-    }
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const bf8v b = *reinterpret_cast<const bf8v *>(B + static_cast<int64_t>(16 * t + (lane & 15)) * ldb + k0 + koff);
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[t], 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int c = 16 * t + (lane & 15);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = m0 + 4 * (lane >> 4) + i;
-      if (r >= M) continue;
-      const float v = acc[t][i];
-      const int64_t o = static_cast<int64_t>(r) * ldc + c;
-      if constexpr (EPI == EPI_ACT) {
-        const float z = v + bias[c];
-        static_cast<__bf16 *>(C)[o] =
-            static_cast<__bf16>(act == RBFFD_ACT_RELU ? __builtin_elementwise_maximum(z, 0.0f) : tanhf(z));
-      } else if constexpr (EPI == EPI_BIAS) {
-        static_cast<float *>(C)[o] = v + bias[c];
-      } else if constexpr (EPI == EPI_DACT) {
-        const float h = static_cast<float>(H[static_cast<int64_t>(r) * ldh + c]);
-        static_cast<__bf16 *>(C)[o] = static_cast<__bf16>(act == RBFFD_ACT_RELU ? (h > 0.0f ? v : 0.0f)
-                                                                                : v * (1.0f - h * h));
-      } else {
-        atomicAdd(static_cast<float *>(C) + o, v);
-      }
-    }
-  }
-}
 
 // ---- fused forward pass -------------------------------------------------
 // One kernel from the state to the normalised correction. The products are
@@ -143,13 +80,13 @@ template <int ACT> __device__ __forceinline__ float act_fn(float v) {
 // 8j + 2g + 1 (four fields each). Branch-free: a slot past the stencil
 // re-reads the node itself (difference 0); slot 37 carries the node value.
 __device__ __forceinline__ bf8v gather_block(const float *__restrict__ y, const int *__restrict__ idx_t, int64_t Na,
-                                             int n, int E, float nodev, float4 inv, int64_t i, int e, float4 own,
+                                             int E, float nodev, float4 inv, int64_t i, int e, float4 own,
                                              int slot0) {
   bf8v x;
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const int slot = slot0 + h;
-    const int64_t j = (slot >= 1 && slot < n) ? idx_t[static_cast<int64_t>(slot) * Na + i] : i;
+    const int64_t j = idx_t[static_cast<int64_t>(slot) * Na + i];
     const float4 f = *reinterpret_cast<const float4 *>(y + (j * E + e) * 4);
     const float4 b = slot == 0 ? make_float4(0.f, 0.f, 0.f, 0.f) : own;
     float v0 = (f.x - b.x) * inv.x, v1 = (f.y - b.y) * inv.y, v2 = (f.z - b.z) * inv.z, v3 = (f.w - b.w) * inv.w;
@@ -173,7 +110,7 @@ __device__ __forceinline__ bf8v gather_block(const float *__restrict__ y, const 
 template <int T, int MLP_WAVES, int MLP_OCC, int ACT>
 __global__ __launch_bounds__(64 * MLP_WAVES) __attribute__((amdgpu_waves_per_eu(MLP_OCC, MLP_OCC))) void
 mlp_forward_kernel(
-    const float *__restrict__ y, const int *__restrict__ idx_t, int64_t Na, int n, int E,
+    const float *__restrict__ y, const int *__restrict__ idx_t, int64_t Na, int E,
     const float *__restrict__ nodef, float4 inv, const __bf16 *__restrict__ frag_g, const float *__restrict__ params,
     float *__restrict__ Y, int64_t S) {
   extern __shared__ __attribute__((aligned(16))) unsigned char mlp_lds[];
@@ -219,7 +156,7 @@ mlp_forward_kernel(
     for (int j = 0; j < 5; ++j)
 #pragma unroll
       for (int tl = 0; tl < T; ++tl)
-        x[j][tl] = gather_block(y, idx_t, Na, n, E, nodev[tl], inv, si[tl], se[tl], own[tl], 8 * j + 2 * g);
+        x[j][tl] = gather_block(y, idx_t, Na, E, nodev[tl], inv, si[tl], se[tl], own[tl], 8 * j + 2 * g);
     bf8v hb[4][T];
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
@@ -312,141 +249,465 @@ template <int SHAPE> __global__ __launch_bounds__(256) void mfma_probe_kernel(fl
   out[static_cast<int64_t>(blockIdx.x) * 256 + tid] = v;
 }
 
-// Input features, one thread per (sample, 4-value group): slot 0 = own
-// fields, slots 1..36 = differences, group 37 = node value + zeros, 38..39 = 0.
-__global__ void features_kernel(const float *__restrict__ y, const int *__restrict__ idx_t, int64_t Na, int n, int E,
-                                const float *__restrict__ nodef, float4 inv_scale, __bf16 *__restrict__ X) {
-  const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t S = Na * E;
-  if (t >= S * 40) return;
-  const int64_t s = t / 40;
-  const int k = static_cast<int>(t - s * 40);
-  const int64_t i = s / E;
-  const int e = static_cast<int>(s - i * E);
-  float v[4] = {0.f, 0.f, 0.f, 0.f};
-  const float4 own = *reinterpret_cast<const float4 *>(y + (i * E + e) * 4);
-  if (k == 0) {
-    v[0] = own.x * inv_scale.x;
-    v[1] = own.y * inv_scale.y;
-    v[2] = own.z * inv_scale.z;
-    v[3] = own.w * inv_scale.w;
-  } else if (k < n) {
-    const int j = idx_t[static_cast<int64_t>(k) * Na + i];
-    const float4 f = *reinterpret_cast<const float4 *>(y + (static_cast<int64_t>(j) * E + e) * 4);
-    v[0] = (f.x - own.x) * inv_scale.x;
-    v[1] = (f.y - own.y) * inv_scale.y;
-    v[2] = (f.z - own.z) * inv_scale.z;
-    v[3] = (f.w - own.w) * inv_scale.w;
-  } else if (k == NSLOT_MAX) {
-    v[0] = nodef[i];
-  }
-  __bf16 *o = X + s * KIN + 4 * k;
-  for (int c = 0; c < 4; ++c) o[c] = static_cast<__bf16>(v[c]);
+// ---- fused training pass -----------------------------------------------
+// Loss and parameter gradient in one persistent kernel: blocks of eight
+// wavefronts (one block per compute unit) take tiles of 64 samples through
+// gather, forward, loss, backward and the weight gradients without leaving
+// LDS, and hold the whole gradient in matrix-core accumulators (at most 80
+// registers per lane) over all their tiles. One partial gradient per block
+// goes to memory; grad_reduce_kernel adds them in a fixed order.
+//
+// Products use v_mfma_f32_32x32x16_bf16 (twice the rate of 16x16x32): lane l
+// holds A[l%32][8(l/32)..+7], B[8(l/32)..+7][l%32] and, in register i,
+// D[8(i/4) + 4(l/32) + i%4][l%32]. Wavefront w owns hidden units
+// 32 (w%4)..+31 and samples 32 (w/4)..+31 of each layer's output, and in the
+// weight gradients the same hidden units and every second half of the
+// columns. The layer outputs lie in LDS as [sample][unit], so the next layer
+// reads rows (16 bytes a lane) and the weight gradients, which contract over
+// the samples, read columns with the transposing LDS load; so do the
+// products with W2 transposed, from the one copy of W2. Rows are 256 bytes;
+// their 16-byte chunks are permuted by row (tr_sw) so that both kinds of
+// read touch every bank once. Most of W1 stays in registers.
+//
+// Feature 150 (padding of the input row, where the network's W1 sees 0) is
+// set to 1: its column of the W1 gradient is the gradient of b1. Likewise
+// output 4 (padding) of dY in LDS is 1, and its row of a product with dH2 the
+// gradient of b2.
+//
+// Bound by the matrix and LDS pipes at two wavefronts per SIMD. 417,792
+// samples (192 members x 2,176 nodes): 161 us per call (146 us this kernel,
+// 9 us the sum of the blocks' gradients), against 1,471 us with one launch per
+// product and the activations, their transposes and atomic weight gradients in
+// HBM. The matrix pipe is busy 32% of the kernel, the vector unit 38%, LDS 45%:
+// what is left is the latency of the four phases between barriers.
+constexpr int TR_S = 64, TR_WAVES = 8, TR_ONE = 150, TR_ONE_DY = 4;
+constexpr int TR_W1_REG = 6;                          // W1 fragments in registers (of 10); the others in LDS
+constexpr unsigned TR_ROWS = TR_S * 256;              // one [64][128] array
+// arrays with 256-byte rows: inputs 0-127 of two tiles, H1, H2 (within the
+// 64 KB that an LDS instruction's offset reaches), dH2, dH1, W2 (the next)
+constexpr unsigned TR_XA = 0, TR_H1 = 2 * TR_ROWS, TR_H2 = 3 * TR_ROWS, TR_HI = 65536, TR_D2 = TR_HI,
+                   TR_D1 = TR_D2 + TR_ROWS, TR_W2 = TR_D1 + TR_ROWS, TR_XB = TR_W2 + HID * 256,
+                   TR_XB_TILE = TR_S * 64, TR_DY = TR_XB + 2 * TR_XB_TILE, TR_W3 = TR_DY + TR_S * 32,
+                   TR_W1 = TR_W3 + 1024, TR_B = TR_W1 + 4 * (10 - TR_W1_REG) * 1024,
+                   TR_LDS = TR_B + (2 * HID + 4) * 4;
+static_assert(TR_H2 + TR_ROWS <= TR_HI, "arrays below the second base");
+static_assert(TR_LDS <= 160 * 1024, "LDS of the training kernel");
+
+typedef __attribute__((ext_vector_type(16))) float f16v;
+typedef __attribute__((ext_vector_type(4))) __bf16 bf4v;
+typedef __attribute__((ext_vector_type(4))) short s4v;
+typedef __attribute__((ext_vector_type(2))) unsigned short u2s;
+
+// LDS by byte address
+template <typename T> __device__ __forceinline__ T lds_get(unsigned at) {
+  return *(const __attribute__((address_space(3))) T *)(at);
+}
+template <typename T> __device__ __forceinline__ void lds_put(unsigned at, T v) {
+  *(__attribute__((address_space(3))) T *)(at) = v;
+}
+// Byte offset of 16-byte chunk c of row `row`: of a 256-byte-row array, and of
+// the inputs' last 32 features (64-byte rows). The permutation touches bits
+// 4-7 (4-5), so (at ^ 16 c') is chunk c ^ c'.
+__device__ __forceinline__ unsigned tr_at(int row, int c) {
+  return row * 256 + ((c ^ (((row & 3) << 2) | ((row >> 2) & 3))) << 4);
+}
+__device__ __forceinline__ unsigned tr_at_x(int row, int c) { return row * 64 + ((c ^ ((row >> 2) & 3)) << 4); }
+
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+// Eight 16-bit values of one column, from the four rows at p0 and the four at
+// p1: in each group of 16 lanes, lane i gives the address of row i/4, columns
+// 4 (i%4)..+3 and receives column i.
+__device__ __forceinline__ bf8v read_tr2(unsigned p0, unsigned p1) {
+  const s4v a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4v *)(p0));
+  const s4v b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4v *)(p1));
+  return __builtin_bit_cast(bf8v, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// out[c][s] = in[s][c] for s < S, 0 for S <= s < Sp (Cn, ldi and Sp multiples
-// of 8); 64x64 tiles through LDS, with 16-byte loads along c and 16-byte
-// stores along s.
-__global__ __launch_bounds__(256) void transpose_kernel(const __bf16 *__restrict__ in, int ldi, int64_t S, int Cn,
-                                                        __bf16 *__restrict__ out, int64_t Sp) {
-  __shared__ __attribute__((aligned(16))) __bf16 tile[64][72];  // [s][c]; 144-byte rows
-  const int64_t s0 = static_cast<int64_t>(blockIdx.x) * 64;
-  const int c0 = blockIdx.y * 64;
-  for (int v = threadIdx.x; v < 512; v += 256) {  // 64 rows x 8 vectors of 8
-    const int r = v >> 3, cv = (v & 7) * 8;
-    const int64_t s = s0 + r;
-    const int c = c0 + cv;
-    bf8v x;
+// Back through the activation: d a'(h), rounded to BF16, from the BF16 values
+// h. relu: h is 0 or above, so the value is kept where h's bits are not 0.
+template <int ACT> __device__ __forceinline__ bf4v act_back(f4v d, bf4v h) {
+  bf4v o;
+  if constexpr (ACT == RBFFD_ACT_RELU) {
 #pragma unroll
-    for (int q = 0; q < 8; ++q) x[q] = static_cast<__bf16>(0.0f);
-    if (s < S && c < Cn) x = *reinterpret_cast<const bf8v *>(in + s * ldi + c);
-    *reinterpret_cast<bf8v *>(&tile[r][cv]) = x;
-  }
-  __syncthreads();
-  for (int v = threadIdx.x; v < 512; v += 256) {  // 64 columns x 8 vectors of 8 samples
-    const int cr = v >> 3, sv = (v & 7) * 8;
-    const int c = c0 + cr;
-    const int64_t s = s0 + sv;
-    if (c < Cn && s < Sp) {
-      bf8v y;
+    for (int i = 0; i < 4; ++i) o[i] = static_cast<__bf16>(d[i]);
+    typedef __attribute__((ext_vector_type(4))) unsigned short u4s;
+    const u4s hb = __builtin_bit_cast(u4s, h);
+    return __builtin_bit_cast(bf4v, static_cast<u4s>(__builtin_bit_cast(u4s, o) *
+                                                     __builtin_elementwise_min(hb, u4s{1, 1, 1, 1})));
+  } else {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) y[q] = tile[sv + q][cr];
-      *reinterpret_cast<bf8v *>(out + static_cast<int64_t>(c) * Sp + s) = y;
+    for (int i = 0; i < 4; ++i) {
+      const float f = static_cast<float>(h[i]);
+      o[i] = static_cast<__bf16>(d[i] * (1.0f - f * f));
     }
+    return o;
   }
 }
 
-// dY = 2 (Y - T) / (4 S) for the 4 outputs (BF16, padded to 32 columns for
-// the next product; FP32 copy [S][4] for the output bias gradient) and the
-// loss sum of (Y - T)^2 / (4 S).
-__global__ void loss_kernel(const float *__restrict__ Y, const float *__restrict__ T, int64_t S,
-                            __bf16 *__restrict__ dY, float *__restrict__ dY32, double *__restrict__ loss) {
-  __shared__ double red[256];
-  const int64_t s = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  double l = 0.0;
-  if (s < S) {
-    const float inv = 1.0f / static_cast<float>(4 * S);
-    for (int c = 0; c < 32; ++c) {
-      float g = 0.0f;
-      if (c < 4) {
-        const float d = Y[s * NOUT + c] - T[s * 4 + c];
-        l += static_cast<double>(d) * d;
-        g = 2.0f * d * inv;
-        dY32[s * 4 + c] = g;
+// Sum over the 32 lanes that share l/32.
+template <typename T> __device__ __forceinline__ T half_sum(T v) {
+  for (int off = 16; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
+template <int ACT>
+__global__ __launch_bounds__(64 * TR_WAVES) __attribute__((amdgpu_waves_per_eu(2, 2))) void train_kernel(
+    const float *__restrict__ y, const int *__restrict__ idx_t, int Na, int E, const float *__restrict__ nodef,
+    float4 inv, const __bf16 *__restrict__ w1, const __bf16 *__restrict__ w2, const __bf16 *__restrict__ w3,
+    const float *__restrict__ params, const float *__restrict__ target, int S, float *__restrict__ part,
+    double *__restrict__ part_loss) {
+  extern __shared__ __attribute__((aligned(256))) unsigned char lds[];
+  const unsigned L0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char *)lds));
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), hg = wave & 3, sg = wave >> 2;
+  const int lc = lane & 31, lh = lane >> 5;            // column and half of the 32x32 products
+  // weights: W1 fragments in registers and LDS, W2, W3's four rows
+  // ([16-byte chunk][row]) and the biases in LDS
+  bf8v fw1[TR_W1_REG];
+  const unsigned w1_at = L0 + TR_W1 + hg * (10 - TR_W1_REG) * 1024 + lane * 16;
+#pragma unroll
+  for (int kk = 0; kk < 10; ++kk) {
+    bf8v v = *reinterpret_cast<const bf8v *>(w1 + (32 * hg + lc) * KIN + 16 * kk + 8 * lh);
+    if (kk == TR_ONE / 16 && lh == (TR_ONE % 16) / 8) v[TR_ONE % 8] = static_cast<__bf16>(0.0f);
+    if (kk < TR_W1_REG)
+      fw1[kk < TR_W1_REG ? kk : 0] = v;
+    else if (sg == 0)
+      lds_put(w1_at + (kk - TR_W1_REG) * 1024, v);
+  }
+  bf8v fw3t;                                           // W3 transposed, contraction over the four outputs
+#pragma unroll
+  for (int q = 0; q < 8; ++q)
+    fw3t[q] = q < 4 && lh == 0 ? w3[q * HID + 32 * hg + lc] : static_cast<__bf16>(0.0f);
+  for (int t = tid; t < HID * 16; t += 64 * TR_WAVES)
+    lds_put(L0 + TR_W2 + tr_at(t >> 4, t & 15), *reinterpret_cast<const bf8v *>(w2 + (t >> 4) * HID + 8 * (t & 15)));
+  if (tid < 64) lds_put(L0 + TR_W3 + tid * 16, *reinterpret_cast<const bf8v *>(w3 + (tid & 3) * HID + 8 * (tid >> 2)));
+  for (int t = tid; t < 2 * HID + 4; t += 64 * TR_WAVES)
+    lds_put(L0 + TR_B + t * 4, t < HID ? params[OB1 + t] : (t < 2 * HID ? params[OB2 + t - HID] : params[OB3 + t - 2 * HID]));
+  for (int t = tid; t < TR_S * 16; t += 64 * TR_WAVES)
+    lds_put(L0 + TR_DY + t * 2, static_cast<__bf16>(t % 16 == TR_ONE_DY ? 1.0f : 0.0f));
+  // the first tile has no predecessor: zeros stand in for its dH1 and inputs
+  for (int t = tid; t < static_cast<int>(TR_ROWS / 16); t += 64 * TR_WAVES) {
+    lds_put(L0 + TR_XA + TR_ROWS + t * 16, f4v{});
+    lds_put(L0 + TR_D1 + t * 16, f4v{});
+  }
+  for (int t = tid; t < static_cast<int>(TR_XB_TILE / 16); t += 64 * TR_WAVES)
+    lds_put(L0 + TR_XB + TR_XB_TILE + t * 16, f4v{});
+
+  // tiles in XCD order: block b takes tiles of XCD b % 8's range, strided
+  const int tiles = (S + TR_S - 1) / TR_S;
+  const int nb = gridDim.x, ng = nb < 8 ? 1 : 8, xcd = blockIdx.x % ng;
+  const int per = (tiles + ng - 1) / ng, step = (nb - xcd + ng - 1) / ng;
+  const int t_end = min(tiles, (xcd + 1) * per);
+  const float scale = 1.0f / static_cast<float>(4 * static_cast<int64_t>(S));
+
+  // input gather: eight threads per sample, thread g8 the groups g8 + 8 j of
+  // four features (group 0: the node, 37: its feature and the constant, others:
+  // slot differences, 0 past the stencil). Samples past S repeat the last one;
+  // their dY is 0.
+  const int gs = tid >> 3, g8 = tid & 7;
+  int gj[5], gi = 0, ge = 0;
+  auto gather_index = [&](int tile) {
+    const unsigned s = min(tile * TR_S + gs, S - 1);
+    gi = s / static_cast<unsigned>(E);
+    ge = s - gi * E;
+#pragma unroll
+    for (int j = 0; j < 5; ++j) gj[j] = idx_t[static_cast<int64_t>(8 * j + g8) * Na + gi];
+  };
+  float4 gf[5], gown;
+  float gnode;
+  auto gather_load = [&]() {
+    gown = *reinterpret_cast<const float4 *>(y + (static_cast<int64_t>(gi) * E + ge) * 4);
+#pragma unroll
+    for (int j = 0; j < 5; ++j) gf[j] = *reinterpret_cast<const float4 *>(y + (static_cast<int64_t>(gj[j]) * E + ge) * 4);
+    gnode = nodef[gi];
+  };
+  unsigned xa_at = L0 + TR_XA + tr_at(gs, g8 >> 1) + 8 * (g8 & 1);      // group g8 + 8 j: chunk g8 / 2 + 4 j
+  unsigned xb_at = L0 + TR_XB + tr_at_x(gs, g8 >> 1) + 8 * (g8 & 1);
+  auto gather_store = [&](unsigned buf) {
+#pragma unroll
+    for (int j = 0; j < 5; ++j) {
+      const float4 f = gf[j];
+      const float4 b = j == 0 && g8 == 0 ? make_float4(0.f, 0.f, 0.f, 0.f) : gown;
+      bf4v x;
+      x[0] = static_cast<__bf16>((f.x - b.x) * inv.x);
+      x[1] = static_cast<__bf16>((f.y - b.y) * inv.y);
+      x[2] = static_cast<__bf16>((f.z - b.z) * inv.z);
+      x[3] = static_cast<__bf16>((f.w - b.w) * inv.w);
+      if (j == 4) {
+        x[0] = g8 == NSLOT_MAX - 32 ? static_cast<__bf16>(gnode) : x[0];
+        x[TR_ONE - 4 * NSLOT_MAX] = static_cast<__bf16>(g8 == NSLOT_MAX - 32 ? 1.0f : static_cast<float>(x[TR_ONE - 4 * NSLOT_MAX]));
+        lds_put(xb_at + buf * TR_XB_TILE, x);
+      } else {
+        lds_put((xa_at ^ (64 * j)) + buf * TR_ROWS, x);
       }
-      dY[s * 32 + c] = static_cast<__bf16>(g);
+    }
+  };
+
+  // lane parts of the LDS addresses: this lane's row (sample, W2 row), chunk
+  // lh + 2 kk = (at ^ 32 kk); its four units of a layer output, chunk 4 hg +
+  // i4 = (at ^ 16 i4); its part of a column read of 16 rows, column tile
+  // ct = (at ^ 64 ct), rows 16 kk on = at + 4096 kk
+  const int srow = 32 * sg + lc, i16 = lane & 15, gq = lane >> 4;
+  unsigned a_row = L0 + tr_at(srow, lh), a_rowx = L0 + TR_XB + tr_at_x(srow, lh), a_w2 = L0 + TR_W2 + tr_at(32 * hg + lc, lh);
+  unsigned a_out = L0 + tr_at(srow, 4 * hg) + 8 * lh;
+  const int r0 = 8 * (gq >> 1) + (i16 >> 2), c0 = 2 * (gq & 1) + ((i16 & 3) >> 1);
+  unsigned a_c0 = L0 + tr_at(r0, c0) + 8 * (i16 & 1), a_c1 = L0 + tr_at(r0 + 4, c0) + 8 * (i16 & 1);
+  unsigned a_x0 = L0 + TR_XB + tr_at_x(r0, c0) + 8 * (i16 & 1), a_x1 = L0 + TR_XB + tr_at_x(r0 + 4, c0) + 8 * (i16 & 1);
+  // keeps the address arithmetic inside the tile loop: hoisted out of it, the
+  // addresses of every read would be held in registers
+  auto opaque = [&]() {
+    asm volatile("" : "+v"(a_row), "+v"(a_rowx), "+v"(a_w2), "+v"(a_out), "+v"(a_c0), "+v"(a_c1));
+  };
+  auto bias16 = [&](unsigned at) {
+    f16v a;
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+      const f4v v = lds_get<f4v>(L0 + at + 4 * (32 * hg + 8 * i4 + 4 * lh));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[4 * i4 + i] = v[i];
+    }
+    return a;
+  };
+  auto store_act = [&](unsigned M, const f16v &acc) {
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+      bf4v h;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) h[i] = static_cast<__bf16>(act_fn<ACT>(acc[4 * i4 + i]));
+      lds_put((a_out ^ (16 * i4)) + M, h);
+    }
+  };
+  // back through the activation whose values are in H
+  auto store_back = [&](unsigned M, unsigned H, const f16v &d) {
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+      const unsigned at = a_out ^ (16 * i4);
+      const bf4v h = lds_get<bf4v>(at + H);
+      const f4v v = {d[4 * i4], d[4 * i4 + 1], d[4 * i4 + 2], d[4 * i4 + 3]};
+      lds_put(at + M, act_back<ACT>(v, h));
+    }
+  };
+
+  f16v dw1[3] = {}, dw2[2] = {};
+  f4v dw3 = {}, db2 = {};
+  float db3[4] = {};
+  double loss = 0.0;
+  // W1 gradient of one tile: column tiles 0, 1, 2 (sg = 0) or 3, 4 (sg = 1)
+  auto grad_w1 = [&](unsigned buf) {
+    const unsigned d0 = a_c0 ^ (64 * hg), d1 = a_c1 ^ (64 * hg);
+    const unsigned p0 = (a_c0 ^ (sg ? 192 : 0)) + buf * TR_ROWS, p1 = (a_c1 ^ (sg ? 192 : 0)) + buf * TR_ROWS;
+    const unsigned q0 = sg ? a_x0 + buf * TR_XB_TILE : (a_c0 ^ 64) + buf * TR_ROWS,
+                   q1 = sg ? a_x1 + buf * TR_XB_TILE : (a_c1 ^ 64) + buf * TR_ROWS;
+    const unsigned qs = sg ? 1024 : 4096;
+    bf8v a[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      a[kk] = read_tr2(d0 + TR_D1 + kk * 4096, d1 + TR_D1 + kk * 4096);
+      dw1[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk], read_tr2(p0 + kk * 4096, p1 + kk * 4096), dw1[0], 0, 0, 0);
+      dw1[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk], read_tr2(q0 + kk * qs, q1 + kk * qs), dw1[1], 0, 0, 0);
+    }
+    if (sg == 0) {
+      const unsigned t0 = (a_c0 ^ 128) + buf * TR_ROWS, t1 = (a_c1 ^ 128) + buf * TR_ROWS;
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+        dw1[2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk], read_tr2(t0 + kk * 4096, t1 + kk * 4096), dw1[2], 0, 0, 0);
+    }
+  };
+
+  int tile = xcd * per + static_cast<int>(blockIdx.x) / ng;
+  unsigned cur = 0;
+  if (tile < t_end) {
+    gather_index(tile);
+    gather_load();
+    gather_store(0);
+    if (tile + step < t_end) gather_index(tile + step);
+  }
+  lds_barrier();
+  for (; tile < t_end; tile += step) {
+    const int next = tile + step;
+    const bool more = next < t_end;
+    opaque();
+    // layer 1, and the previous tile's W1 gradient
+    {
+      f16v acc = bias16(TR_B);
+#pragma unroll
+      for (int kk = 0; kk < 10; ++kk) {
+        const bf8v a = kk < TR_W1_REG ? fw1[kk < TR_W1_REG ? kk : 0] : lds_get<bf8v>(w1_at + (kk - TR_W1_REG) * 1024);
+        const bf8v x = kk < 8 ? lds_get<bf8v>((a_row ^ (32 * kk)) + cur * TR_ROWS)
+                              : lds_get<bf8v>((a_rowx ^ (32 * (kk - 8))) + cur * TR_XB_TILE);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, x, acc, 0, 0, 0);
+      }
+      store_act(TR_H1, acc);
+    }
+    if (more) gather_load();
+    grad_w1(cur ^ 1);
+    lds_barrier();
+    const int s_own = tile * TR_S + srow;
+    const float4 t_own = *reinterpret_cast<const float4 *>(target + static_cast<int64_t>(min(s_own, S - 1)) * 4);
+    opaque();
+    // layer 2
+    {
+      f16v acc = bias16(TR_B + HID * 4);
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_get<bf8v>(a_w2 ^ (32 * kk)),
+                                                      lds_get<bf8v>((a_row ^ (32 * kk)) + TR_H1), acc, 0, 0, 0);
+      store_act(TR_H2, acc);
+    }
+    if (more) gather_store(cur ^ 1);
+    if (next + step < t_end) gather_index(next + step);
+    lds_barrier();
+    opaque();
+    // output layer (each wavefront for its samples), loss, and dH2
+    {
+      f16v acc = {};
+      const unsigned a_w3 = L0 + TR_W3 + lh * 64 + (lane & 3) * 16;
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_get<bf8v>(a_w3 + kk * 128),
+                                                      lds_get<bf8v>((a_row ^ (32 * kk)) + TR_H2), acc, 0, 0, 0);
+      bf8v dy = {};
+      if (lh == 0 && s_own < S) {  // outputs 0-3: registers 0-3 of lanes 0-31
+        const float t[4] = {t_own.x, t_own.y, t_own.z, t_own.w};
+        const f4v b3 = lds_get<f4v>(L0 + TR_B + 2 * HID * 4);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float d = acc[i] + b3[i] - t[i];
+          const float g = 2.0f * d * scale;
+          dy[i] = static_cast<__bf16>(g);
+          if (hg == 0) {
+            db3[i] += g;
+            loss += static_cast<double>(d) * d;
+          }
+        }
+      }
+      if (hg == 0 && lh == 0) lds_put(L0 + TR_DY + srow * 32, __builtin_shufflevector(dy, dy, 0, 1, 2, 3));
+      f16v d2 = {};
+      d2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw3t, dy, d2, 0, 0, 0);
+      store_back(TR_D2, TR_H2, d2);
+    }
+    lds_barrier();
+    opaque();
+    // dH1, and the W2, W3 and b2 gradients
+    {
+      f16v d1 = {};
+      const unsigned w0 = (a_c0 ^ (64 * hg)) + TR_W2, w1c = (a_c1 ^ (64 * hg)) + TR_W2;
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk)
+        d1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_tr2(w0 + kk * 4096, w1c + kk * 4096),
+                                                     lds_get<bf8v>((a_row ^ (32 * kk)) + TR_D2), d1, 0, 0, 0);
+      store_back(TR_D1, TR_H1, d1);
+      const unsigned d0 = (a_c0 ^ (64 * hg)) + TR_D2, d1c = (a_c1 ^ (64 * hg)) + TR_D2;
+      const unsigned h0 = (a_c0 ^ (128 * sg)) + TR_H1, h1 = (a_c1 ^ (128 * sg)) + TR_H1;
+      const unsigned g0 = (a_c0 ^ (128 * sg + 64)) + TR_H1, g1 = (a_c1 ^ (128 * sg + 64)) + TR_H1;
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        const bf8v a = read_tr2(d0 + kk * 4096, d1c + kk * 4096);
+        dw2[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, read_tr2(h0 + kk * 4096, h1 + kk * 4096), dw2[0], 0, 0, 0);
+        dw2[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, read_tr2(g0 + kk * 4096, g1 + kk * 4096), dw2[1], 0, 0, 0);
+      }
+    }
+    // 16x16x32 products: lane l holds rows 8(l/16)..+7 of column l%16; this
+    // wavefront's 16 hidden units
+    {
+      const int r = 8 * gq + (i16 >> 2), c = 2 * wave + ((i16 & 3) >> 1);
+      const unsigned pd = L0 + TR_DY + r * 32 + 8 * (i16 & 3);
+      const unsigned p0 = L0 + tr_at(r, c) + 8 * (i16 & 1), p1 = L0 + tr_at(r + 4, c) + 8 * (i16 & 1);
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        const bf8v a = read_tr2(pd + kk * 1024, pd + kk * 1024 + 128);
+        const unsigned o = kk * 8192;
+        dw3 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, read_tr2(p0 + o + TR_H2, p1 + o + TR_H2), dw3, 0, 0, 0);
+        db2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, read_tr2(p0 + o + TR_D2, p1 + o + TR_D2), db2, 0, 0, 0);
+      }
+    }
+    lds_barrier();
+    cur ^= 1;
+  }
+  grad_w1(cur ^ 1);
+
+  // this block's partial gradient, in the parameters' layout
+  float *p = part + static_cast<int64_t>(blockIdx.x) * NPARAM;
+  const int n1 = sg == 0 ? 3 : 2;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    if (c >= n1) break;
+    const int f = 32 * (3 * sg + c) + lc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int h = 32 * hg + 8 * (i / 4) + 4 * lh + i % 4;
+      p[f == TR_ONE ? OB1 + h : OW1 + h * KIN + f] = dw1[c][i];
+      if (f == TR_ONE) p[OW1 + h * KIN + f] = 0.0f;
     }
   }
-  red[threadIdx.x] = l;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) atomicAdd(loss, red[0] / (4.0 * static_cast<double>(S)));
-}
-
-// grad[c] += sum_s D[s][c] over a chunk of samples (bias gradients). A block
-// is COLSUM_SLICES x 128 threads: each column's chunk is summed in that many
-// interleaved slices (independent loads in flight), the slices are added in
-// LDS, and one atomic per column and block goes to grad.
-constexpr int COLSUM_SLICES = 8;
-template <class T>
-__global__ __launch_bounds__(128 * COLSUM_SLICES) void colsum_kernel(const T *__restrict__ D, int ldd, int64_t S,
-                                                                    int Cn, int64_t chunk, float *__restrict__ grad) {
-  __shared__ float part[COLSUM_SLICES][128];
-  const int c = static_cast<int>(threadIdx.x) & 127, sl = static_cast<int>(threadIdx.x) >> 7;
-  float acc = 0.0f;
-  if (c < Cn) {
-    const int64_t b = static_cast<int64_t>(blockIdx.x) * chunk, e = min(S, b + chunk);
-#pragma unroll 8
-    for (int64_t s = b + sl; s < e; s += COLSUM_SLICES) acc += static_cast<float>(D[s * ldd + c]);
-  }
-  part[sl][c] = acc;
-  __syncthreads();
-  if (sl == 0 && c < Cn) {
-    float t = 0.0f;
 #pragma unroll
-    for (int q = 0; q < COLSUM_SLICES; ++q) t += part[q][c];
-    atomicAdd(grad + c, t);
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      p[OW2 + (32 * hg + 8 * (i / 4) + 4 * lh + i % 4) * HID + 32 * (2 * sg + c) + lc] = dw2[c][i];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int o = 4 * gq + i;
+    p[OW3 + o * HID + 16 * wave + i16] = o < 4 ? dw3[i] : 0.0f;
+    if (o == TR_ONE_DY) p[OB2 + 16 * wave + i16] = db2[i];
+  }
+  // b3 and the loss: lanes hold samples; the two sample halves meet in LDS
+  lds_barrier();
+  float *red = reinterpret_cast<float *>(lds);            // [2][4]
+  double *redl = reinterpret_cast<double *>(lds + 64);    // [2]
+  if (hg == 0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float v = half_sum(db3[i]);
+      if (lane == 0) red[sg * 4 + i] = v;
+    }
+    loss = half_sum(loss);
+    if (lane == 0) redl[sg] = loss;
+  }
+  lds_barrier();
+  if (tid < NOUT) p[OB3 + tid] = tid < 4 ? red[tid] + red[4 + tid] : 0.0f;
+  if (tid == 0) part_loss[blockIdx.x] = redl[0] + redl[1];
+}
+
+// grad = sum of the nb blocks' partial gradients (four interleaved slices per
+// parameter, added in LDS), and the loss.
+constexpr int GR_PARAMS = 64, GR_SLICES = 4;
+__global__ __launch_bounds__(GR_PARAMS *GR_SLICES) void grad_reduce_kernel(const float *__restrict__ part,
+                                                                          const double *__restrict__ part_loss, int nb,
+                                                                          int64_t S, float *__restrict__ grad,
+                                                                          double *__restrict__ loss) {
+  __shared__ float s[GR_SLICES][GR_PARAMS];
+  const int c = threadIdx.x % GR_PARAMS, sl = threadIdx.x / GR_PARAMS;
+  const int q = blockIdx.x * GR_PARAMS + c;
+  float v = 0.0f;
+  if (q < NPARAM) {
+#pragma unroll 8
+    for (int b = sl; b < nb; b += GR_SLICES) v += part[static_cast<int64_t>(b) * NPARAM + q];
+  }
+  s[sl][c] = v;
+  __syncthreads();
+  if (sl == 0 && q < NPARAM) grad[q] = (s[0][c] + s[1][c]) + (s[2][c] + s[3][c]);
+  if (blockIdx.x == 0) {  // one wavefront: nb / 64 values a lane, then across the lanes
+    if (threadIdx.x < 64) {
+      double l = 0.0;
+      for (int b = threadIdx.x; b < nb; b += 64) l += part_loss[b];
+      for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, 64);
+      if (threadIdx.x == 0) *loss = l / (4.0 * static_cast<double>(S));
+    }
   }
 }
 
-// BF16 copies of the weights (and the transposed W2, W3 the backward pass uses).
+// BF16 copies of the weights for the training kernel.
 __global__ void pack_kernel(const float *__restrict__ p, __bf16 *__restrict__ w1, __bf16 *__restrict__ w2,
-                            __bf16 *__restrict__ w3, __bf16 *__restrict__ w2t, __bf16 *__restrict__ w3t) {
+                            __bf16 *__restrict__ w3) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t < HID * KIN) w1[t] = static_cast<__bf16>(p[OW1 + t]);
-  if (t < HID * HID) {
-    const int r = t / HID, c = t % HID;
-    w2[t] = static_cast<__bf16>(p[OW2 + t]);
-    w2t[c * HID + r] = static_cast<__bf16>(p[OW2 + t]);
-  }
-  if (t < NOUT * HID) {
-    const int r = t / HID, c = t % HID;
-    w3[t] = static_cast<__bf16>(p[OW3 + t]);
-    w3t[c * 32 + r] = static_cast<__bf16>(p[OW3 + t]);   // columns 16..31 stay 0
-  }
+  if (t < HID * HID) w2[t] = static_cast<__bf16>(p[OW2 + t]);
+  if (t < NOUT * HID) w3[t] = static_cast<__bf16>(p[OW3 + t]);
 }
 
 __global__ void adam_kernel(float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m1,
@@ -497,6 +758,17 @@ __global__ void scale_out_kernel(const float *__restrict__ Y, int ys, int64_t S,
   out[s * 4 + 3] = Y[s * ys + 3] * sc.w;
 }
 
+// The gather's neighbours, one row per group of four input features: row k the
+// node of slot k (1 <= k < n), the node itself in every other row, so that a
+// slot past the stencil gives the difference 0.
+constexpr int NGROUP = KIN / 4;
+__global__ void gather_rows_fill_kernel(const int *__restrict__ idx_t, int64_t Na, int n, int *__restrict__ out) {
+  const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (t >= Na * NGROUP) return;
+  const int64_t k = t / Na;
+  out[t] = k >= 1 && k < n ? idx_t[t] : static_cast<int>(t - k * Na);
+}
+
 __global__ void f64_to_f32_kernel(const double *__restrict__ a, int64_t n, float *__restrict__ b) {
   const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (t < n) b[t] = static_cast<float>(a[t]);
@@ -506,12 +778,11 @@ __global__ void f64_to_f32_kernel(const double *__restrict__ a, int64_t n, float
 
 struct rbffd_closure {
   rbffd_model *model = nullptr;
-  int64_t max_s = 0, sp_max = 0;
+  int64_t max_s = 0;
   float4 inv_in{}, out_sc{};
   DevBuf params, grad, m1, m2, nodef, idx;
-  DevBuf w1, w2, w3, w2t, w3t;                       // BF16 weights
-  DevBuf X, H1, H2, Y, dY, dY32, dH1, dH2;           // activations [S][.]
-  DevBuf XT, H1T, H2T, dH1T, dH2T, dYT;              // transposed [.][Sp]
+  DevBuf w1, w2, w3;                                 // BF16 weights
+  DevBuf part, part_loss;                            // training: each block's partial gradient and loss
   DevBuf frag, Yc;                                   // fused forward: packed weights, Y [S][4]
   DevBuf loss, bad;
   int64_t step = 0;
@@ -521,80 +792,26 @@ struct rbffd_closure {
 
 namespace {
 
-template <int EPI, int NT>
-void gemm(hipStream_t s, const __bf16 *A, int lda, const __bf16 *B, int ldb, int M, int K, int k_chunk,
-          const float *bias, const __bf16 *H, int ldh, void *C, int ldc, int act = RBFFD_ACT_TANH) {
-  dim3 grid((M + 63) / 64, (K + k_chunk - 1) / k_chunk);
-  gemm_nt_kernel<EPI, NT><<<grid, 256, 0, s>>>(A, lda, B, ldb, M, K, k_chunk, bias, H, ldh, C, ldc, act);
-}
-
-template <class T> const T *cp(const DevBuf &b) { return b.as<T>(); }
-
-// Forward pass for S = Na * E samples of `state` into Y (normalised output).
-int forward(rbffd_ctx *ctx, rbffd_closure *cl, const void *state, int64_t S) {
+// Loss and parameter gradient (into cl->grad) for targets T [S][4]: one block
+// per compute unit, fewer when there are fewer tiles.
+int gradient(rbffd_ctx *ctx, rbffd_closure *cl, const void *state, const float *T, int64_t S) {
   hipStream_t s = ctx->stream;
   rbffd_model *m = cl->model;
-  features_kernel<<<grid_for(S * 40, 256), 256, 0, s>>>(static_cast<const float *>(state), cl->idx.as<int>(), m->Na,
-                                                         m->n, m->E, cl->nodef.as<float>(), cl->inv_in,
-                                                         cl->X.as<__bf16>());
-  const float *p = cl->params.as<float>();
-  const int Si = static_cast<int>(S);
-  gemm<EPI_ACT, 8>(s, cp<__bf16>(cl->X), KIN, cp<__bf16>(cl->w1), KIN, Si, KIN, KIN, p + OB1, nullptr, 0,
-                   cl->H1.p, HID, cl->act);
-  gemm<EPI_ACT, 8>(s, cp<__bf16>(cl->H1), HID, cp<__bf16>(cl->w2), HID, Si, HID, HID, p + OB2, nullptr, 0,
-                   cl->H2.p, HID, cl->act);
-  gemm<EPI_BIAS, 1>(s, cp<__bf16>(cl->H2), HID, cp<__bf16>(cl->w3), HID, Si, HID, HID, p + OB3, nullptr, 0,
-                    cl->Y.p, NOUT);
-  RBFFD_HIP(ctx, hipGetLastError());
-  return RBFFD_OK;
-}
-
-// Loss and parameter gradient (into cl->grad) for targets T [S][4].
-int backward(rbffd_ctx *ctx, rbffd_closure *cl, const float *T, int64_t S) {
-  hipStream_t s = ctx->stream;
-  const int Si = static_cast<int>(S);
-  const int64_t Sp = (S + 31) / 32 * 32;
-  float *g = cl->grad.as<float>();
-  RBFFD_HIP(ctx, hipMemsetAsync(cl->grad.p, 0, sizeof(float) * NPARAM, s));
-  RBFFD_HIP(ctx, hipMemsetAsync(cl->loss.p, 0, sizeof(double), s));
-  loss_kernel<<<grid_for(S, 256), 256, 0, s>>>(cl->Y.as<float>(), T, S, cl->dY.as<__bf16>(), cl->dY32.as<float>(),
-                                               cl->loss.as<double>());
-  // back through the layers: dH2 = (dY W3) a'(h2), dH1 = (dH2 W2) a'(h1)
-  gemm<EPI_DACT, 8>(s, cp<__bf16>(cl->dY), 32, cp<__bf16>(cl->w3t), 32, Si, 32, 32, nullptr, cp<__bf16>(cl->H2),
-                    HID, cl->dH2.p, HID, cl->act);
-  gemm<EPI_DACT, 8>(s, cp<__bf16>(cl->dH2), HID, cp<__bf16>(cl->w2t), HID, Si, HID, HID, nullptr,
-                    cp<__bf16>(cl->H1), HID, cl->dH1.p, HID, cl->act);
-  // transposes for the weight gradients (contraction over samples)
-  auto tr = [&](const __bf16 *in, int ldi, int Cn, DevBuf &out) {
-    dim3 grid(static_cast<unsigned>((Sp + 63) / 64), (Cn + 63) / 64);
-    transpose_kernel<<<grid, 256, 0, s>>>(in, ldi, S, Cn, out.as<__bf16>(), Sp);
-  };
-  tr(cp<__bf16>(cl->X), KIN, KIN, cl->XT);
-  tr(cp<__bf16>(cl->H1), HID, HID, cl->H1T);
-  tr(cp<__bf16>(cl->H2), HID, HID, cl->H2T);
-  tr(cp<__bf16>(cl->dH1), HID, HID, cl->dH1T);
-  tr(cp<__bf16>(cl->dH2), HID, HID, cl->dH2T);
-  tr(cp<__bf16>(cl->dY), 32, NOUT, cl->dYT);
-  const int Ki = static_cast<int>(Sp);
-  const int chunk = 1024;
-  gemm<EPI_ATOMIC, 10>(s, cp<__bf16>(cl->dH1T), Ki, cp<__bf16>(cl->XT), Ki, HID, Ki, chunk, nullptr, nullptr, 0,
-                       g + OW1, KIN);
-  gemm<EPI_ATOMIC, 8>(s, cp<__bf16>(cl->dH2T), Ki, cp<__bf16>(cl->H1T), Ki, HID, Ki, chunk, nullptr, nullptr, 0,
-                      g + OW2, HID);
-  gemm<EPI_ATOMIC, 8>(s, cp<__bf16>(cl->dYT), Ki, cp<__bf16>(cl->H2T), Ki, NOUT, Ki, chunk, nullptr, nullptr, 0,
-                      g + OW3, HID);
-  const int64_t cch = 2048;
-  const unsigned nb = static_cast<unsigned>((S + cch - 1) / cch);
-  colsum_kernel<__bf16><<<nb, 128 * COLSUM_SLICES, 0, s>>>(cp<__bf16>(cl->dH1), HID, S, HID, cch, g + OB1);
-  colsum_kernel<__bf16><<<nb, 128 * COLSUM_SLICES, 0, s>>>(cp<__bf16>(cl->dH2), HID, S, HID, cch, g + OB2);
-  colsum_kernel<float><<<nb, 128 * COLSUM_SLICES, 0, s>>>(cp<float>(cl->dY32), 4, S, 4, cch, g + OB3);
+  const int nb = static_cast<int>(std::min<int64_t>(ctx->n_cu, (S + TR_S - 1) / TR_S));
+  auto kern = cl->act == RBFFD_ACT_RELU ? train_kernel<RBFFD_ACT_RELU> : train_kernel<RBFFD_ACT_TANH>;
+  kern<<<nb, 64 * TR_WAVES, TR_LDS, s>>>(static_cast<const float *>(state), cl->idx.as<int>(), static_cast<int>(m->Na),
+                                         m->E, cl->nodef.as<float>(), cl->inv_in, cl->w1.as<__bf16>(),
+                                         cl->w2.as<__bf16>(), cl->w3.as<__bf16>(), cl->params.as<float>(), T,
+                                         static_cast<int>(S), cl->part.as<float>(), cl->part_loss.as<double>());
+  grad_reduce_kernel<<<grid_for(NPARAM, GR_PARAMS), GR_PARAMS * GR_SLICES, 0, s>>>(
+      cl->part.as<float>(), cl->part_loss.as<double>(), nb, S, cl->grad.as<float>(), cl->loss.as<double>());
   RBFFD_HIP(ctx, hipGetLastError());
   return RBFFD_OK;
 }
 
 void repack(rbffd_closure *cl, hipStream_t s) {
   pack_kernel<<<grid_for(HID * KIN, 256), 256, 0, s>>>(cl->params.as<float>(), cl->w1.as<__bf16>(), cl->w2.as<__bf16>(),
-                                                        cl->w3.as<__bf16>(), cl->w2t.as<__bf16>(), cl->w3t.as<__bf16>());
+                                                        cl->w3.as<__bf16>());
   frag_pack_kernel<<<grid_for(NFRAG * 512, 256), 256, 0, s>>>(cl->params.as<float>(), cl->frag.as<__bf16>());
 }
 
@@ -621,6 +838,10 @@ void set_mlp_lds(bool &ok) {
   set_mlp_lds_shape<2>(ok);
   set_mlp_lds_shape<3>(ok);
   set_mlp_lds_shape<4>(ok);
+  ok = ok && hipFuncSetAttribute(reinterpret_cast<const void *>(train_kernel<RBFFD_ACT_RELU>),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, TR_LDS) == hipSuccess;
+  ok = ok && hipFuncSetAttribute(reinterpret_cast<const void *>(train_kernel<RBFFD_ACT_TANH>),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, TR_LDS) == hipSuccess;
 }
 
 // Fused forward pass into cl->Yc [S][4] in launch shape S. Resident blocks per
@@ -636,7 +857,7 @@ void launch_forward(rbffd_ctx *ctx, rbffd_closure *cl, const void *state, int64_
   const unsigned nb = static_cast<unsigned>(
       std::max<int64_t>(1, std::min<int64_t>(static_cast<int64_t>(ctx->n_cu) * per_cu, (units + sh.waves - 1) / sh.waves)));
   auto kern = cl->act == RBFFD_ACT_RELU ? mlp_kernel<SH, RBFFD_ACT_RELU>() : mlp_kernel<SH, RBFFD_ACT_TANH>();
-  kern<<<nb, 64 * sh.waves, MLP_LDS, ctx->stream>>>(static_cast<const float *>(state), cl->idx.as<int>(), m->Na, m->n,
+  kern<<<nb, 64 * sh.waves, MLP_LDS, ctx->stream>>>(static_cast<const float *>(state), cl->idx.as<int>(), m->Na,
                                                     m->E, cl->nodef.as<float>(), cl->inv_in, cl->frag.as<__bf16>(),
                                                     cl->params.as<float>(), cl->Yc.as<float>(), S);
 }
@@ -673,23 +894,15 @@ int closure_create(rbffd_ctx *ctx, rbffd_model *m, const rbffd_closure_desc *d, 
   cl->model = m;
   cl->act = d->activation;
   cl->max_s = d->max_samples;
-  cl->sp_max = (d->max_samples + 31) / 32 * 32;
   cl->inv_in = make_float4(1.0f / d->in_scale[0], 1.0f / d->in_scale[1], 1.0f / d->in_scale[2], 1.0f / d->in_scale[3]);
   cl->out_sc = make_float4(d->out_scale[0], d->out_scale[1], d->out_scale[2], d->out_scale[3]);
-  const size_t Sx = static_cast<size_t>(cl->max_s), Sp = static_cast<size_t>(cl->sp_max), b2 = 2;
+  const size_t Sx = static_cast<size_t>(cl->max_s), b2 = 2, n_cu = static_cast<size_t>(ctx->n_cu);
   bool ok = cl->params.alloc(4 * NPARAM) == hipSuccess && cl->grad.alloc(4 * NPARAM) == hipSuccess &&
             cl->m1.alloc(4 * NPARAM) == hipSuccess && cl->m2.alloc(4 * NPARAM) == hipSuccess &&
-            cl->nodef.alloc(4 * m->Na) == hipSuccess && cl->idx.alloc(4 * m->Na * m->n) == hipSuccess &&
+            cl->nodef.alloc(4 * m->Na) == hipSuccess && cl->idx.alloc(4 * m->Na * NGROUP) == hipSuccess &&
             cl->w1.alloc(b2 * HID * KIN) == hipSuccess && cl->w2.alloc(b2 * HID * HID) == hipSuccess &&
-            cl->w3.alloc(b2 * NOUT * HID) == hipSuccess && cl->w2t.alloc(b2 * HID * HID) == hipSuccess &&
-            cl->w3t.alloc(b2 * HID * 32) == hipSuccess && cl->X.alloc(b2 * Sx * KIN) == hipSuccess &&
-            cl->H1.alloc(b2 * Sx * HID) == hipSuccess && cl->H2.alloc(b2 * Sx * HID) == hipSuccess &&
-            cl->Y.alloc(4 * Sx * NOUT) == hipSuccess && cl->dY.alloc(b2 * Sx * 32) == hipSuccess &&
-            cl->dY32.alloc(4 * Sx * 4) == hipSuccess && cl->dH1.alloc(b2 * Sx * HID) == hipSuccess &&
-            cl->dH2.alloc(b2 * Sx * HID) == hipSuccess && cl->XT.alloc(b2 * KIN * Sp) == hipSuccess &&
-            cl->H1T.alloc(b2 * HID * Sp) == hipSuccess && cl->H2T.alloc(b2 * HID * Sp) == hipSuccess &&
-            cl->dH1T.alloc(b2 * HID * Sp) == hipSuccess && cl->dH2T.alloc(b2 * HID * Sp) == hipSuccess &&
-            cl->dYT.alloc(b2 * NOUT * Sp) == hipSuccess && cl->loss.alloc(8) == hipSuccess &&
+            cl->w3.alloc(b2 * NOUT * HID) == hipSuccess && cl->part.alloc(4 * NPARAM * n_cu) == hipSuccess &&
+            cl->part_loss.alloc(8 * n_cu) == hipSuccess && cl->loss.alloc(8) == hipSuccess &&
             cl->bad.alloc(4 * m->E) == hipSuccess && cl->frag.alloc(b2 * NFRAG * 512) == hipSuccess &&
             cl->Yc.alloc(4 * Sx * 4) == hipSuccess;
   if (!ok) {
@@ -700,28 +913,25 @@ int closure_create(rbffd_ctx *ctx, rbffd_model *m, const rbffd_closure_desc *d, 
   set_mlp_lds(lds_ok);
   if (!lds_ok) {
     delete cl;
-    return rbffd_fail(ctx, RBFFD_EDEVICE, "closure: LDS size of the fused forward kernel");
+    return rbffd_fail(ctx, RBFFD_EDEVICE, "closure: LDS size of the fused kernels");
   }
   hipStream_t s = ctx->stream;
   bool cp_ok = hipMemcpyAsync(cl->params.p, d->init_params, 4 * NPARAM, hipMemcpyDeviceToDevice, s) == hipSuccess &&
                hipMemsetAsync(cl->m1.p, 0, 4 * NPARAM, s) == hipSuccess &&
-               hipMemsetAsync(cl->m2.p, 0, 4 * NPARAM, s) == hipSuccess &&
-               hipMemsetAsync(cl->w3t.p, 0, b2 * HID * 32, s) == hipSuccess &&
-               hipMemsetAsync(cl->w3.p, 0, b2 * NOUT * HID, s) == hipSuccess;
+               hipMemsetAsync(cl->m2.p, 0, 4 * NPARAM, s) == hipSuccess;
   if (!cp_ok) {
     delete cl;
     return rbffd_fail(ctx, RBFFD_EDEVICE, "closure set-up copies");
   }
   f64_to_f32_kernel<<<grid_for(m->Na, 256), 256, 0, s>>>(d->node_feature, m->Na, cl->nodef.as<float>());
-  const int64_t cnt = m->Na * m->n;
-  const hipError_t e_idx = hipMemcpyAsync(cl->idx.p, m->idx_t.p, sizeof(int) * cnt, hipMemcpyDeviceToDevice, s);
+  gather_rows_fill_kernel<<<grid_for(m->Na * NGROUP, 256), 256, 0, s>>>(m->idx_t.as<int>(), m->Na, m->n, cl->idx.as<int>());
   repack(cl, s);
   const hipError_t e_launch = hipGetLastError();
   const hipError_t e_sync = hipStreamSynchronize(s);
-  if (e_idx != hipSuccess || e_launch != hipSuccess || e_sync != hipSuccess) {
+  if (e_launch != hipSuccess || e_sync != hipSuccess) {
     delete cl;
-    return rbffd_fail(ctx, RBFFD_EDEVICE, "closure set-up: index copy %s, launches %s, synchronisation %s",
-                      hipGetErrorString(e_idx), hipGetErrorString(e_launch), hipGetErrorString(e_sync));
+    return rbffd_fail(ctx, RBFFD_EDEVICE, "closure set-up: launches %s, synchronisation %s",
+                      hipGetErrorString(e_launch), hipGetErrorString(e_sync));
   }
   *out = cl;
   return RBFFD_OK;
@@ -785,8 +995,7 @@ int closure_tune(rbffd_ctx *ctx, rbffd_closure *cl, const void *state, int *chos
 int closure_gradient(rbffd_ctx *ctx, rbffd_closure *cl, const void *state, const float *target, float *grad,
                      double *loss) {
   const int64_t S = cl->model->Na * cl->model->E;
-  int rc = forward(ctx, cl, state, S);
-  if (!rc) rc = backward(ctx, cl, target, S);
+  int rc = gradient(ctx, cl, state, target, S);
   if (rc) return rc;
   if (grad) RBFFD_HIP(ctx, hipMemcpyAsync(grad, cl->grad.p, 4 * NPARAM, hipMemcpyDeviceToDevice, ctx->stream));
   RBFFD_HIP(ctx, hipMemcpyAsync(loss, cl->loss.p, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));

@@ -190,3 +190,57 @@ def test_learned_closure_beats_plain_coarse_run():
 
 
 import time  # noqa: E402
+
+
+@pytest.mark.parametrize("nx, nz, n, E, act", [(10, 5, 13, 1, OC.RELU),      # one tile of 64 samples, not full
+                                               (16, 4, 13, 1, OC.TANH),      # exactly one tile
+                                               (24, 9, 37, 77, OC.RELU),     # more tiles than compute units, a remainder
+                                               (24, 9, 21, 7, OC.TANH)])
+def test_closure_gradient_tile_edges(nx, nz, n, E, act):
+    """The fused training kernel at the edges of its 64-sample tiles and for
+    stencils shorter than 37, against the bfloat16-emulating oracle; the
+    padding parameters (nonzero here) get no gradient.
+
+    Bar: FP32 sums of up to 160 terms are off by at most 160 x 2^-24 of their
+    size, against a bfloat16 spacing of 2^-8, so about 1% of the stored values
+    at most round the other way, each by 2^-8: sqrt(0.01) 2^-8 = 4e-4 relative
+    l2 per layer, over three layers 1.2e-3."""
+    import torch
+    from paper_1509_02615_amd import rbffd as R
+    h = 1.0 / nx
+    i, j = np.meshgrid(np.arange(nx), np.arange(nz))
+    xy = np.stack([i.ravel() * h, j.ravel() * h], 1)
+    na = len(xy)
+    ghost = np.concatenate([xy[:nx] - [0.0, h], xy[-nx:] + [0.0, h]])
+    xy = np.concatenate([xy, ghost])
+    bnd = np.concatenate([np.arange(nx), na - nx + np.arange(nx)]).astype(np.int32)
+    ctx = R.Context(0)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()              # noqa: E731
+    ops = [(R.DX, 0, 0), (R.DZ, 0, 0), (R.LAP, 0, 0), (R.HYPERLAP, 3, 7)]
+    idx, W, _, _ = R.rbffd_weights(ctx, dev(xy), ops, n, 7, 2, period_x=1.0, n_centers=na)
+    _, Ww, _, _ = R.rbffd_weights(ctx, dev(xy), [(R.DZ, 0, 0), (R.DZZ, 0, 0)], n, 7, 2, period_x=1.0, centers=dev(bnd))
+    model = R.Model(ctx, R.PHYS_NS, idx, W, dev(xy), na, field_dtype=R.F32, weight_dtype=R.F32, ensemble=E,
+                    hv_coeff=0.0, consts=dict(c_p=1004.0, c_v=717.0, R_d=287.0, g=9.81, theta_bar=300.0, mu=75.0),
+                    bnd_nodes=dev(bnd), bnd_ghosts=dev((na + np.arange(2 * nx)).astype(np.int32)),
+                    bnd_normal=dev(np.zeros(2 * nx, np.int32)), bnd_d1=Ww[0].contiguous(), bnd_d2=Ww[1].contiguous())
+    rng = np.random.default_rng(7)
+    p = OC.init_params(seed=3)
+    for a, b in ((OC.OB1, OC.OW2), (OC.OB2, OC.OW3), (OC.OB3, OC.OB3 + 4)):
+        p[a:b] = rng.normal(0, 0.1, b - a)
+    state = (rng.normal(0, 1, (len(xy), E, 4)) * np.array(IN_SCALE)).astype(np.float32)
+    nodef = xy[:na, 1].astype(np.float32).astype(np.float64)
+    cl = R.Closure(ctx, model, dev(p), dev(nodef), IN_SCALE, OUT_SCALE, activation=act)
+    T = rng.normal(0, 1, (na * E, 4)).astype(np.float32)
+    g, loss = cl.gradient(dev(state), dev(T.reshape(na, E, 4)))
+    g = g.cpu().numpy().astype(np.float64)
+    X = OC.features(state.astype(np.float64), idx.cpu().numpy(), nodef, IN_SCALE)
+    loss_e, g_e = OC.loss_and_grad(p.astype(np.float64), X, T.astype(np.float64), emulate=True, act=act)
+    say(f"closure gradient, {na * E} samples, n = {n}: loss {loss:.8f} against {loss_e:.8f}")
+    assert abs(loss - loss_e) <= 1e-4 * loss_e
+    for name, a, b in BLOCKS:
+        say(f"   {name}: {_rel(g[a:b], g_e[a:b]):.2e}")
+        assert _rel(g[a:b], g_e[a:b]) < 1.2e-3, name
+    assert np.all(g[OC.OW1:OC.OB1].reshape(OC.HID, OC.KIN)[:, 149:] == 0.0)
+    assert np.all(g[OC.OW3 + 4 * OC.HID:OC.OB3] == 0.0) and np.all(g[OC.OB3 + 4:] == 0.0)
+    g2, loss2 = cl.gradient(dev(state), dev(T.reshape(na, E, 4)))
+    assert loss2 == loss and np.array_equal(g2.cpu().numpy().astype(np.float64), g)   # fixed summation order
