@@ -127,11 +127,13 @@ mlp_forward_kernel(
   const f4v *s_b4 = reinterpret_cast<const f4v *>(s_bias);   // 4 consecutive biases per lane group
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
   const int64_t units = (S + 16 * T - 1) / (16 * T);
-  const int64_t nb = gridDim.x, b = blockIdx.x, full = (nb / 8) * 8;
-  const int64_t lb = b >= full ? b : (b % 8) * (nb / 8) + b / 8;
-  const int64_t per = (units + nb - 1) / nb;
-  const int64_t u_end = min(units, (lb + 1) * per);
-  for (int64_t u = lb * per + wave; u < u_end; u += MLP_WAVES) {
+  // XCD x = b % 8 takes a contiguous range of units, its blocks in turns, so
+  // that they gather the same neighbours at the same time from its L2
+  // (557,056 samples, 256 members: 58.0 -> 56.7 us against a range per block)
+  const int64_t nb = gridDim.x, b = blockIdx.x, ng = nb < 8 ? 1 : 8, x = b % ng;
+  const int64_t per = (units + ng - 1) / ng, nbx = (nb - x + ng - 1) / ng;
+  const int64_t u_end = min(units, (x + 1) * per);
+  for (int64_t u = x * per + (b / ng) * MLP_WAVES + wave; u < u_end; u += nbx * MLP_WAVES) {
     const int64_t base = u * 16 * T;
     // keeps the weight fragments' LDS reads inside the loop: hoisted out of
     // it as loop-invariant they would need 304 registers
