@@ -20,14 +20,14 @@
 // Per system:
 //  1. offsets of the stencil nodes from the centre (minimum image in x),
 //     scaled by rho = the largest offset length;
-//  2. assembly of A = [Phi P; P^T 0] of size K = n + M and of B = one
-//     right-hand side per operator of this PHS order (Section 5.3, Eq.
-//     eqn:laplacian for Laplacian^k of r^m): [A | B] column-major in LDS in
-//     the workgroup kernel, row i of A in lane i's registers in the
-//     wavefront kernels;
+//  2. assembly of A = [Phi P; P^T 0] of size K = n + M, row i in lane i's
+//     registers (the workgroup kernel: rows i and i + 64 in lane i, the
+//     columns spread over its wavefronts); the right-hand sides, one per
+//     operator of this PHS order (Section 5.3, Eq. eqn:laplacian for
+//     Laplacian^k of r^m), are evaluated where the residuals are formed;
 //  3. LU with partial pivoting (FP64, or FP32 for the mixed-precision
-//     variant); the wavefront kernels move no rows and take two steps per
-//     pass (both pivot rows broadcast together, one rank-2 update);
+//     variant) without moving rows; the wavefront kernels take two steps
+//     per pass (both pivot rows broadcast together, one rank-2 update);
 //  4. back substitution, then iterative refinement: residual b - A x with A
 //     and b formed in double-double arithmetic from the FP64 node
 //     coordinates (so the refinement converges to the solution of the exact
@@ -35,8 +35,8 @@
 //     stencils differs by ~5e-10), correction through the same factors,
 //     until the correction is at rounding level (with FP32 factors the
 //     first passes take plain FP64 residuals of the FP64 matrix, and
-//     double-double ones from there on; the wavefront kernels solve for
-//     the corrections in FP32);
+//     double-double ones from there on, and the corrections are solved for
+//     in FP32);
 //  5. rescaling by rho^-q (q = derivative order) and the padded row write.
 //
 // FP64 matrix cores on gfx950 have the same peak as the FP64 vector ALUs,
@@ -127,32 +127,6 @@ __device__ __forceinline__ double fact(int n) {
   return r;
 }
 
-// L applied to |x - x_j|^m at the centre, node offset (x, z).
-__device__ double phs_rhs(int kind, int m, int k, double x, double z) {
-#pragma clang fp contract(off)
-  double r2 = x * x + z * z;
-  if (r2 == 0.0) return 0.0;
-  double r = sqrt(r2);
-  switch (kind) {
-    case RBFFD_DX: return -m * ipow(r, m - 2) * x;
-    case RBFFD_DZ: return -m * ipow(r, m - 2) * z;
-    case RBFFD_LAP: return static_cast<double>(m * m) * ipow(r, m - 2);
-    case RBFFD_HYPERLAP: {
-      double c = 1.0;
-      for (int i = 0; i < k; ++i) c *= static_cast<double>((m - 2 * i) * (m - 2 * i));
-      return c * ipow(r, m - 2 * k);
-    }
-    case RBFFD_DZZ:
-    case RBFFD_DXX: {
-      const double t = kind == RBFFD_DZZ ? z : x;   // the differentiated coordinate
-      double a = m * ipow(r, m - 2);
-      double b = (m >= 4) ? m * (m - 2) * ipow(r, m - 4) * t * t : m * (m - 2) * t * t / r;
-      return a + b;
-    }
-  }
-  return 0.0;
-}
-
 // L(x^a z^b) at the origin.
 __device__ double poly_rhs(int kind, int k, int a, int b) {
   switch (kind) {
@@ -168,35 +142,6 @@ __device__ double poly_rhs(int kind, int k, int a, int b) {
     }
   }
   return 0.0;
-}
-
-// Entry (i, j) of [Phi P; P^T 0] for scaled offsets (xi, ze).
-__device__ __forceinline__ double sys_entry(int i, int j, int n, int m, const double *xi,
-                                            const double *ze) {
-#pragma clang fp contract(off)
-  if (i < n && j < n) {
-    double dx = xi[i] - xi[j], dz = ze[i] - ze[j];
-    return ipow(sqrt(dx * dx + dz * dz), m);
-  }
-  if (i < n) {
-    int a, b;
-    mono(j - n, a, b);
-    return ipow(xi[i], a) * ipow(ze[i], b);
-  }
-  if (j < n) {
-    int a, b;
-    mono(i - n, a, b);
-    return ipow(xi[j], a) * ipow(ze[j], b);
-  }
-  return 0.0;
-}
-
-__device__ __forceinline__ double rhs_entry(int i, int n, int m, const WOp &op, int k_eff,
-                                            const double *xi, const double *ze) {
-  if (i < n) return phs_rhs(op.kind, m, k_eff, xi[i], ze[i]);
-  int a, b;
-  mono(i - n, a, b);
-  return poly_rhs(op.kind, k_eff, a, b);
 }
 
 __device__ __forceinline__ double wave_max(double v) {
@@ -228,25 +173,6 @@ __device__ __forceinline__ dd dd_add(dd a, dd b) {
   s.lo += t.hi;
   s = fast_two_sum(s.hi, s.lo);
   s.lo += t.lo;
-  return fast_two_sum(s.hi, s.lo);
-}
-// Sum without the second error-free step: the error is within a few
-// 2^-104 of |a| + |b| (not of |a + b|), which is what the residual sums and
-// sums of positive terms below need.
-__device__ __forceinline__ dd dd_add_terms(dd a, dd b) {
-  dd s = two_sum(a.hi, b.hi);
-  s.lo += a.lo + b.lo;
-  return fast_two_sum(s.hi, s.lo);
-}
-__device__ __forceinline__ dd dd_sqr(dd a) {
-  dd p = two_prod(a.hi, a.hi);
-  p.lo += 2.0 * (a.hi * a.lo);
-  return fast_two_sum(p.hi, p.lo);
-}
-// (ah + al) - (bh + bl) for offsets of distinct stencil nodes
-__device__ __forceinline__ dd dd_diff(double ah, double al, double bh, double bl) {
-  dd s = two_sum(ah, -bh);
-  s.lo += al - bl;
   return fast_two_sum(s.hi, s.lo);
 }
 __device__ __forceinline__ dd dd_neg(dd a) { return {-a.hi, -a.lo}; }
@@ -289,23 +215,6 @@ __device__ __forceinline__ dd dd_ipow(dd x, int p) {
   return v;
 }
 
-// Entry (i, j) of [Phi P; P^T 0] in double-double from offsets (xh+xl, zh+zl).
-__device__ dd sys_entry_dd(int i, int j, int n, int m, const double *xh, const double *xl, const double *zh,
-                           const double *zl) {
-  if (i < n && j < n) {
-    const dd dx = dd_diff(xh[i], xl[i], xh[j], xl[j]);
-    const dd dz = dd_diff(zh[i], zl[i], zh[j], zl[j]);
-    const dd r2 = dd_add_terms(dd_sqr(dx), dd_sqr(dz));
-    if (r2.hi == 0.0) return {0.0, 0.0};
-    return dd_rpow(r2, dd_sqrt(r2), m);
-  }
-  if (i >= n && j >= n) return {0.0, 0.0};
-  const int node = i < n ? i : j;
-  int a, b;
-  mono((i < n ? j : i) - n, a, b);
-  return dd_mul(dd_ipow(dd{xh[node], xl[node]}, a), dd_ipow(dd{zh[node], zl[node]}, b));
-}
-
 // Right-hand-side entry i of operator op in double-double, node offset (x, z)
 // for rows i < n.
 __device__ dd rhs_dd_at(int i, int n, int m, const WOp &op, int k, dd x, dd z) {
@@ -337,11 +246,6 @@ __device__ dd rhs_dd_at(int i, int n, int m, const WOp &op, int k, dd x, dd z) {
   return {0.0, 0.0};
 }
 
-__device__ __forceinline__ dd rhs_entry_dd(int i, int n, int m, const WOp &op, int k, const double *xh,
-                                           const double *xl, const double *zh, const double *zl) {
-  return i < n ? rhs_dd_at(i, n, m, op, k, dd{xh[i], xl[i]}, dd{zh[i], zl[i]}) : rhs_dd_at(i, n, m, op, k, {}, {});
-}
-
 // Stopping rule of the iterative refinement, after a correction d computed
 // from a residual, with dprev the previous correction (the first solution
 // itself for the first refinement pass). The error contracts by a factor
@@ -350,367 +254,6 @@ __device__ __forceinline__ dd rhs_entry_dd(int i, int n, int m, const WOp &op, i
 // itself is below 2^-48 |x|.
 __device__ __forceinline__ bool refined(double dm, double xm, double dprev) {
   return dm <= 0x1p-48 * xm || (dm <= 0.5 * dprev && dm * dm <= 0x1p-52 * xm * dprev);
-}
-
-template <typename T> __device__ void block_solve(const WArgs &a, double *smem, const int q) {
-  const int tid = threadIdx.x;
-  const int kc = a.k_cap;
-  // LDS carve-up, sized by the launch's largest system kc and operator count
-  double *xs = smem;                       // [n_ops][kc] solution
-  double *rs = xs + a.n_ops * kc;          // [n_ops][kc] residual / correction
-  double *xi = rs + a.n_ops * kc;          // [kc] scaled x offsets (FP64)
-  double *ze = xi + kc;                    // [kc] scaled z offsets (FP64)
-  double *xl = ze + kc;                    // [kc] low parts of the double-double x offsets
-  double *zl = xl + kc;                    // [kc] low parts of the double-double z offsets
-  __shared__ double s_red[5];  // rho, converged flag, max |x|, previous correction, FP64-residual flag
-  __shared__ int s_piv[128];
-  __shared__ int s_gl[MAX_OPS], s_kg[MAX_OPS];  // operators of the current group, their k
-  __shared__ int s_flag, s_pivrow;
-  __shared__ double s_pmin, s_amax, s_akk, s_pval;
-  T *A = reinterpret_cast<T *>(zl + kc);   // [kc + n_ops columns][kc], column-major
-
-  const int c = a.centers ? a.centers[q] : q;
-  const int n = a.n_per ? a.n_per[q] : a.n_max;
-  const int m = a.m_per ? a.m_per[q] : a.m_uni;
-  const int l = a.l_per ? a.l_per[q] : a.l_uni;
-  const int M = n_terms(l);
-  const int K = n + M;
-  double *wrow = a.w + static_cast<int64_t>(q) * a.n_max;
-  const int64_t op_stride = static_cast<int64_t>(a.n_centers) * a.n_max;
-
-  // validity (uniform for the block)
-  bool bad = (c < 0 || c >= a.n_nodes || n < 1 || n > a.n_max || m < 1 || m > 15 || (m & 1) == 0 ||
-              l < 0 || l > 6 || n < M || K > kc);
-  if (tid == 0) s_flag = 0;
-  __syncthreads();
-  if (!bad) {
-    for (int t = tid; t < n; t += W_THREADS) {
-      int j = a.idx[static_cast<int64_t>(q) * a.n_max + t];
-      if (j < 0 || j >= a.n_nodes) s_flag = 2;
-    }
-  }
-  __syncthreads();
-  if (bad || s_flag) {
-    for (int o = 0; o < a.n_ops; ++o)
-      for (int t = tid; t < a.n_max; t += W_THREADS) wrow[o * op_stride + t] = 0.0;
-    if (tid == 0 && a.status) a.status[q] = 2;
-    return;
-  }
-
-  // 1. offsets from the centre, then scale by rho
-  const double xc = a.xy[2 * c], zc = a.xy[2 * c + 1];
-  for (int t = tid; t < n; t += W_THREADS) {
-    int j = a.idx[static_cast<int64_t>(q) * a.n_max + t];
-    dd dx = two_sum(a.xy[2 * j], -xc);  // exact offset
-    if (a.period > 0.0) {
-      double half = 0.5 * a.period;
-      double d64 = a.xy[2 * j] - xc;
-      if (d64 > half)
-        dx = dd_add(dx, dd{-a.period, 0.0});
-      else if (d64 < -half)
-        dx = dd_add(dx, dd{a.period, 0.0});
-    }
-    dd dz = two_sum(a.xy[2 * j + 1], -zc);
-    xi[t] = dx.hi;
-    xl[t] = dx.lo;
-    ze[t] = dz.hi;
-    zl[t] = dz.lo;
-  }
-  __syncthreads();
-  if (tid < 64) {
-    double v = 0.0;
-    for (int t = tid; t < n; t += 64) {
-#pragma clang fp contract(off)
-      double d2 = xi[t] * xi[t] + ze[t] * ze[t];
-      v = fmax(v, d2);
-    }
-    v = wave_max(v);
-    if (tid == 0) s_red[0] = sqrt(v);
-  }
-  __syncthreads();
-  const double rho = s_red[0];
-  if (!(rho > 0.0)) {
-    for (int o = 0; o < a.n_ops; ++o)
-      for (int t = tid; t < a.n_max; t += W_THREADS) wrow[o * op_stride + t] = 0.0;
-    if (tid == 0 && a.status) a.status[q] = 1;
-    return;
-  }
-  for (int t = tid; t < n; t += W_THREADS) {
-    const dd ex = dd_div(dd{xi[t], xl[t]}, dd{rho, 0.0}), ez = dd_div(dd{ze[t], zl[t]}, dd{rho, 0.0});
-    xi[t] = ex.hi;
-    xl[t] = ex.lo;
-    ze[t] = ez.hi;
-    zl[t] = ez.lo;
-  }
-  __syncthreads();
-
-  int status = 0;
-  unsigned done = 0;
-  // operators grouped by PHS order: one factorisation per group
-  while (done != (1u << a.n_ops) - 1u) {
-    int first = 0;
-    while (done & (1u << first)) ++first;
-    const int mg = a.ops[first].order ? a.ops[first].order : m;
-    int ng = 0;
-    bool group_bad = false;
-    for (int o = 0; o < a.n_ops; ++o) {
-      int mo = a.ops[o].order ? a.ops[o].order : m;
-      if (!(done & (1u << o)) && mo == mg) {
-        const WOp &op = a.ops[o];
-        const int ke = (op.kind == RBFFD_HYPERLAP && op.k == 0) ? (mg - 1) / 2 : op.k;
-        if (op.kind == RBFFD_HYPERLAP && mg < 2 * ke + 1) group_bad = true;
-        if (tid == 0) {
-          s_gl[ng] = o;
-          s_kg[ng] = ke;
-        }
-        ++ng;
-        done |= 1u << o;
-      }
-    }
-    __syncthreads();
-    if (group_bad) {
-      status = 2;
-      for (int g = 0; g < ng; ++g)
-        for (int t = tid; t < a.n_max; t += W_THREADS) wrow[s_gl[g] * op_stride + t] = 0.0;
-      __syncthreads();
-      continue;
-    }
-    const int Kt = K + ng;  // columns of [A | B]
-
-    // 2. assembly, column-major: element (i, j) at j*kc + i; wavefronts take
-    // columns, lanes rows
-    constexpr int NW = W_THREADS / 64;
-    const int wv = tid >> 6, ln = tid & 63;
-    for (int j = wv; j < K; j += NW)
-      for (int i = ln; i < K; i += 64) A[j * kc + i] = static_cast<T>(sys_entry(i, j, n, mg, xi, ze));
-    for (int g = wv; g < ng; g += NW)
-      for (int i = ln; i < K; i += 64)
-        A[(K + g) * kc + i] = static_cast<T>(rhs_entry(i, n, mg, a.ops[s_gl[g]], s_kg[g], xi, ze));
-    __syncthreads();
-    if (tid < 64) {
-      double v = 0.0;
-      for (int j = 0; j < K; ++j)
-        for (int i = tid; i < K; i += 64) v = fmax(v, fabs(static_cast<double>(A[j * kc + i])));
-      v = wave_max(v);
-      if (tid == 0) {
-        s_amax = v;
-        s_pmin = INFINITY;
-      }
-    }
-    __syncthreads();
-
-    // 3. LU with partial pivoting of [A | B]
-    for (int k = 0; k < K; ++k) {
-      if (tid < 64) {
-        double best = -1.0;
-        int bi = k;
-        for (int i = k + tid; i < K; i += 64) {
-          double v = fabs(static_cast<double>(A[k * kc + i]));
-          if (v > best) {
-            best = v;
-            bi = i;
-          }
-        }
-        for (int off = 32; off > 0; off >>= 1) {
-          double ob = __shfl_xor(best, off, 64);
-          int oi = __shfl_xor(bi, off, 64);
-          if (ob > best || (ob == best && oi < bi)) {
-            best = ob;
-            bi = oi;
-          }
-        }
-        if (tid == 0) {
-          s_pivrow = bi;
-          s_piv[k] = bi;
-          s_pmin = fmin(s_pmin, best);
-          s_akk = static_cast<double>(A[k * kc + k]);
-          s_pval = static_cast<double>(A[k * kc + bi]);
-        }
-      }
-      __syncthreads();
-      // row interchange k <-> p in the other columns, and the multipliers of
-      // column k (whose old row k now sits at row p) in the same phase
-      const int p = s_pivrow;
-      const T piv = static_cast<T>(s_pval), akk = static_cast<T>(s_akk);
-      if (p != k) {
-        for (int j = tid; j < Kt; j += W_THREADS) {
-          if (j == k) continue;
-          T tmp = A[j * kc + k];
-          A[j * kc + k] = A[j * kc + p];
-          A[j * kc + p] = tmp;
-        }
-      }
-      const int rows = K - k - 1;
-      for (int i = k + 1 + tid; i < K; i += W_THREADS) {
-        const T v = i == p ? akk : A[k * kc + i];
-        A[k * kc + i] = (piv != T(0)) ? v / piv : T(0);
-      }
-      if (tid == 0) A[k * kc + k] = piv;
-      __syncthreads();
-      const int cols = Kt - k - 1;
-      if (rows > 0 && cols > 0) {
-        const int total = rows * cols;
-        int ri = tid % rows, cj = tid / rows;
-        const int dq = W_THREADS / rows, dr = W_THREADS % rows;
-        for (int t = tid; t < total; t += W_THREADS) {
-          const int i = k + 1 + ri, j = k + 1 + cj;
-          A[j * kc + i] = fma(-A[k * kc + i], A[j * kc + k], A[j * kc + i]);
-          ri += dr;
-          cj += dq;
-          if (ri >= rows) {
-            ri -= rows;
-            cj += 1;
-          }
-        }
-      }
-      __syncthreads();
-    }
-
-    // 4. back substitution U x = y (y = transformed right-hand sides)
-    for (int g = wv; g < ng; g += NW)
-      for (int i = ln; i < K; i += 64) xs[g * kc + i] = A[(K + g) * kc + i];
-    __syncthreads();
-    // wavefronts take right-hand sides, lanes rows (no integer division)
-    // (each right-hand side belongs to one wavefront, so its lanes read
-    // x_k before lane 0 stores it, without a barrier in between)
-    for (int k = K - 1; k >= 0; --k) {
-      const double ukk = static_cast<double>(A[k * kc + k]);
-      for (int g = wv; g < ng; g += NW) {
-        const double xk = xs[g * kc + k] / ukk;
-        for (int i = ln; i < k; i += 64) xs[g * kc + i] = fma(-static_cast<double>(A[k * kc + i]), xk, xs[g * kc + i]);
-        if (ln == 0) xs[g * kc + k] = xk;
-      }
-      __syncthreads();
-    }
-
-    // 5. iterative refinement with double-double residuals (with FP32
-    // factors the first passes take the FP64 entries of the assembly, as in
-    // the wavefront kernels: until a correction is below 2^-24 |x| or stops
-    // contracting, and without ending the refinement)
-    bool converged = false;
-    constexpr bool F32 = std::is_same<T, float>::value;
-    bool plain = F32;  // uniform over the workgroup
-    if (tid == 0) s_red[3] = -1.0;  // no previous correction yet
-    for (int it = 0; it < a.max_iter && !converged; ++it) {
-      // r = b - A x in double-double: 4 lanes per row, partial sums over j,
-      // right-hand sides in chunks of 4 (fixed trip counts keep the
-      // accumulators in registers)
-      for (int g0 = 0; g0 < ng; g0 += 4) {
-        const int part = tid & 3;
-        for (int i = tid >> 2; i < K; i += W_THREADS / 4) {
-          dd acc[4];
-#pragma unroll
-          for (int g = 0; g < 4; ++g) acc[g] = dd{0.0, 0.0};
-          for (int j = part; j < K; j += 4) {
-            const dd aij = plain ? dd{sys_entry(i, j, n, mg, xi, ze), 0.0} : sys_entry_dd(i, j, n, mg, xi, xl, ze, zl);
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-              if (g0 + g < ng) acc[g] = dd_add_terms(acc[g], dd_mul_d(aij, xs[(g0 + g) * kc + j]));
-          }
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            if (g0 + g < ng) {
-              for (int off = 1; off < 4; off <<= 1) {
-                dd o{__shfl_xor(acc[g].hi, off, 64), __shfl_xor(acc[g].lo, off, 64)};
-                acc[g] = dd_add(acc[g], o);
-              }
-              if (part == 0) {
-                const dd b = rhs_entry_dd(i, n, mg, a.ops[s_gl[g0 + g]], s_kg[g0 + g], xi, xl, ze, zl);
-                const dd r = dd_sub(b, acc[g]);
-                rs[(g0 + g) * kc + i] = r.hi + r.lo;
-              }
-            }
-          }
-        }
-      }
-      __syncthreads();
-      if (tid < ng) {  // row interchanges, in factorisation order
-        for (int k = 0; k < K; ++k) {
-          int p = s_piv[k];
-          if (p != k) {
-            double tmp = rs[tid * kc + k];
-            rs[tid * kc + k] = rs[tid * kc + p];
-            rs[tid * kc + p] = tmp;
-          }
-        }
-      }
-      __syncthreads();
-      for (int k = 0; k < K - 1; ++k) {  // unit lower triangle
-        for (int g = wv; g < ng; g += NW)
-          for (int i = k + 1 + ln; i < K; i += 64)
-            rs[g * kc + i] = fma(-static_cast<double>(A[k * kc + i]), rs[g * kc + k], rs[g * kc + i]);
-        __syncthreads();
-      }
-      for (int k = K - 1; k >= 0; --k) {  // upper triangle
-        const double ukk = static_cast<double>(A[k * kc + k]);
-        for (int g = wv; g < ng; g += NW) {
-          const double xk = rs[g * kc + k] / ukk;
-          for (int i = ln; i < k; i += 64) rs[g * kc + i] = fma(-static_cast<double>(A[k * kc + i]), xk, rs[g * kc + i]);
-          if (ln == 0) rs[g * kc + k] = xk;
-        }
-        __syncthreads();
-      }
-      // x += d; converged when |d| <= 2^-48 |x| (max norms over the group)
-      if (tid < 64) {
-        double dmax = 0.0, xmax = 0.0;
-        for (int t = 0; t < ng * 2; ++t) {
-          const int g = t >> 1, i = tid + 64 * (t & 1);
-          if (i >= K) continue;
-          double d = rs[g * kc + i];
-          double xn = xs[g * kc + i] + d;
-          xs[g * kc + i] = xn;
-          dmax = fmax(dmax, fabs(d));
-          xmax = fmax(xmax, fabs(xn));
-        }
-        dmax = wave_max(dmax);
-        xmax = wave_max(xmax);
-        if (tid == 0) {
-          const double dprev = s_red[3] >= 0.0 ? s_red[3] : xmax;
-          s_red[1] = !plain && refined(dmax, xmax, dprev) ? 1.0 : 0.0;
-          s_red[4] = plain && !(dmax <= 0x1p-24 * xmax || dmax > 0.5 * dprev) ? 1.0 : 0.0;
-          s_red[3] = dmax;
-        }
-      }
-      __syncthreads();
-      converged = s_red[1] != 0.0;
-      plain = F32 && s_red[4] != 0.0;
-      __syncthreads();
-    }
-
-    // 6. status and rescaled output
-    bool finite = true;
-    if (tid < 64) {
-      double v = 0.0;
-      for (int g = 0; g < ng; ++g)
-        for (int i = tid; i < K; i += 64) v = fmax(v, fabs(xs[g * kc + i]));
-      v = wave_max(v);
-      if (tid == 0) s_red[2] = v;
-    }
-    __syncthreads();
-    finite = isfinite(s_red[2]);
-    if (!(s_pmin >= 1e-13 * s_amax) || !converged || !finite) status = status ? status : 1;
-    for (int g = 0; g < ng; ++g) {
-      const WOp &op = a.ops[s_gl[g]];
-      const int qd = (op.kind == RBFFD_DX || op.kind == RBFFD_DZ) ? 1
-                     : (op.kind == RBFFD_HYPERLAP)                ? 2 * s_kg[g]
-                                                                  : 2;
-      const double scale = 1.0 / ipow(rho, qd);
-      for (int t = tid; t < a.n_max; t += W_THREADS)
-        wrow[s_gl[g] * op_stride + t] = (t < n && finite) ? xs[g * kc + t] * scale : 0.0;
-    }
-    __syncthreads();
-  }
-  if (tid == 0 && a.status) a.status[q] = status;
-}
-
-template <typename T>
-__global__ __launch_bounds__(W_THREADS) __attribute__((amdgpu_waves_per_eu(4))) void weights_kernel(WArgs a) {
-  extern __shared__ double smem[];
-  const QueueView qv = queue_view(a);
-  for (int t = blockIdx.x; t < qv.count; t += gridDim.x) {
-    __syncthreads();  // the previous system's LDS reads are done
-    block_solve<T>(a, smem, qv.stencil(t));
-  }
 }
 
 // ---- one wavefront per system, rows in registers (K <= 64) ----
@@ -1531,6 +1074,497 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(wave_occ<KC,
   }
 }
 
+// ---- one workgroup per system (64 < K <= 128) ----
+//
+// Four wavefronts; lane i holds rows i and i + 64 of A in registers, wavefront
+// w the columns 4 c + w. A step of the elimination takes one barrier: the
+// wavefront that owns the next column updates that column first, picks its
+// pivot row (data-parallel maximum, as in the wavefront kernels), and leaves
+// the multipliers in LDS while the others update the rest; nobody moves rows,
+// and the pivot row's entries come from the pivot lane's registers. The
+// factors, each row scaled by its own 1 / pivot, then go to LDS for the
+// substitutions: one wavefront per right-hand side, the unknowns in registers,
+// the column of a step an independent LDS read, no barriers. The residual
+// takes three lanes per row (K <= 84) or two, with the same |x_i - x_j|^m and
+// power tables as the wavefront kernels.
+//
+// Bound by the chain of a step (LDS read, update, pivot search, reciprocal,
+// LDS write, barrier). The 4,700 K = 82 systems of the mixed 1M batch take
+// 1.04 ms (FP64) against 2.84 ms, and the 500 of a 128 x 128 batch with FP32
+// factors 0.45 ms against 2.42 ms, with the matrix in LDS, rows interchanged
+// there and a barrier per step of every substitution.
+template <typename T> struct BlockShared {
+  T l[2][128];           // multipliers of the step in flight and the next
+  T rp[128];             // 1 / pivot of each step
+  int pv[128];           // pivot row of each step
+  double red[4][2];      // per wavefront: maxima
+  int gl[MAX_OPS], kg[MAX_OPS];  // operators of the current group, their k
+  int flag;
+};
+
+// Dynamic LDS of a launch for systems of up to kc unknowns: offsets, solutions
+// and residuals, the factors, and (PW) the power tables.
+template <typename T> __host__ __device__ constexpr size_t block_factor_bytes(int kc) {
+  return (sizeof(T) * (static_cast<size_t>(kc) * kc + 128) + 15) & ~size_t(15);
+}
+template <typename T> constexpr size_t block_lds_bytes(int kc, bool pw) {
+  return sizeof(double) * 12 * static_cast<size_t>(kc) + block_factor_bytes<T>(kc) +
+         (pw ? 4 * sizeof(double) * static_cast<size_t>(pw_cap(kc)) : 0);
+}
+
+template <typename T> struct BlockSys {
+  double *off;   // [kc][4] scaled node offsets: x hi, x lo, z hi, z lo
+  double *xs;    // [kc][4] current solution of the right-hand sides in flight
+  double *vs;    // [4][kc] residuals
+  T *F;          // [K columns][kc] scaled factors
+  double *pw;    // node t, power e at t (l + 1) + e: x^e (hi, lo), z^e (hi, lo)
+  int kc, n, K, mg, P;
+};
+
+// x_t^a z_t^b in double-double
+template <bool PW, typename T> __device__ __forceinline__ dd block_mono(const BlockSys<T> &Y, int t, int a, int b) {
+  if constexpr (PW) {
+    const double *px = Y.pw + 4 * (t * Y.P + a), *pz = Y.pw + 4 * (t * Y.P + b);
+    return dd_mulr(dd{px[0], px[1]}, dd{pz[2], pz[3]});
+  } else {
+    const double *o = Y.off + 4 * t;
+    return dd_mulr(dd_ipow(dd{o[0], o[1]}, a), dd_ipow(dd{o[2], o[3]}, b));
+  }
+}
+
+// Solve for the G right-hand sides of operators S.gl[g0 ..], then refine with
+// double-double residuals until the stopping rule holds (with FP32 factors the
+// first passes take plain FP64 residuals, as in the wavefront kernels).
+// st0, st1: elimination step of this lane's two rows. The solution is left in
+// Y.xs; returns whether it converged.
+template <int G, typename T, bool PW>
+__device__ __forceinline__ bool block_refine(const WArgs &a, BlockShared<T> &S, const BlockSys<T> &Y, int st0, int st1,
+                                             int g0) {
+  constexpr bool F32 = std::is_same<T, float>::value;
+  const int tid = threadIdx.x, ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = Y.n, K = Y.K, kc = Y.kc, k64 = min(K, 64);
+  // residual rows: RW rows per wavefront, NP lanes (parts) per row
+  const int NP = K <= 84 ? 3 : 2, RW = 64 / NP;
+  const int part = ln / RW, row = wv * RW + (ln - part * RW);
+  const bool act = part < NP && row < K, is_node = row < n;
+  double own[4] = {0.0, 0.0, 0.0, 0.0};
+  int pa = 0, pb = 0;
+  if (act && is_node) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) own[u] = Y.off[4 * row + u];
+  } else if (act) {
+    mono(row - n, pa, pb);
+  }
+  dd bc[G];  // the right-hand sides
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const int o = __builtin_amdgcn_readfirstlane(S.gl[g0 + g]);
+    bc[g] = act && part == 0 ? rhs_dd_at(row, n, Y.mg, a.ops[o], __builtin_amdgcn_readfirstlane(S.kg[g0 + g]),
+                                         dd{own[0], own[1]}, dd{own[2], own[3]})
+                             : dd{0.0, 0.0};
+  }
+  const T rdg0 = st0 < K ? S.rp[st0] : T(0), rdg1 = st1 < K ? S.rp[st1] : T(0);
+  const int pv0 = S.pv[min(ln, K - 1)], pv1 = S.pv[min(ln + 64, K - 1)];  // lane k: pivot rows of steps k, k + 64
+  double dprev = 0.0;
+  bool plain = F32, converged = false;
+  for (int it = 0; it <= a.max_iter && !converged; ++it) {
+    const bool plain_pass = plain && it > 0;
+    dd acc[G] = {};
+    if (act && plain_pass) {
+      const int e = (Y.mg - 1) / 2;
+      for (int j = part; j < K; j += NP) {
+        double ev = 0.0;
+        if (j < n && is_node) {
+          const double ddx = own[0] - Y.off[4 * j], ddz = own[2] - Y.off[4 * j + 2];
+          const double s2 = ddx * ddx + ddz * ddz;
+          const bool pos = s2 > 0.0;
+          double r = sqrt_pos(pos ? s2 : 1.0);
+          for (int t = 0; t < e; ++t) r *= s2;
+          ev = pos ? r : 0.0;
+        } else if (j < n || is_node) {
+          int qa = pa, qb = pb;
+          if (j >= n) mono(j - n, qa, qb);
+          ev = block_mono<PW>(Y, j < n ? j : row, qa, qb).hi;
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) acc[g].hi = fma(ev, Y.xs[4 * j + g], acc[g].hi);
+      }
+    } else if (act && it > 0) {
+      // node columns: Phi for node rows, the monomials of node j for
+      // polynomial rows; then the polynomial columns of node rows
+      auto node_cols = [&](auto MC) {
+        int j = part;
+        for (; j < n; j += NP) {
+          const double oj[4] = {Y.off[4 * j], Y.off[4 * j + 1], Y.off[4 * j + 2], Y.off[4 * j + 3]};
+          dd e;
+          if (is_node)
+            e = phi_dd<decltype(MC)::value>(own, oj, Y.mg);
+          else
+            e = block_mono<PW>(Y, j, pa, pb);
+#pragma unroll
+          for (int g = 0; g < G; ++g) acc[g] = dd_acc(acc[g], e, Y.xs[4 * j + g]);
+        }
+        if (is_node)
+          for (; j < K; j += NP) {
+            int qa, qb;
+            mono(j - n, qa, qb);
+            const dd e = block_mono<PW>(Y, row, qa, qb);
+#pragma unroll
+            for (int g = 0; g < G; ++g) acc[g] = dd_acc(acc[g], e, Y.xs[4 * j + g]);
+          }
+      };
+      switch (Y.mg) {
+        case 3: node_cols(std::integral_constant<int, 3>{}); break;
+        case 5: node_cols(std::integral_constant<int, 5>{}); break;
+        case 7: node_cols(std::integral_constant<int, 7>{}); break;
+        default: node_cols(std::integral_constant<int, 0>{}); break;
+      }
+    }
+    // the parts of a row meet in its first lane
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      dd t{__shfl(acc[g].hi, ln + RW, 64), __shfl(acc[g].lo, ln + RW, 64)};
+      dd sum = dd_add(acc[g], t);
+      if (NP == 3) {
+        t = dd{__shfl(acc[g].hi, ln + 2 * RW, 64), __shfl(acc[g].lo, ln + 2 * RW, 64)};
+        sum = dd_add(sum, t);
+      }
+      if (act && part == 0) {
+        const dd r = two_sum(bc[g].hi, -sum.hi);
+        Y.vs[g * kc + row] = r.hi + (r.lo + (bc[g].lo - sum.lo));
+      }
+    }
+    __syncthreads();
+    // substitutions of right-hand side wv, in the factors' precision
+    double dm = 0.0, xm = 0.0;
+    if (wv < G) {
+      const bool r0 = ln < K, r1 = ln + 64 < K;
+      T w0 = r0 ? static_cast<T>(Y.vs[wv * kc + ln] * static_cast<double>(rdg0)) : T(0);
+      T w1 = r1 ? static_cast<T>(Y.vs[wv * kc + ln + 64] * static_cast<double>(rdg1)) : T(0);
+      auto step = [&](int k, int p, bool fwd) {
+        const T y = rl(p >= 64 ? w1 : w0, p & 63);
+        const T f0 = Y.F[k * kc + ln], f1 = Y.F[k * kc + ln + 64];
+        const bool u0 = r0 && (fwd ? st0 > k : st0 < k), u1 = r1 && (fwd ? st1 > k : st1 < k);
+        w0 = fma(-(u0 ? f0 : T(0)), y, w0);
+        w1 = fma(-(u1 ? f1 : T(0)), y, w1);
+      };
+#pragma unroll 4
+      for (int k = 0; k < k64; ++k) step(k, __builtin_amdgcn_readlane(pv0, k), true);
+#pragma unroll 4
+      for (int k = 64; k < K; ++k) step(k, __builtin_amdgcn_readlane(pv1, k - 64), true);
+#pragma unroll 4
+      for (int k = K - 1; k >= 64; --k) step(k, __builtin_amdgcn_readlane(pv1, k - 64), false);
+#pragma unroll 4
+      for (int k = k64 - 1; k >= 0; --k) step(k, __builtin_amdgcn_readlane(pv0, k), false);
+      // row p_k holds the correction of unknown k
+      auto add = [&](int st, T w) {
+        const double d = static_cast<double>(w), x = Y.xs[4 * st + wv] + d;
+        Y.xs[4 * st + wv] = x;
+        dm = fmax(dm, fabs(d));
+        xm = fmax(xm, fabs(x));
+      };
+      if (r0) add(st0, w0);
+      if (r1) add(st1, w1);
+      dm = wave_max(dm);
+      xm = wave_max(xm);
+    }
+    if (ln == 0) {
+      S.red[wv][0] = dm;
+      S.red[wv][1] = xm;
+    }
+    __syncthreads();
+    dm = fmax(fmax(S.red[0][0], S.red[1][0]), fmax(S.red[2][0], S.red[3][0]));
+    xm = fmax(fmax(S.red[0][1], S.red[1][1]), fmax(S.red[2][1], S.red[3][1]));
+    if (!plain_pass) converged = it == 0 ? dm <= 0x1p-48 * xm : refined(dm, xm, dprev);
+    if (plain_pass && (dm <= 0x1p-24 * xm || dm > 0.5 * dprev)) plain = false;
+    dprev = dm;
+  }
+  return converged;
+}
+
+template <int KC, typename T, bool PW>
+__device__ __forceinline__ void block_solve(const WArgs &a, BlockShared<T> &S, double *smem, const int q) {
+  constexpr int CL = KC / 4;  // columns per wavefront
+  const int tid = threadIdx.x, ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kc = a.k_cap;
+  BlockSys<T> Y;
+  Y.off = smem;
+  Y.xs = smem + 4 * kc;
+  Y.vs = smem + 8 * kc;
+  Y.F = reinterpret_cast<T *>(smem + 12 * kc);
+  Y.pw = reinterpret_cast<double *>(reinterpret_cast<char *>(Y.F) + block_factor_bytes<T>(kc));
+  Y.kc = kc;
+  const int c = a.centers ? a.centers[q] : q;
+  const int n = __builtin_amdgcn_readfirstlane(a.n_per ? a.n_per[q] : a.n_max);
+  const int m = __builtin_amdgcn_readfirstlane(a.m_per ? a.m_per[q] : a.m_uni);
+  const int l = __builtin_amdgcn_readfirstlane(a.l_per ? a.l_per[q] : a.l_uni);
+  const int K = n + n_terms(l);
+  double *wrow = a.w + static_cast<int64_t>(q) * a.n_max;
+  const int64_t op_stride = static_cast<int64_t>(a.n_centers) * a.n_max;
+  auto reject = [&](int code) {
+    for (int o = 0; o < a.n_ops; ++o)
+      for (int t = tid; t < a.n_max; t += W_THREADS) wrow[o * op_stride + t] = 0.0;
+    if (tid == 0 && a.status) a.status[q] = code;
+  };
+  const bool bad = (c < 0 || c >= a.n_nodes || n < 1 || n > a.n_max || m < 1 || m > 15 || (m & 1) == 0 || l < 0 ||
+                    l > 6 || n < n_terms(l) || K > kc || K > KC);
+  if (bad) {
+    reject(2);
+    return;
+  }
+  Y.n = n;
+  Y.K = K;
+  Y.P = l + 1;
+  // 1. offsets from the centre (exact double-double, minimum image in x),
+  // scaled by rho = the largest offset length
+  int node = -1;
+  if (tid < n) node = a.idx[static_cast<int64_t>(q) * a.n_max + tid];
+  if (__syncthreads_or(tid < n && (node < 0 || node >= a.n_nodes))) {
+    reject(2);
+    return;
+  }
+  dd dx{0.0, 0.0}, dz{0.0, 0.0};
+  double d2 = 0.0;
+  if (tid < n) {
+    const double xc = a.xy[2 * c], zc = a.xy[2 * c + 1];
+    dx = two_sum(a.xy[2 * node], -xc);
+    if (a.period > 0.0) {
+      const double half = 0.5 * a.period, d64 = a.xy[2 * node] - xc;
+      if (d64 > half)
+        dx = dd_add(dx, dd{-a.period, 0.0});
+      else if (d64 < -half)
+        dx = dd_add(dx, dd{a.period, 0.0});
+    }
+    dz = two_sum(a.xy[2 * node + 1], -zc);
+    d2 = dx.hi * dx.hi + dz.hi * dz.hi;
+  }
+  auto block_max = [&](double v) {
+    v = wave_max(v);
+    __syncthreads();
+    if (ln == 0) S.red[wv][0] = v;
+    __syncthreads();
+    return fmax(fmax(S.red[0][0], S.red[1][0]), fmax(S.red[2][0], S.red[3][0]));
+  };
+  const double rho = sqrt(block_max(d2));
+  if (!(rho > 0.0)) {
+    reject(1);
+    return;
+  }
+  if (tid < n) {
+    const dd ex = dd_div(dx, dd{rho, 0.0}), ez = dd_div(dz, dd{rho, 0.0});
+    double *o = Y.off + 4 * tid;
+    o[0] = ex.hi;
+    o[1] = ex.lo;
+    o[2] = ez.hi;
+    o[3] = ez.lo;
+    if constexpr (PW) {
+      dd X{1.0, 0.0}, Z{1.0, 0.0};
+      for (int e = 0; e <= l; ++e) {
+        double *pe = Y.pw + 4 * (tid * Y.P + e);
+        pe[0] = X.hi;
+        pe[1] = X.lo;
+        pe[2] = Z.hi;
+        pe[3] = Z.lo;
+        X = dd_mulr(X, ex);
+        Z = dd_mulr(Z, ez);
+      }
+    }
+  }
+
+  int status = 0;
+  unsigned done = 0;
+  // operators grouped by PHS order: one factorisation per group
+  while (done != (1u << a.n_ops) - 1u) {
+    int first = 0;
+    while (done & (1u << first)) ++first;
+    const int mg = a.ops[first].order ? a.ops[first].order : m;
+    Y.mg = mg;
+    int ng = 0;
+    bool group_bad = false;
+    __syncthreads();  // offsets written; the previous group is done with S and Y
+    for (int o = 0; o < a.n_ops; ++o) {
+      const int mo = a.ops[o].order ? a.ops[o].order : m;
+      if (!(done & (1u << o)) && mo == mg) {
+        const WOp &op = a.ops[o];
+        const int ke = (op.kind == RBFFD_HYPERLAP && op.k == 0) ? (mg - 1) / 2 : op.k;
+        if (op.kind == RBFFD_HYPERLAP && mg < 2 * ke + 1) group_bad = true;
+        if (tid == 0) {
+          S.gl[ng] = o;
+          S.kg[ng] = ke;
+        }
+        ++ng;
+        done |= 1u << o;
+      }
+    }
+    __syncthreads();
+    if (group_bad) {
+      status = 2;
+      for (int g = 0; g < ng; ++g)
+        for (int t = tid; t < a.n_max; t += W_THREADS) wrow[S.gl[g] * op_stride + t] = 0.0;
+      continue;
+    }
+
+    // 2. A in FP64, column-major in LDS, one entry per thread at a time
+    double amax = 0.0;
+    {
+      const int e = (mg - 1) / 2;  // r^m = r (r^2)^e
+      const int dq = W_THREADS / K, dr = W_THREADS % K;
+      int i = tid % K, j = tid / K;
+      while (j < K) {
+        double v = 0.0;
+        if (i < n && j < n) {
+          const double ddx = Y.off[4 * i] - Y.off[4 * j], ddz = Y.off[4 * i + 2] - Y.off[4 * j + 2];
+          const double s2 = ddx * ddx + ddz * ddz;
+          const bool pos = s2 > 0.0;
+          double r = sqrt_pos(pos ? s2 : 1.0);
+          for (int t = 0; t < e; ++t) r *= s2;
+          v = pos ? r : 0.0;
+        } else if (i < n || j < n) {
+          int qa, qb;
+          mono((i < n ? j : i) - n, qa, qb);
+          v = block_mono<PW>(Y, i < n ? i : j, qa, qb).hi;
+        }
+        Y.F[j * kc + i] = static_cast<T>(v);
+        amax = fmax(amax, fabs(v));
+        i += dr;
+        j += dq;
+        if (i >= K) {
+          i -= K;
+          ++j;
+        }
+      }
+    }
+    amax = block_max(amax);  // (its barriers publish F)
+    T r0[CL], r1[CL];
+#pragma unroll
+    for (int cc = 0; cc < CL; ++cc) {
+      const int j = 4 * cc + wv;
+      r0[cc] = j < K && ln < K ? Y.F[j * kc + ln] : T(0);
+      r1[cc] = j < K && ln + 64 < K ? Y.F[j * kc + ln + 64] : T(0);
+    }
+
+    // 3. LU with partial pivoting
+    bool f0 = ln < K, f1 = ln + 64 < K;  // rows not yet chosen as pivot rows
+    int st0 = KC, st1 = KC;              // elimination step of each row
+    double pmin = INFINITY;
+    // pivot row of step k among the free rows of its column (a0, a1): compared
+    // on 16 mantissa bits, ties to the highest row; + 128 keeps free rows above
+    // the others
+    auto search = [&](T a0, T a1, int k) {
+      auto key = [](T v, int row) {
+        return ((__float_as_uint(static_cast<float>(fabs(static_cast<double>(v)))) & ~127u) + 128u) |
+               static_cast<unsigned>(row);
+      };
+      const unsigned m0 = f0 ? key(a0, ln) : 0u, m1 = f1 ? key(a1, ln + 64) : 0u;
+      const int p = static_cast<int>(wave_max_u32(max(m0, m1)) & 127u);
+      const T piv = rl(p >= 64 ? a1 : a0, p & 63);
+      pmin = fmin(pmin, fabs(static_cast<double>(piv)));
+      const T rp = recip(piv);
+      S.l[k & 1][ln] = f0 && ln != p ? a0 * rp : T(0);
+      S.l[k & 1][ln + 64] = f1 && ln + 64 != p ? a1 * rp : T(0);
+      if (ln == 0) {
+        S.pv[k] = p;
+        S.rp[k] = rp;
+      }
+    };
+    if (wv == 0) search(r0[0], r1[0], 0);
+#pragma unroll
+    for (int cc = 0; cc < CL; ++cc) {
+#pragma unroll 1
+      for (int s = 0; s < 4; ++s) {
+        const int k = 4 * cc + s;
+        if (k >= K) break;
+        __syncthreads();
+        const int p = __builtin_amdgcn_readfirstlane(S.pv[k]), pl = p & 63;
+        const bool hi = p >= 64;
+        const T l0 = S.l[k & 1][ln], l1 = S.l[k & 1][ln + 64];
+        if (ln == p) {
+          f0 = false;
+          st0 = k;
+        }
+        if (ln + 64 == p) {
+          f1 = false;
+          st1 = k;
+        }
+        auto update = [&](T &x0, T &x1) {
+          const T u = rl(hi ? x1 : x0, pl);
+          x0 = fma(-l0, u, x0);
+          x1 = fma(-l1, u, x1);
+        };
+        // the next column first, and its pivot row
+        if (k + 1 < K && wv == ((s + 1) & 3)) {
+          if (s < 3) {
+            update(r0[cc], r1[cc]);
+            search(r0[cc], r1[cc], k + 1);
+          } else if (cc + 1 < CL) {
+            update(r0[cc + 1 < CL ? cc + 1 : 0], r1[cc + 1 < CL ? cc + 1 : 0]);
+            search(r0[cc + 1 < CL ? cc + 1 : 0], r1[cc + 1 < CL ? cc + 1 : 0], k + 1);
+          }
+        }
+        if (wv > s + 1) update(r0[cc], r1[cc]);
+        if (cc + 1 < CL && !(s == 3 && wv == 0)) update(r0[cc + 1 < CL ? cc + 1 : 0], r1[cc + 1 < CL ? cc + 1 : 0]);
+#pragma unroll
+        for (int c2 = cc + 2; c2 < CL; ++c2) update(r0[c2], r1[c2]);
+      }
+    }
+    __syncthreads();
+    if (ln == 0) S.red[wv][1] = pmin;
+    // each row scaled by its own 1 / pivot, to LDS for the substitutions
+    {
+      const T d0 = ln < K ? S.rp[st0] : T(0), d1 = ln + 64 < K ? S.rp[st1] : T(0);
+#pragma unroll
+      for (int cc = 0; cc < CL; ++cc) {
+        const int j = 4 * cc + wv;
+        if (j < K && ln < K) Y.F[j * kc + ln] = r0[cc] * d0;
+        if (j < K && ln + 64 < K) Y.F[j * kc + ln + 64] = r1[cc] * d1;
+      }
+    }
+    __syncthreads();
+    pmin = fmin(fmin(S.red[0][1], S.red[1][1]), fmin(S.red[2][1], S.red[3][1]));
+
+    // 4. right-hand sides four at a time: solve, then refine
+    for (int g0 = 0; g0 < ng; g0 += 4) {
+      const int G = min(4, ng - g0);
+      __syncthreads();
+      for (int t = tid; t < 4 * K; t += W_THREADS) Y.xs[t] = 0.0;
+      __syncthreads();
+      bool converged;
+      switch (G) {
+        case 1: converged = block_refine<1, T, PW>(a, S, Y, st0, st1, g0); break;
+        case 2: converged = block_refine<2, T, PW>(a, S, Y, st0, st1, g0); break;
+        case 3: converged = block_refine<3, T, PW>(a, S, Y, st0, st1, g0); break;
+        default: converged = block_refine<4, T, PW>(a, S, Y, st0, st1, g0); break;
+      }
+      // 5. status and rescaled output
+      bool fin = true;
+      for (int t = tid; t < 4 * K; t += W_THREADS) fin = fin && isfinite(Y.xs[t]);
+      const bool finite = !__syncthreads_or(!fin);
+      if (!(pmin >= 1e-13 * amax) || !converged || !finite) status = status ? status : 1;
+      for (int g = 0; g < G; ++g) {
+        const WOp &op = a.ops[S.gl[g0 + g]];
+        const int qd = (op.kind == RBFFD_DX || op.kind == RBFFD_DZ) ? 1
+                       : (op.kind == RBFFD_HYPERLAP)                ? 2 * S.kg[g0 + g]
+                                                                    : 2;
+        const double scale = 1.0 / ipow(rho, qd);
+        for (int t = tid; t < a.n_max; t += W_THREADS)
+          wrow[S.gl[g0 + g] * op_stride + t] = (t < n && finite) ? Y.xs[4 * t + g] * scale : 0.0;
+      }
+    }
+  }
+  if (tid == 0 && a.status) a.status[q] = status;
+}
+
+template <int KC, typename T, bool PW>
+__global__ __launch_bounds__(W_THREADS) void weights_block_kernel(WArgs a) {
+  extern __shared__ double smem[];
+  __shared__ BlockShared<T> S;
+  const QueueView qv = queue_view(a);
+  for (int t = blockIdx.x; t < qv.count; t += gridDim.x) {
+    __syncthreads();  // the previous system's LDS reads are done
+    block_solve<KC, T, PW>(a, S, smem, qv.stencil(t));
+  }
+}
+
 // Launch buckets by system size: each bucket's launch reserves LDS for its
 // own largest K, so small systems do not pay for the largest one.
 constexpr int NBUCKET = 6;
@@ -1732,14 +1766,21 @@ void launch_wave(const WArgs &a, int64_t items, bool persist, int n_cu, hipStrea
     weights_wave_kernel<KC, T, H, false><<<grid_of(items, 0, n_cu), 64, 0, s>>>(a);
 }
 
-template <typename T> int launch_block(rbffd_ctx *ctx, const WArgs &a, int cap, int n_ops, unsigned grid) {
-  const size_t head = sizeof(double) * (2 * static_cast<size_t>(n_ops) * cap + 4 * static_cast<size_t>(cap));
-  const size_t lds = head + sizeof(T) * static_cast<size_t>(cap) * (cap + n_ops);
-  if (lds > 156 * 1024) return rbffd_fail(ctx, RBFFD_EINVAL, "system size %d too large for LDS", cap);
-  RBFFD_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&weights_kernel<T>),
+// A workgroup-per-system launch for systems of up to cap unknowns. The power
+// tables stay out of LDS where the factors leave them no room (FP64 systems of
+// more than 120 unknowns).
+template <int KC, typename T, bool PW> int launch_block_as(rbffd_ctx *ctx, const WArgs &a, unsigned grid) {
+  const size_t lds = block_lds_bytes<T>(a.k_cap, PW);
+  RBFFD_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&weights_block_kernel<KC, T, PW>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
-  weights_kernel<T><<<grid, W_THREADS, lds, ctx->stream>>>(a);
+  weights_block_kernel<KC, T, PW><<<grid, W_THREADS, lds, ctx->stream>>>(a);
   return RBFFD_OK;
+}
+template <typename T> int launch_block(rbffd_ctx *ctx, const WArgs &a, unsigned grid) {
+  constexpr size_t limit = 160 * 1024 - 256 - sizeof(BlockShared<T>);
+  if (a.k_cap <= 96) return launch_block_as<96, T, true>(ctx, a, grid);
+  if (block_lds_bytes<T>(a.k_cap, true) <= limit) return launch_block_as<128, T, true>(ctx, a, grid);
+  return launch_block_as<128, T, false>(ctx, a, grid);
 }
 
 }  // namespace
@@ -1850,7 +1891,7 @@ int weights_run(rbffd_ctx *ctx, const rbffd_stencils *st, const rbffd_op *ops, i
               : launch_wave<64, float, 1>(a, cnt[b], persist, n_cu, s);
       } else {  // one 256-thread workgroup per system
         const unsigned g = grid_of(cnt[b], kBlockShapes[shapes[b]], n_cu);
-        const int rc = f64 ? launch_block<double>(ctx, a, a.k_cap, n_ops, g) : launch_block<float>(ctx, a, a.k_cap, n_ops, g);
+        const int rc = f64 ? launch_block<double>(ctx, a, g) : launch_block<float>(ctx, a, g);
         if (rc) return rc;
       }
       RBFFD_HIP(ctx, hipGetLastError());
@@ -1875,7 +1916,7 @@ int weights_run(rbffd_ctx *ctx, const rbffd_stencils *st, const rbffd_op *ops, i
     if (n_large > 0) {
       f.qinfo = queue + Q_STALL_HI;
       f.k_cap = kc;
-      const int rc = launch_block<double>(ctx, f, kc, n_ops, grid_of(n_large, 2, n_cu));
+      const int rc = launch_block<double>(ctx, f, grid_of(n_large, 2, n_cu));
       if (rc) return rc;
     }
     mark_fallback_kernel<<<grid_for(nc, 256), 256, 0, s>>>(st_out, d_fl, nc, queue + Q_STALL_LO, queue + Q_STALL_HI);

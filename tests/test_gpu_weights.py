@@ -285,6 +285,21 @@ def test_two_systems_per_wavefront(R, ctx, precision):
 
 
 @pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("K", [65, 81, 84, 85, 96, 97, 113, 120, 121, 128])
+def test_weights_workgroup_systems(R, ctx, K, precision):
+    """One workgroup per system (K > 64) at the edges of its variants: three or
+    two residual lanes per row (K = 84 | 85), 24 or 32 columns per wavefront
+    (96 | 97), power tables in LDS or not (FP64, near 120), the largest; six
+    operators of one order (right-hand sides in chunks of four)."""
+    nd = jittered_square(24, seed=9)
+    n = K - 21
+    say(f"weights: K = {K} (n = {n}, r^7, degree 5), 6 operators, 20 stencils, precision {precision}")
+    centers = np.random.default_rng(K).choice(nd.n_active, 20, replace=False).astype(np.int32)
+    ops = [(O.DX, 0, 0), (O.DZ, 0, 0), (O.LAP, 0, 0), (O.DZZ, 0, 0), (O.DXX, 0, 0), (O.HYPERLAP, 3, 0)]
+    _weights_parity(R, ctx, nd.xy, ops, n, 7, 5, 0.0, centers, precision=precision)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
 def test_weights_full_size_mixed_samples(R, ctx, precision):
     """The 1M mixed batch in both solve precisions (FP64 LU, and the FP32
     factorisation with FP64 refinement, which is accepted only at the
