@@ -112,13 +112,6 @@ template <int BLOCK = RHS_BLOCK> __device__ __forceinline__ int64_t xcd_thread()
   return lb * BLOCK + threadIdx.x;
 }
 
-__device__ __forceinline__ int64_t xcd_block() {
-  const int64_t b = blockIdx.x, nb = gridDim.x;
-  const int64_t full = (nb / 8) * 8;
-  if (b >= full) return b;
-  return (b % 8) * (nb / 8) + b / 8;
-}
-
 template <class FT> struct F4 {
   FT v[4];
 };
@@ -173,6 +166,8 @@ struct NSArgs {
   int acc_mode;  // 0: none; 1: acc = yn + cb f; 2: acc += cb f
   DevMisc *misc;
   int check;     // record the step of the first non-finite output
+  int step;      // this step's place after misc->step_ctr
+  int k0;        // stencil slot of the first streamed slot (0 or 1)
 };
 
 // MW ("member wavefront"): the ensemble size is a multiple of 64, so a
@@ -180,12 +175,27 @@ struct NSArgs {
 // wave-uniform and the weight records are fetched once per wavefront through
 // the scalar cache and broadcast (the gathers stay vector loads, 64
 // consecutive members = one contiguous 1 KiB span in FP32).
-template <class FT, int WDT, int S, bool MW = false>
-__global__ __launch_bounds__(StageShape<S>::block) void ns_stage_kernel(NSArgs a) {
+//
+// P > 1: the slots of a unit of 64 (node, member) pairs are split over P
+// wavefronts of one block, whose sums meet in LDS; the first one applies the
+// stage. For launches of few wavefronts, where a wavefront's chain of loads
+// over all slots is what takes the time (split_of). Parts are ranges of
+// stencil slots, whether or not the centre slot is streamed.
+template <class FT, int WDT, int S, bool MW = false, int P = 1>
+__global__ __launch_bounds__(P == 1 ? StageShape<S>::block : 64 * P) void ns_stage_kernel(NSArgs a) {
   using SH = StageShape<S>;
   constexpr bool NT = SH::nt && !MW;
-  const int64_t t = xcd_thread<SH::block>();
-  if (t >= a.Na * a.E) return;
+  const int64_t total = a.Na * a.E;
+  int64_t t = xcd_thread<P == 1 ? SH::block : 64>();
+  const int part = P == 1 ? 0 : __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  bool live = true;
+  if constexpr (P == 1) {
+    if (t >= total) return;
+  } else {
+    t -= 64 * part;       // the lanes of a block's wavefronts hold the same 64 pairs
+    live = t < total;
+    t = min(t, total - 1);
+  }
   const int E = a.E;
   int64_t i = E == 1 ? t : t / E;
   const int e = static_cast<int>(t - i * E);  // the member
@@ -195,9 +205,14 @@ __global__ __launch_bounds__(StageShape<S>::block) void ns_stage_kernel(NSArgs a
     i = a.order ? a.order[li] : li;
     ri = a.rec_t ? li : i;
   }
+  int kb = 0, ke = a.n;  // this wavefront's slots
+  if constexpr (P > 1) {
+    const int per = (a.n + a.k0 - 1 + P - 1) / P;   // of the stencil's slots past the centre
+    kb = part == 0 ? 0 : min(a.n, 1 - a.k0 + part * per);
+    ke = min(a.n, 1 - a.k0 + (part + 1) * per);
+  }
   const FT *ys = static_cast<const FT *>(a.ys);
   const F4<FT> own = load4(ys + (i * E + e) * 4);
-  const int n = a.n;
   const int64_t Na = a.Na;
   // the 15 stencil sums, in FP64 for the epilogue: Dx and Dz of the four
   // fields, Lap of u, w, theta', Lap^k of all four; ux and wz the divergence
@@ -218,7 +233,7 @@ __global__ __launch_bounds__(StageShape<S>::block) void ns_stage_kernel(NSArgs a
       // a node next to a wall (wave-uniform): the ghost neighbours' closure
       // values' FP64 remainders are added as well, as in the one-member path
 #pragma unroll 1
-      for (int k = 0; k < n; ++k) {
+      for (int k = kb; k < ke; ++k) {
         const RecMW r = recs[k * Na];
         if (r.idx < Na) continue;
         const float4 q4 = *reinterpret_cast<const float4 *>(a.ghrem + ((r.idx - Na) * E + e) * 4);
@@ -235,7 +250,7 @@ __global__ __launch_bounds__(StageShape<S>::block) void ns_stage_kernel(NSArgs a
       }
     }
 #pragma unroll SH::unroll
-    for (int k = 0; k < n; ++k) {
+    for (int k = kb; k < ke; ++k) {
       const RecMW r = recs[k * Na];
       const F4<FT> f = gather(r.idx);
       const double wl = r.lap;
@@ -355,10 +370,10 @@ __global__ __launch_bounds__(StageShape<S>::block) void ns_stage_kernel(NSArgs a
     };
     if (a.ghrem) {
 #pragma unroll SH::unroll
-      for (int k = 0; k < n; ++k) step(slot(k), std::true_type{});
+      for (int k = kb; k < ke; ++k) step(slot(k), std::true_type{});
     } else {
 #pragma unroll SH::unroll
-      for (int k = 0; k < n; ++k) step(slot(k), std::false_type{});
+      for (int k = kb; k < ke; ++k) step(slot(k), std::false_type{});
     }
     for (int c = 0; c < 4; ++c) {
       gx[c] = static_cast<double>(sdx[c]);
@@ -367,6 +382,30 @@ __global__ __launch_bounds__(StageShape<S>::block) void ns_stage_kernel(NSArgs a
     }
     ux = DIV64 ? sux : gx[0];
     wz = DIV64 ? swz : gz[1];
+  }
+  const uint8_t kd = a.kind[i];
+  const double pibar = a.pibar[i];
+  const int64_t o = (i * E + e) * 4;
+  F4<FT> b{}, base{};  // bases of the stage update and of the accumulator
+  if (a.mode && part == 0) {
+    b = load4(static_cast<const FT *>(a.mode == 1 ? a.yn : a.acc) + o);
+    if (a.acc_mode) base = load4(static_cast<const FT *>(a.acc_mode == 1 ? a.yn : a.acc) + o);
+  }
+  if constexpr (P > 1) {  // sums of the parts, in slot order
+    __shared__ double s_sum[P - 1][15][64];
+    const int ln = threadIdx.x & 63;
+    double *v[15] = {&ux, &gx[1], &gx[2], &gx[3], &gz[0], &wz, &gz[2], &gz[3],
+                     &gl[0], &gl[1], &gl[2], &shv[0], &shv[1], &shv[2], &shv[3]};
+    if (part > 0) {
+#pragma unroll
+      for (int c = 0; c < 15; ++c) s_sum[part - 1][c][ln] = *v[c];
+    }
+    __syncthreads();
+    if (part > 0 || !live) return;
+#pragma unroll
+    for (int c = 0; c < 15; ++c)
+#pragma unroll
+      for (int q = 0; q < P - 1; ++q) *v[c] += s_sum[q][c][ln];
   }
   // Eqs. uEq..piEq (perturbation form), evaluated in FP64; a uniform
   // background wind u_bar joins u in the advective terms
@@ -377,19 +416,15 @@ __global__ __launch_bounds__(StageShape<S>::block) void ns_stage_kernel(NSArgs a
   f[0] = -ua * ux - w * gz[0] - cp_th * gx[3] + a.mu * gl[0] + a.hv * shv[0];
   f[1] = -ua * gx[1] - w * wz - cp_th * gz[3] + a.g * th / a.theta_bar + a.mu * gl[1] + a.hv * shv[1];
   f[2] = -ua * gx[2] - w * gz[2] + a.mu * gl[2] + a.hv * shv[2];
-  f[3] = -ua * gx[3] - w * (a.dpibar + gz[3]) - a.rcv * (a.pibar[i] + pi) * (ux + wz) + a.hv * shv[3];
-  const uint8_t kd = a.kind[i];
+  f[3] = -ua * gx[3] - w * (a.dpibar + gz[3]) - a.rcv * (pibar + pi) * (ux + wz) + a.hv * shv[3];
   if (kd & KIND_ZWALL) f[1] = 0.0;  // w stays 0 on walls normal to z
   if (kd & KIND_XWALL) f[0] = 0.0;  // u stays 0 on walls normal to x
-  const int64_t o = (i * E + e) * 4;
   double r[4];
   if (a.mode == 0) {
     for (int c = 0; c < 4; ++c) r[c] = f[c];
   } else {
-    const F4<FT> b = load4(static_cast<const FT *>(a.mode == 1 ? a.yn : a.acc) + o);
     for (int c = 0; c < 4; ++c) r[c] = static_cast<double>(b.v[c]) + a.ca * f[c];
     if (a.acc_mode) {
-      const F4<FT> base = load4(static_cast<const FT *>(a.acc_mode == 1 ? a.yn : a.acc) + o);
       double q[4];
       for (int c = 0; c < 4; ++c) q[c] = static_cast<double>(base.v[c]) + a.cb * f[c];
       store4(static_cast<FT *>(a.acc) + o, q);
@@ -398,7 +433,7 @@ __global__ __launch_bounds__(StageShape<S>::block) void ns_stage_kernel(NSArgs a
   store4(static_cast<FT *>(a.out) + o, r);
   if (a.check) {
     bool fin = isfinite(r[0]) && isfinite(r[1]) && isfinite(r[2]) && isfinite(r[3]);
-    if (!fin) atomicMin(&a.misc->nonfinite_step, a.misc->step_ctr);
+    if (!fin) atomicMin(&a.misc->nonfinite_step, a.misc->step_ctr + a.step);
   }
 }
 
@@ -416,21 +451,33 @@ struct AdvArgs {
   int mode, acc_mode;
   DevMisc *misc;
   int check;
+  int step;                       // this step's place after misc->step_ctr
   const int *mir_off, *mir_list;  // stage updates: also write each node's mirror ghosts (or null)
 };
 
-template <class FT>
-__global__ __launch_bounds__(RHS_BLOCK) void adv_stage_kernel(AdvArgs a) {
-  const int64_t t = xcd_block() * RHS_BLOCK + threadIdx.x;
-  if (t >= a.Na * a.E) return;
+// P > 1: as in ns_stage_kernel.
+template <class FT, int P>
+__global__ __launch_bounds__(P == 1 ? RHS_BLOCK : 64 * P) void adv_stage_kernel(AdvArgs a) {
+  const int64_t total = a.Na * a.E;
+  int64_t t = xcd_thread<P == 1 ? RHS_BLOCK : 64>();
+  const int part = P == 1 ? 0 : __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  bool live = true;
+  if constexpr (P == 1) {
+    if (t >= total) return;
+  } else {
+    t -= 64 * part;
+    live = t < total;
+    t = min(t, total - 1);
+  }
   const int E = a.E;
   const int64_t i = E == 1 ? t : t / E;
   const int e = static_cast<int>(t - i * E);
   const FT *ys = static_cast<const FT *>(a.ys);
   double sa = 0.0, sh = 0.0;
   const int64_t Na = a.Na;
-#pragma unroll 4
-  for (int k = 0; k < a.n; ++k) {
+  const int per = (a.n + P - 1) / P, kb = min(a.n, part * per), ke = min(a.n, kb + per);
+#pragma unroll 5
+  for (int k = kb; k < ke; ++k) {
     const int64_t s = static_cast<int64_t>(k) * Na + i;
     const int j = a.idx_t[s];
     const RecAdv r = a.rec[s];
@@ -438,27 +485,43 @@ __global__ __launch_bounds__(RHS_BLOCK) void adv_stage_kernel(AdvArgs a) {
     sa = fma(r.adv, v, sa);
     sh = fma(r.hv, v, sh);
   }
-  double ts = a.t_fixed;
-  if (a.misc) ts = (a.misc->t0 + static_cast<double>(a.misc->step_ctr) * a.dt) + a.t_off;
-  const double f = -cos(a.omega * ts) * sa + a.hv * sh;
   const int64_t o = i * E + e;
+  double b = 0.0, base = 0.0;
+  if (a.mode && part == 0) {
+    b = static_cast<const FT *>(a.mode == 1 ? a.yn : a.acc)[o];
+    if (a.acc_mode) base = static_cast<const FT *>(a.acc_mode == 1 ? a.yn : a.acc)[o];
+  }
+  double ts = a.t_fixed;
+  if (a.misc) ts = (a.misc->t0 + static_cast<double>(a.misc->step_ctr + a.step) * a.dt) + a.t_off;
+  if constexpr (P > 1) {
+    __shared__ double s_sum[P - 1][2][64];
+    const int ln = threadIdx.x & 63;
+    if (part > 0) {
+      s_sum[part - 1][0][ln] = sa;
+      s_sum[part - 1][1][ln] = sh;
+    }
+    __syncthreads();
+    if (part > 0 || !live) return;
+#pragma unroll
+    for (int q = 0; q < P - 1; ++q) {
+      sa += s_sum[q][0][ln];
+      sh += s_sum[q][1][ln];
+    }
+  }
+  const double f = -cos(a.omega * ts) * sa + a.hv * sh;
   double r;
   if (a.mode == 0) {
     r = f;
   } else {
-    const FT *b = static_cast<const FT *>(a.mode == 1 ? a.yn : a.acc);
-    r = static_cast<double>(b[o]) + a.ca * f;
-    if (a.acc_mode) {
-      const FT *base = static_cast<const FT *>(a.acc_mode == 1 ? a.yn : a.acc);
-      static_cast<FT *>(a.acc)[o] = static_cast<FT>(static_cast<double>(base[o]) + a.cb * f);
-    }
+    r = b + a.ca * f;
+    if (a.acc_mode) static_cast<FT *>(a.acc)[o] = static_cast<FT>(base + a.cb * f);
   }
   static_cast<FT *>(a.out)[o] = static_cast<FT>(r);
   if (a.mir_off) {  // the value the mirror boundary would copy into this node's ghosts
     for (int g = a.mir_off[i]; g < a.mir_off[i + 1]; ++g)
       static_cast<FT *>(a.out)[(Na + a.mir_list[g]) * E + e] = static_cast<FT>(r);
   }
-  if (a.check && !isfinite(r)) atomicMin(&a.misc->nonfinite_step, a.misc->step_ctr);
+  if (a.check && !isfinite(r)) atomicMin(&a.misc->nonfinite_step, a.misc->step_ctr + a.step);
 }
 
 struct GArgs {
@@ -664,48 +727,84 @@ __global__ __launch_bounds__(RHS_BLOCK) void ghost_apply_kernel(GArgs a) {
   }
 }
 
-// Ensembles (E >= GHOST_MEMBER_LANES): the same two steps with one thread
-// per (boundary row, member), members in consecutive lanes, so every
-// stencil slot and inverse entry is one coalesced load across the
-// wavefront. Sums run in slot / entry order, so such members agree with
-// single-member runs to rounding rather than bit for bit.
+// Ensembles (E >= GHOST_MEMBER_LANES): the same two steps with the members in
+// consecutive lanes, so every stencil slot and inverse entry is one coalesced
+// load across the wavefront. A unit of 64 (boundary row, member) pairs is one
+// block of GHOST_PARTS wavefronts, each with its range of the slots or window
+// entries; the ranges' sums meet in LDS. A closure has few rows (256 of the
+// 400 m channel at 64 members: 256 units), so one wavefront per unit left most
+// of the chip idle in a chain of 37 and 243 loads: 10.9 and 16.4 us against
+// 5.8 and 7.8. Sums run in slot / entry order per range, so such members
+// agree with single-member runs to rounding rather than bit for bit.
 constexpr int GHOST_MEMBER_LANES = 16;
+constexpr int GHOST_PARTS = 4;
 
-template <class FT>
-__global__ __launch_bounds__(RHS_BLOCK) void ghost_resid_members_kernel(GArgs a) {
-  const int64_t t = static_cast<int64_t>(blockIdx.x) * RHS_BLOCK + threadIdx.x;
-  if (t >= static_cast<int64_t>(a.R) * a.E) return;
-  const int64_t row = t / a.E;
-  const int e = static_cast<int>(t - row * a.E);
-  const int nrm = a.bnd_normal[row];
-  double ru = 0.0, rw = 0.0, rt = 0.0, rp = 0.0;
-#pragma unroll 4
-  for (int k = 0; k < a.n; ++k) resid_slot<FT>(a, row, k, e, nrm, ru, rw, rt, rp);
-  resid_store<FT>(a, row, e, nrm, ru, rw, rt, rp);
+// Sums over the parts into part 0's v, in part order (a barrier every thread passes).
+__device__ __forceinline__ void sum_parts(int part, double (&v)[4]) {
+  __shared__ double s[GHOST_PARTS - 1][4][64];
+  const int ln = threadIdx.x & 63;
+  if (part > 0) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) s[part - 1][c][ln] = v[c];
+  }
+  __syncthreads();
+  if (part > 0) return;
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int q = 0; q < GHOST_PARTS - 1; ++q) v[c] += s[q][c][ln];
 }
 
 template <class FT>
-__global__ __launch_bounds__(RHS_BLOCK) void ghost_apply_members_kernel(GArgs a) {
-  const int64_t t = static_cast<int64_t>(blockIdx.x) * RHS_BLOCK + threadIdx.x;
-  if (t >= static_cast<int64_t>(a.R) * a.E) return;
+__global__ __launch_bounds__(64 * GHOST_PARTS) void ghost_resid_members_kernel(GArgs a) {
+  const int part = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int64_t total = static_cast<int64_t>(a.R) * a.E;
+  const int64_t u = static_cast<int64_t>(blockIdx.x) * 64 + (threadIdx.x & 63), t = min(u, total - 1);
+  const int64_t row = t / a.E;
+  const int e = static_cast<int>(t - row * a.E);
+  const int nrm = a.bnd_normal[row];
+  const int per = (a.n + GHOST_PARTS - 1) / GHOST_PARTS, kb = min(a.n, part * per), ke = min(a.n, kb + per);
+  double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 5
+  for (int k = kb; k < ke; ++k) resid_slot<FT>(a, row, k, e, nrm, v[0], v[1], v[2], v[3]);
+  sum_parts(part, v);
+  if (part == 0 && u < total) resid_store<FT>(a, row, e, nrm, v[0], v[1], v[2], v[3]);
+}
+
+// This part's range [qb, qe) of a window of len entries.
+__device__ __forceinline__ void part_range(int part, int len, int &qb, int &qe) {
+  const int per = (len + GHOST_PARTS - 1) / GHOST_PARTS;
+  qb = min(len, part * per);
+  qe = min(len, qb + per);
+}
+
+template <class FT>
+__global__ __launch_bounds__(64 * GHOST_PARTS) void ghost_apply_members_kernel(GArgs a) {
+  const int part = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int64_t total = static_cast<int64_t>(a.R) * a.E;
+  const int64_t u = static_cast<int64_t>(blockIdx.x) * 64 + (threadIdx.x & 63), t = min(u, total - 1);
   const int64_t row = t / a.E;
   const int e = static_cast<int>(t - row * a.E);
   double v[4] = {0.0, 0.0, 0.0, 0.0};
+  int qb, qe;
   if (!a.u_shared) {
     const InvRow w = inv_row(a, 0, row);
+    part_range(part, w.len, qb, qe);
 #pragma unroll 4
-    for (int q = 0; q < w.len; ++q) v[0] = fma(w.val[q], a.gres[(win_row(w, q) * a.E + e) * 4], v[0]);
+    for (int q = qb; q < qe; ++q) v[0] = fma(w.val[q], a.gres[(win_row(w, q) * a.E + e) * 4], v[0]);
   }
   {
     const InvRow w = inv_row(a, 1, row);
-#pragma unroll 4
-    for (int q = 0; q < w.len; ++q) v[1] = fma(w.val[q], a.gres[(win_row(w, q) * a.E + e) * 4 + 1], v[1]);
+    part_range(part, w.len, qb, qe);
+#pragma unroll 8
+    for (int q = qb; q < qe; ++q) v[1] = fma(w.val[q], a.gres[(win_row(w, q) * a.E + e) * 4 + 1], v[1]);
   }
   {
     const InvRow w = inv_row(a, 2, row);
+    part_range(part, w.len, qb, qe);
     if (a.u_shared) {
-#pragma unroll 4
-      for (int q = 0; q < w.len; ++q) {
+#pragma unroll 8
+      for (int q = qb; q < qe; ++q) {
         const double c = w.val[q];
         const double4 r = *reinterpret_cast<const double4 *>(a.gres + (win_row(w, q) * a.E + e) * 4);
         v[0] = fma(c, r.x, v[0]);
@@ -713,8 +812,8 @@ __global__ __launch_bounds__(RHS_BLOCK) void ghost_apply_members_kernel(GArgs a)
         v[3] = fma(c, r.w, v[3]);
       }
     } else {
-#pragma unroll 4
-      for (int q = 0; q < w.len; ++q) {
+#pragma unroll 8
+      for (int q = qb; q < qe; ++q) {
         const double c = w.val[q];
         const double2 r = *reinterpret_cast<const double2 *>(a.gres + (win_row(w, q) * a.E + e) * 4 + 2);
         v[2] = fma(c, r.x, v[2]);
@@ -722,6 +821,8 @@ __global__ __launch_bounds__(RHS_BLOCK) void ghost_apply_members_kernel(GArgs a)
       }
     }
   }
+  sum_parts(part, v);
+  if (part > 0 || u >= total) return;
   const int64_t go = (static_cast<int64_t>(a.bnd_ghosts[row]) * a.E + e) * 4;
   store4(static_cast<FT *>(a.y) + go, v);
   if (a.ghrem) store_remainder(a.ghrem + go - a.Na * a.E * 4, v);
@@ -733,7 +834,7 @@ __global__ void misc_init_kernel(DevMisc *m, double t0) {
   m->t0 = t0;
 }
 
-__global__ void tick_kernel(DevMisc *m) { m->step_ctr += 1; }
+__global__ void tick_kernel(DevMisc *m, int steps) { m->step_ctr += steps; }
 
 // ---- host-side launchers ----------------------------------------------------
 
@@ -783,14 +884,14 @@ int launch_ghost(rbffd_ctx *ctx, rbffd_model *m, void *y) {
   g.bc_scale = m->g / (m->c_p * m->theta_bar);
   g.theta_bar = m->theta_bar;
   const int64_t cnt = static_cast<int64_t>(m->n_bnd) * m->E;
-  if (m->E >= GHOST_MEMBER_LANES) {                                       // one thread each
-    const unsigned grid = grid_for(cnt, RHS_BLOCK);
+  if (m->E >= GHOST_MEMBER_LANES) {                                       // members in lanes
+    const unsigned grid = grid_for(cnt, 64), block = 64 * GHOST_PARTS;
     if (m->fdt == RBFFD_F64) {
-      ghost_resid_members_kernel<double><<<grid, RHS_BLOCK, 0, ctx->stream>>>(g);
-      ghost_apply_members_kernel<double><<<grid, RHS_BLOCK, 0, ctx->stream>>>(g);
+      ghost_resid_members_kernel<double><<<grid, block, 0, ctx->stream>>>(g);
+      ghost_apply_members_kernel<double><<<grid, block, 0, ctx->stream>>>(g);
     } else {
-      ghost_resid_members_kernel<float><<<grid, RHS_BLOCK, 0, ctx->stream>>>(g);
-      ghost_apply_members_kernel<float><<<grid, RHS_BLOCK, 0, ctx->stream>>>(g);
+      ghost_resid_members_kernel<float><<<grid, block, 0, ctx->stream>>>(g);
+      ghost_apply_members_kernel<float><<<grid, block, 0, ctx->stream>>>(g);
     }
   } else {
     const unsigned grid = grid_for(cnt, RHS_BLOCK / 64);                 // one wavefront each
@@ -821,23 +922,56 @@ hipError_t launch_timed(void (*k)(A), unsigned grid, unsigned block, hipStream_t
   return hipGetLastError();
 }
 
-template <class FT, int WDT, int S>
+// Wavefronts per unit of 64 (node, member) pairs. One wavefront walks its
+// slots in a chain of loads; with fewer units than fill the chip (1,024 SIMDs)
+// that latency is the launch's time, so the slots are split. Small ensembles
+// go by the node count alone, so that members agree with a single run bit for
+// bit. Measured on hexagonal channels, us per right-hand side unsplit | split
+// (with the closure, 9 us of each): FP32 600 units 29.2 | 18.7, 2,064 39.7 |
+// 30.6, 3,600 43.6 | 41.2, 4,096 45.1 | 45.8, 8,192 78.6 | 92.8 (the weight
+// stream is then at the HBM rate, and the sums' exchange only costs); FP64 600
+// 26.0 | 18.3, 3,600 67.5 | 67.2, 4,096 72.5 | 79.2; BF16 2,064 39.7 | 29.7;
+// 64 members a unit 2,176 27.2 | 26.5, 6,528 48.7 | 59.4. Transport 625 7.1 |
+// 5.4, 1,024 9.2 | 10.4.
+constexpr int SPLIT = 4, ADV_SPLIT = 8;
+constexpr int64_t SPLIT_UNITS = 4096, ADV_SPLIT_UNITS = 768;
+inline bool split_of(int64_t na, int E, int64_t limit) {
+  return (na * (E < 16 ? 1 : E) + 63) / 64 < limit;
+}
+
+template <class FT, int WDT, int S, bool MW>
 hipError_t launch_ns_one(int64_t cnt, hipStream_t st, const NSArgs &a, hipEvent_t e0, hipEvent_t e1) {
+  if (split_of(a.Na, a.E, SPLIT_UNITS)) {
+    // (block sizes do not apply: one instance per unrolling and load kind)
+    constexpr int C = kShapes[S].unroll == 1 ? 0 : kShapes[S].unroll == 2 ? 1 : 5;
+    return launch_timed(ns_stage_kernel<FT, WDT, C, MW, SPLIT>, grid_for(cnt, 64), 64 * SPLIT, st, a, e0, e1);
+  }
   constexpr int B = StageShape<S>::block;
-  if (a.E % 64 == 0) return launch_timed(ns_stage_kernel<FT, WDT, S, true>, grid_for(cnt, B), B, st, a, e0, e1);
-  return launch_timed(ns_stage_kernel<FT, WDT, S, false>, grid_for(cnt, B), B, st, a, e0, e1);
+  return launch_timed(ns_stage_kernel<FT, WDT, S, MW>, grid_for(cnt, B), B, st, a, e0, e1);
+}
+
+template <class FT, int WDT, bool MW>
+hipError_t launch_ns_shape_as(int shape, int64_t cnt, hipStream_t st, const NSArgs &a, hipEvent_t e0, hipEvent_t e1) {
+  switch (shape) {
+    case 0: return launch_ns_one<FT, WDT, 0, MW>(cnt, st, a, e0, e1);
+    case 1: return launch_ns_one<FT, WDT, 1, MW>(cnt, st, a, e0, e1);
+    case 2: return launch_ns_one<FT, WDT, 2, MW>(cnt, st, a, e0, e1);
+    case 3: return launch_ns_one<FT, WDT, 3, MW>(cnt, st, a, e0, e1);
+    case 4: return launch_ns_one<FT, WDT, 4, MW>(cnt, st, a, e0, e1);
+    default: return launch_ns_one<FT, WDT, 5, MW>(cnt, st, a, e0, e1);
+  }
 }
 
 template <class FT, int WDT>
 hipError_t launch_ns_shape(int shape, int64_t cnt, hipStream_t st, const NSArgs &a, hipEvent_t e0, hipEvent_t e1) {
-  switch (shape) {
-    case 0: return launch_ns_one<FT, WDT, 0>(cnt, st, a, e0, e1);
-    case 1: return launch_ns_one<FT, WDT, 1>(cnt, st, a, e0, e1);
-    case 2: return launch_ns_one<FT, WDT, 2>(cnt, st, a, e0, e1);
-    case 3: return launch_ns_one<FT, WDT, 3>(cnt, st, a, e0, e1);
-    case 4: return launch_ns_one<FT, WDT, 4>(cnt, st, a, e0, e1);
-    default: return launch_ns_one<FT, WDT, 5>(cnt, st, a, e0, e1);
-  }
+  return a.E % 64 == 0 ? launch_ns_shape_as<FT, WDT, true>(shape, cnt, st, a, e0, e1)
+                       : launch_ns_shape_as<FT, WDT, false>(shape, cnt, st, a, e0, e1);
+}
+
+template <class FT> hipError_t launch_adv(int64_t cnt, hipStream_t st, const AdvArgs &a, hipEvent_t e0, hipEvent_t e1) {
+  if (split_of(a.Na, a.E, ADV_SPLIT_UNITS))
+    return launch_timed(adv_stage_kernel<FT, ADV_SPLIT>, grid_for(cnt, 64), 64 * ADV_SPLIT, st, a, e0, e1);
+  return launch_timed(adv_stage_kernel<FT, 1>, grid_for(cnt, RHS_BLOCK), RHS_BLOCK, st, a, e0, e1);
 }
 
 struct StageSpec {
@@ -845,6 +979,7 @@ struct StageSpec {
   void *out;
   double ca, cb, t_off;
   int mode, acc_mode, check;
+  int step = 0;
 };
 
 int launch_stage(rbffd_ctx *ctx, rbffd_model *m, const StageSpec &sp, double t_fixed, bool use_misc, double dt) {
@@ -892,6 +1027,8 @@ int launch_stage(rbffd_ctx *ctx, rbffd_model *m, const StageSpec &sp, double t_f
     a.acc_mode = sp.acc_mode;
     a.misc = misc;
     a.check = sp.check;
+    a.step = sp.step;
+    a.k0 = m->k0;
     const int shape = m->shape >= 0 ? m->shape : default_shape(m->wdt);
     if (m->fdt == RBFFD_F64)
       RBFFD_HIP(ctx, (launch_ns_shape<double, RBFFD_F64>(shape, cnt, ctx->stream, a, ev0, ev1)));
@@ -921,14 +1058,15 @@ int launch_stage(rbffd_ctx *ctx, rbffd_model *m, const StageSpec &sp, double t_f
     a.acc_mode = sp.acc_mode;
     a.misc = use_misc ? misc : nullptr;
     a.check = sp.check;
+    a.step = sp.step;
     if (sp.mode != 0 && m->n_mirror > 0) {
       a.mir_off = m->mirror_off.as<int>();
       a.mir_list = m->mirror_list.as<int>();
     }
     if (m->fdt == RBFFD_F64)
-      RBFFD_HIP(ctx, launch_timed(adv_stage_kernel<double>, grid_for(cnt, RHS_BLOCK), RHS_BLOCK, ctx->stream, a, ev0, ev1));
+      RBFFD_HIP(ctx, launch_adv<double>(cnt, ctx->stream, a, ev0, ev1));
     else
-      RBFFD_HIP(ctx, launch_timed(adv_stage_kernel<float>, grid_for(cnt, RHS_BLOCK), RHS_BLOCK, ctx->stream, a, ev0, ev1));
+      RBFFD_HIP(ctx, launch_adv<float>(cnt, ctx->stream, a, ev0, ev1));
   }
   return RBFFD_OK;
 }
@@ -946,8 +1084,9 @@ bool needs_ghost(const rbffd_model *m, const StageSpec &sp, const void *y) {
   return m->physics != RBFFD_PHYS_ADVECTION || sp.ys == y;
 }
 
-// One full time step, as a sequence of launches on the context stream.
-int enqueue_step(rbffd_ctx *ctx, rbffd_model *m, void *y, double dt, int tableau) {
+// One full time step, number `step` after the device's step counter, as a
+// sequence of launches on the context stream.
+int enqueue_step(rbffd_ctx *ctx, rbffd_model *m, void *y, double dt, int tableau, int step) {
   int rc;
   void *ya = m->ya.p, *yb = m->yb.p;
   if (tableau == RBFFD_RK4) {
@@ -957,7 +1096,8 @@ int enqueue_step(rbffd_ctx *ctx, rbffd_model *m, void *y, double dt, int tableau
         {yb, y, ya, dt, dt / 3.0, 0.5 * dt, 1, 2, 0},
         {ya, nullptr, y, dt / 6.0, 0.0, dt, 2, 0, 1},
     };
-    for (const StageSpec &sp : st) {
+    for (StageSpec sp : st) {
+      sp.step = step;
       if (needs_ghost(m, sp, y) && (rc = launch_ghost(ctx, m, const_cast<void *>(sp.ys)))) return rc;
       if ((rc = launch_stage(ctx, m, sp, 0.0, true, dt))) return rc;
     }
@@ -967,12 +1107,22 @@ int enqueue_step(rbffd_ctx *ctx, rbffd_model *m, void *y, double dt, int tableau
         {ya, y, yb, dt / 2.0, 0.0, dt / 3.0, 1, 0, 0},
         {yb, y, y, dt, 0.0, dt / 2.0, 1, 0, 1},
     };
-    for (const StageSpec &sp : st) {
+    for (StageSpec sp : st) {
+      sp.step = step;
       if (needs_ghost(m, sp, y) && (rc = launch_ghost(ctx, m, const_cast<void *>(sp.ys)))) return rc;
       if ((rc = launch_stage(ctx, m, sp, 0.0, true, dt))) return rc;
     }
   }
-  tick_kernel<<<1, 1, 0, ctx->stream>>>(m->dev_misc.as<DevMisc>());
+  return RBFFD_OK;
+}
+
+// n steps, and the device's step counter past them.
+int enqueue_steps(rbffd_ctx *ctx, rbffd_model *m, void *y, double dt, int tableau, int n) {
+  for (int k = 0; k < n; ++k) {
+    const int rc = enqueue_step(ctx, m, y, dt, tableau, k);
+    if (rc) return rc;
+  }
+  tick_kernel<<<1, 1, 0, ctx->stream>>>(m->dev_misc.as<DevMisc>(), n);
   RBFFD_HIP(ctx, hipGetLastError());
   return RBFFD_OK;
 }
@@ -1028,7 +1178,7 @@ int capture_steps(rbffd_ctx *ctx, rbffd_model *m, void *state, double dt, int ta
   hipGraph_t graph = nullptr;
   hipError_t ec = eb;
   if (eb == hipSuccess) {
-    for (int i = 0; i < k && rc == RBFFD_OK; ++i) rc = enqueue_step(ctx, m, state, dt, tableau);
+    rc = enqueue_steps(ctx, m, state, dt, tableau, k);
     ec = hipStreamEndCapture(cs, &graph);
   }
   ctx->stream = saved;
@@ -1051,7 +1201,7 @@ int model_step(rbffd_ctx *ctx, rbffd_model *m, void *state, double *t, double dt
   RBFFD_HIP(ctx, hipGetLastError());
   if (m->profile) {
     for (int64_t k = 0; k < n_steps; ++k) {
-      int rc = enqueue_step(ctx, m, state, dt, tableau);
+      int rc = enqueue_steps(ctx, m, state, dt, tableau, 1);
       if (rc) return rc;
     }
   } else {

@@ -725,3 +725,68 @@ def test_full_size_ghost_closure_holds_the_wall_conditions(R, ctx):
             assert r.max() <= tol, (fdt, f, float(r.max()))
         say(f"   field dtype {fdt}: worst relative wall-condition residual {worst:.2e}")
         gm.close()
+
+
+@pytest.mark.parametrize("n", [2, 4, 13, 37])
+@pytest.mark.parametrize("na, E", [(61, 1), (321, 3), (321, 16), (21, 64), (700, 70)])
+def test_split_slots(R, ctx, na, E, n):
+    """Small launches split each node's slots over several wavefronts: every
+    remainder of nodes and slots (parts without a slot included), against
+    plain FP64 sums over arbitrary stencils and weights, both physics. Bars:
+    each sum's rounding, (n + 8) 2^-53 of the summed magnitudes (FP32 fields:
+    2^-23, for its weights, differences and products)."""
+    import torch
+    rng = np.random.default_rng(100 * n + na)
+    idx = rng.integers(0, na, (na, n)).astype(np.int32)
+    if na % 2:
+        idx[:, 0] = np.arange(na)                 # the centre slot left out of the stream, or kept
+    W = rng.normal(0, 1, (4, na, n))
+    xy = rng.uniform(0, 1, (na, 2))
+    c = dict(c_p=1004.0, c_v=717.0, R_d=287.0, g=9.81, theta_bar=300.0, mu=0.7, u_bar=0.3)
+    for fdt, dt, eps in ((R.F64, np.float64, 2.0 ** -53), (R.F32, np.float32, 2.0 ** -23)):
+        y = rng.normal(0, 1, (na, E, 4)).astype(dt)
+        m = R.Model(ctx, R.PHYS_NS, dev(idx, torch.int32), dev(W, torch.float64), dev(xy, torch.float64), na,
+                    field_dtype=fdt, weight_dtype=fdt, ensemble=E, hv_coeff=0.4, consts=c)
+        s = torch.from_numpy(y).cuda()
+        f = torch.empty_like(s)
+        R.rbffd_rhs(ctx, m, 0.0, s, f)
+        y = y.astype(np.float64)
+        d = y[idx] - y[:, None]                                       # [na][n][E][4]
+        D = np.einsum("qik,ikef->qief", W, d)
+        A = np.einsum("qik,ikef->qief", np.abs(W), np.abs(d)) + np.abs(D)
+        u, w, th, pi = [y[..., q] for q in range(4)]
+        pib = (1.0 - c["g"] * xy[:, 1] / (c["c_p"] * c["theta_bar"]))[:, None]
+        ua, cpt = u + c["u_bar"], c["c_p"] * (c["theta_bar"] + th)
+        rcv, dpb = c["R_d"] / c["c_v"], -c["g"] / (c["c_p"] * c["theta_bar"])
+
+        def tend(X, a, sign):
+            x, z, lp, hv = X
+            r = np.empty_like(y)
+            r[..., 0] = sign * (a(ua) * x[..., 0] + a(w) * z[..., 0] + a(cpt) * x[..., 3]) + c["mu"] * lp[..., 0]
+            r[..., 1] = (sign * (a(ua) * x[..., 1] + a(w) * z[..., 1] + a(cpt) * z[..., 3])
+                         + a(c["g"] * th / c["theta_bar"]) + c["mu"] * lp[..., 1])
+            r[..., 2] = sign * (a(ua) * x[..., 2] + a(w) * z[..., 2]) + c["mu"] * lp[..., 2]
+            r[..., 3] = sign * (a(ua) * x[..., 3] + a(w) * (a(np.float64(dpb)) + z[..., 3])
+                                + a(rcv * (pib + pi)) * (x[..., 0] + z[..., 1]))
+            return r + 0.4 * hv
+        want, mag = tend(D, lambda v: v, -1.0), tend(A, np.abs, 1.0)
+        err = np.abs(host(f) - want)
+        say(f"split slots: NS na {na}, E {E}, n {n}, {dt.__name__}: {(err / np.maximum(mag, 1e-300)).max() / eps:.2f} eps")
+        assert np.all(err <= (n + 8) * eps * mag)
+        U, V = rng.normal(0, 1, (2, na))
+        psi = rng.normal(0, 1, (na, E, 1)).astype(dt)
+        m = R.Model(ctx, R.PHYS_ADVECTION, dev(idx, torch.int32), dev(W[:3], torch.float64), dev(xy, torch.float64), na,
+                    field_dtype=fdt, ensemble=E, hv_coeff=0.4, vel_u=dev(U, torch.float64), vel_v=dev(V, torch.float64),
+                    vel_period=5.0)
+        s = torch.from_numpy(psi).cuda()
+        f = torch.empty_like(s)
+        R.rbffd_rhs(ctx, m, 0.25, s, f)
+        adv = W[0] * U[idx] + W[1] * V[idx]
+        g = psi.astype(np.float64)[idx][..., 0]
+        cs = np.cos(np.pi * 0.25 / 5.0)
+        want = -cs * np.einsum("ik,ike->ie", adv, g) + 0.4 * np.einsum("ik,ike->ie", W[2], g)
+        mag = (np.einsum("ik,ike->ie", np.abs(W[0] * U[idx]) + np.abs(W[1] * V[idx]), np.abs(g))
+               + 0.4 * np.einsum("ik,ike->ie", np.abs(W[2]), np.abs(g)))
+        err = np.abs(host(f)[..., 0] - want)
+        say(f"   transport: {(err / np.maximum(mag, 1e-300)).max() / eps:.2f} eps")
+        assert np.all(err <= (n + 8) * eps * mag)
