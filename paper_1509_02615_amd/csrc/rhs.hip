@@ -540,7 +540,20 @@ struct GArgs {
   int R, n, E;
   int u_shared;                // 1: u's block equals theta prime's (no wall normal to x)
   double bc_scale, theta_bar;  // dpi/dz = bc_scale * th / (theta_bar + th) on walls normal to z
+  void *zero;                  // tendency whose ghost rows are set to 0 as well (or NULL)
 };
+
+// A ghost row's values out, and 0 into its row of a tendency (every node past
+// the active ones is the ghost of one boundary row, so this clears them all
+// without a launch of its own: 3 us of a 1024 x 129 right-hand side's 32).
+template <class FT> __device__ __forceinline__ void ghost_store(const GArgs &a, int64_t go, const double (&v)[4]) {
+  store4(static_cast<FT *>(a.y) + go, v);
+  if (a.ghrem) store_remainder(a.ghrem + go - a.Na * a.E * 4, v);
+  if (a.zero) {
+    const double z[4] = {0.0, 0.0, 0.0, 0.0};
+    store4(static_cast<FT *>(a.zero) + go, z);
+  }
+}
 
 // Sum over the wavefront (full exec mask), returned in every lane: adds of
 // data-parallel moves within rows of 16 lanes (quad permutes, half-mirror,
@@ -721,10 +734,7 @@ __global__ __launch_bounds__(RHS_BLOCK) void ghost_apply_kernel(GArgs a) {
     apply_sum(a, wt, ww, wu, q + 64, t1, v);
   }
   for (int f = 0; f < 4; ++f) v[f] = wave_sum(v[f]);
-  if (lane == 0) {
-    store4(static_cast<FT *>(a.y) + go, v);
-    if (a.ghrem) store_remainder(a.ghrem + go - a.Na * a.E * 4, v);
-  }
+  if (lane == 0) ghost_store<FT>(a, go, v);
 }
 
 // Ensembles (E >= GHOST_MEMBER_LANES): the same two steps with the members in
@@ -824,8 +834,7 @@ __global__ __launch_bounds__(64 * GHOST_PARTS) void ghost_apply_members_kernel(G
   sum_parts(part, v);
   if (part > 0 || u >= total) return;
   const int64_t go = (static_cast<int64_t>(a.bnd_ghosts[row]) * a.E + e) * 4;
-  store4(static_cast<FT *>(a.y) + go, v);
-  if (a.ghrem) store_remainder(a.ghrem + go - a.Na * a.E * 4, v);
+  ghost_store<FT>(a, go, v);
 }
 
 __global__ void misc_init_kernel(DevMisc *m, double t0) {
@@ -849,7 +858,8 @@ __global__ void mirror_kernel(FT *__restrict__ y, const int *__restrict__ src, i
   y[(na + k) * E + e] = y[static_cast<int64_t>(src[k]) * E + e];
 }
 
-int launch_ghost(rbffd_ctx *ctx, rbffd_model *m, void *y) {
+// `zero`: a tendency whose ghost rows become 0 (Navier-Stokes closures), or NULL.
+int launch_ghost(rbffd_ctx *ctx, rbffd_model *m, void *y, void *zero = nullptr) {
   if (m->physics == RBFFD_PHYS_ADVECTION && m->n_mirror > 0) {
     const int64_t cnt = m->n_mirror * m->E;
     if (m->fdt == RBFFD_F64)
@@ -883,6 +893,7 @@ int launch_ghost(rbffd_ctx *ctx, rbffd_model *m, void *y) {
   g.E = m->E;
   g.bc_scale = m->g / (m->c_p * m->theta_bar);
   g.theta_bar = m->theta_bar;
+  g.zero = zero;
   const int64_t cnt = static_cast<int64_t>(m->n_bnd) * m->E;
   if (m->E >= GHOST_MEMBER_LANES) {                                       // members in lanes
     const unsigned grid = grid_for(cnt, 64), block = 64 * GHOST_PARTS;
@@ -1132,12 +1143,14 @@ int enqueue_steps(rbffd_ctx *ctx, rbffd_model *m, void *y, double dt, int tablea
 int model_ghost(rbffd_ctx *ctx, rbffd_model *m, void *state) { return launch_ghost(ctx, m, state); }
 
 int model_rhs(rbffd_ctx *ctx, rbffd_model *m, double t, void *state, void *tendency) {
-  int rc = launch_ghost(ctx, m, state);
+  // the Navier-Stokes closure clears the tendency's ghost rows too
+  const bool cleared = m->physics == RBFFD_PHYS_NS && m->n_bnd > 0;
+  int rc = launch_ghost(ctx, m, state, cleared ? tendency : nullptr);
   if (rc) return rc;
   StageSpec sp{state, state, tendency, 0.0, 0.0, 0.0, 0, 0, 0};
   rc = launch_stage(ctx, m, sp, t, false, 0.0);
   if (rc) return rc;
-  if (m->N > m->Na) {
+  if (m->N > m->Na && !cleared) {
     const int64_t row = static_cast<int64_t>(m->E) * m->F * m->field_bytes();
     const int64_t first = m->Na * row, bytes = (m->N - m->Na) * row;
     zero_rows_kernel<<<grid_for(bytes / 4, 256), 256, 0, ctx->stream>>>(tendency, first, bytes);
