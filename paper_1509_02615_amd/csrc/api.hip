@@ -80,6 +80,10 @@ int rbffd_create(rbffd_ctx **out, int device, void *hip_stream) {
 }
 
 int rbffd_destroy(rbffd_ctx *ctx) {
+  if (ctx && ctx->arena) {
+    (void)hipSetDevice(ctx->device);
+    (void)hipFree(ctx->arena);
+  }
   delete ctx;
   return RBFFD_OK;
 }
@@ -116,7 +120,10 @@ int rbffd_knn(rbffd_ctx *ctx, const rbffd_stencils *st, int32_t *idx) {
   if (st->n_centers == 0) return RBFFD_OK;  // empty batch: nothing to write
   if (!idx) return rbffd_fail(ctx, RBFFD_EINVAL, "null idx");
   RBFFD_ENTER(ctx);
-  Workspace ws;
+  const size_t bytes = CHECK_SCRATCH_BYTES + knn_scratch_bytes(st->n_nodes, st->n_centers);
+  ScratchLease mem(ctx, bytes);
+  if (!mem.get()) return rbffd_fail(ctx, RBFFD_ENOMEM, "device allocation of %zu bytes failed", bytes);
+  Workspace ws(mem.get(), bytes);
   rc = check_stencils_device(ctx, st, nullptr, 0, false, ws);
   if (rc) return rc;
   return knn_run(ctx, st, idx, ws);
@@ -158,6 +165,12 @@ static int check_weights_host(rbffd_ctx *ctx, const rbffd_stencils *st, const rb
   return RBFFD_OK;
 }
 
+// Scratch of a weights call: checks, search (unless the stencils are given), solves.
+static size_t weights_call_bytes(const rbffd_stencils *st) {
+  return CHECK_SCRATCH_BYTES + (st->idx_in ? 0 : knn_scratch_bytes(st->n_nodes, st->n_centers)) +
+         weights_scratch_bytes(st->n_centers);
+}
+
 // A1-A4 on a workspace: device argument checks (nothing is written before
 // they pass), the search (or a copy of the given stencils), then the solves
 // (tuned: one run per candidate launch shape, the fastest shape per size
@@ -194,7 +207,10 @@ int rbffd_weights(rbffd_ctx *ctx, const rbffd_stencils *st, const rbffd_op *ops,
   if (!w) return rbffd_fail(ctx, RBFFD_EINVAL, "null w");
   if (!st->idx_in && !idx) return rbffd_fail(ctx, RBFFD_EINVAL, "need idx output or idx_in");
   RBFFD_ENTER(ctx);
-  Workspace ws;
+  const size_t bytes = weights_call_bytes(st);
+  ScratchLease mem(ctx, bytes);
+  if (!mem.get()) return rbffd_fail(ctx, RBFFD_ENOMEM, "device allocation of %zu bytes failed", bytes);
+  Workspace ws(mem.get(), bytes);
   return weights_impl(ctx, st, ops, n_ops, precision, idx, w, status, ws);
 }
 
@@ -212,7 +228,10 @@ int rbffd_weights_tune(rbffd_ctx *ctx, const rbffd_stencils *st, const rbffd_op 
   if (!w) return rbffd_fail(ctx, RBFFD_EINVAL, "null w");
   if (!st->idx_in && !idx) return rbffd_fail(ctx, RBFFD_EINVAL, "need idx output or idx_in");
   RBFFD_ENTER(ctx);
-  Workspace ws;
+  const size_t bytes = weights_call_bytes(st);
+  ScratchLease mem(ctx, bytes);
+  if (!mem.get()) return rbffd_fail(ctx, RBFFD_ENOMEM, "device allocation of %zu bytes failed", bytes);
+  Workspace ws(mem.get(), bytes);
   return weights_impl(ctx, st, ops, n_ops, precision, idx, w, status, ws, true, shapes, bucket_ms);
 }
 

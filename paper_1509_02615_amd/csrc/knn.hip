@@ -654,6 +654,7 @@ int knn_run(rbffd_ctx *ctx, const rbffd_stencils *st, int32_t *idx, Workspace &w
     query_wide_kernel<<<n_over, KNN_BLOCK, 0, s>>>(st->xy, g, d_start, d_nodes, st->centers, st->n_per, st->n_max,
                                                    d_over, idx);
     RBFFD_HIP(ctx, hipGetLastError());
+    RBFFD_HIP(ctx, hipStreamSynchronize(s));  // results are complete on return, as after query_kernel
   }
   return RBFFD_OK;
 }
