@@ -34,9 +34,8 @@ struct Grid {
 
 __device__ __forceinline__ int cell_x(const Grid &g, double x) {
   int ix = static_cast<int>(floor((x - g.x0) / g.sx));
-  if (g.period > 0.0) {
-    ix %= g.ncx;
-    if (ix < 0) ix += g.ncx;
+  if (g.period > 0.0) {  // nodes lie within one period of x0
+    if (ix >= g.ncx) ix -= g.ncx;
   } else {
     ix = ix < 0 ? 0 : (ix >= g.ncx ? g.ncx - 1 : ix);
   }
@@ -274,27 +273,51 @@ __device__ __forceinline__ int block_cell(const Grid &g, const CellBlock &b, int
   return (b.z_lo + t / b.nxc) * g.ncx + ix;
 }
 
+// First radius of a search for nq nodes: enough cells for about nq nodes at the
+// mean density (the smallest r >= 1 with pi r^2 >= nq).
+__host__ __device__ inline int first_radius(int nq) {
+  int r = 1;
+  while (314159 * r * r < 100000 * nq) ++r;
+  return r;
+}
+
+// Inclusive sum over lanes 0 .. 31 by data-parallel moves (shifts by 1, 2, 4
+// and 8 within rows of 16, then row 0's total into row 1).
+__device__ __forceinline__ int scan32(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);  // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);  // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);  // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15 into row 1 (and 3)
+  return v;
+}
+
 // The usual query: one wavefront per centre, four per block, no barriers. The
 // block's candidates are held in registers (at most KNN_REG per lane); those
 // inside the radius that the block provably covers are compacted into LDS,
-// and each takes its place in the result by counting the smaller keys among
-// them (broadcast reads), so nothing is sorted and only about n / 0.75 keys
-// are compared. Bound by vector issue (the count loop) and the three
-// dependent loads cell start -> node number -> coordinates, which 32
-// wavefronts per compute unit hide: 4 KB of LDS per wavefront, where the
-// LDS sort below needs 25 KB and runs six. The whole search of the 524,288
-// centres of the 2048 x 256 channel (n = 37) takes 1.03 ms, against 6.06 ms
-// with every centre sorted in LDS. A centre whose block holds more
-// than KNN_KEYS candidates (denser than about 2.5 nodes per cell there) or more
-// than KNN_ROWS rows (a sparse one) goes to `over`, for query_list_kernel.
+// and each takes its place in the result by counting the keys with a smaller
+// distance (broadcast reads, two keys each); keys of equal distance (lattices
+// have many) meet in LDS and count the smaller node numbers among themselves.
+// So nothing is sorted and only about n / 0.75 keys are compared. Bound by
+// vector issue (the vector unit is busy throughout); 3 KB of LDS per wavefront,
+// where the LDS sort below needs 25 KB and runs six wavefronts per compute
+// unit. The whole search of the 524,288 centres of the 2048 x 256 channel
+// (n = 37) takes 0.57 ms (this kernel 0.46 ms, 495 vector instructions per
+// centre), against 6.06 ms with every centre sorted in LDS and 0.86 ms (917
+// instructions) with whole (d, j) keys compared and each candidate's row found
+// by a test per row. A centre whose block holds more than KNN_KEYS candidates
+// (denser than about 2.5 nodes per cell there) or more than KNN_ROWS rows (a
+// sparse one) goes to `over`, for query_list_kernel.
 constexpr int KNN_WAVES = 4;
 constexpr int KNN_REG = 4;
 constexpr int KNN_KEYS = 64 * KNN_REG;
 constexpr int KNN_ROWS = 32;
 
-struct __align__(16) Key {
-  double d;
-  int j, pad;
+struct KnnShared {
+  // distances of the candidates (then the sizes of the groups of equal ones);
+  // before them, the block's rows {shift, place of the second range, its shift}
+  double d[KNN_KEYS + 2];
+  int j[KNN_KEYS];  // their nodes, then the nodes by group
 };
 
 __device__ __forceinline__ void knn_wave_sync() {
@@ -305,9 +328,10 @@ __device__ __forceinline__ void knn_wave_sync() {
 
 __global__ __launch_bounds__(64 * KNN_WAVES) void query_kernel(
     const double *__restrict__ xy, Grid g, const int *__restrict__ start, const int *__restrict__ cell_nodes,
-    const int *__restrict__ centers, int n_centers, const int *__restrict__ n_per, int n_max, int *__restrict__ idx,
-    int *__restrict__ over, int *__restrict__ n_over) {
-  __shared__ Key s_keys[KNN_WAVES][KNN_KEYS];
+    const int *__restrict__ centers, int n_centers, const int *__restrict__ n_per, int n_max, int r_uniform,
+    int *__restrict__ idx, int *__restrict__ over, int *__restrict__ n_over) {
+  __shared__ __attribute__((aligned(16))) KnnShared s_all[KNN_WAVES];
+  static_assert(sizeof(KnnShared) % 16 == 0 && KNN_ROWS * 16 <= sizeof(double) * KNN_KEYS, "aligned views of LDS");
   // block ids go round-robin over the 8 XCDs: each XCD takes a contiguous
   // range of centres, whose candidates then stay in its L2
   const int nb = gridDim.x, full = (nb / 8) * 8, bid = blockIdx.x;
@@ -316,55 +340,56 @@ __global__ __launch_bounds__(64 * KNN_WAVES) void query_kernel(
   const int lane = threadIdx.x & 63;
   const int q = lb * KNN_WAVES + wave;
   if (q >= n_centers) return;
-  Key *keys = s_keys[wave];
-  const int c = centers ? centers[q] : q;
-  const int nq = n_per ? n_per[q] : n_max;
+  KnnShared &S = s_all[wave];
+  int4 *rows = reinterpret_cast<int4 *>(S.d);
+  int *group = reinterpret_cast<int *>(S.d);
+  const int c = __builtin_amdgcn_readfirstlane(centers ? centers[q] : q);
+  const int nq = __builtin_amdgcn_readfirstlane(n_per ? n_per[q] : n_max);
   const double2 *pt = reinterpret_cast<const double2 *>(xy);
   const double xc = xy[2 * static_cast<int64_t>(c)], zc = xy[2 * static_cast<int64_t>(c) + 1];
-  const int cx = cell_x(g, xc), cz = cell_z(g, zc);
+  const int cx = __builtin_amdgcn_readfirstlane(cell_x(g, xc)), cz = __builtin_amdgcn_readfirstlane(cell_z(g, zc));
   const double smin = fmin(g.sx, g.sz);
-  int r = max(1, static_cast<int>(ceil(sqrt(nq / 3.14159))));
+  int r = n_per ? first_radius(nq) : r_uniform;
   for (;; ++r) {
     const CellBlock b = cell_block(g, cx, cz, r);
     // lane t: the node ranges of the block's row t
     int a0 = 0, b0 = 0, a1 = 0, b1 = 0;
     if (b.nzc <= KNN_ROWS && lane < b.nzc) block_row(g, b, b.z_lo + lane, start, a0, b0, a1, b1);
     const int len0 = b0 - a0, len = len0 + (b1 - a1);
-    int incl = len;
-    for (int off = 1; off < KNN_ROWS; off <<= 1) {
-      const int v = __shfl_up(incl, off, 64);
-      if (lane >= off) incl += v;
-    }
+    const int incl = scan32(len);
     const int total = __builtin_amdgcn_readlane(incl, KNN_ROWS - 1);
     if (b.nzc > KNN_ROWS || total > KNN_KEYS) {
       if (lane == 0) over[atomicAdd(n_over, 1)] = q;
       return;
     }
-    // candidate lane + 64 u: its place in cell_nodes, row by row
-    const bool wraps = __ballot(b1 > a1) != 0;
-    const int first = incl - len;
-    int p[KNN_REG];
-#pragma unroll
-    for (int u = 0; u < KNN_REG; ++u) p[u] = -1;
+    // candidate k = lane + 64 u, in row order: its row is the number of rows
+    // that end at or before k
+    const int first = incl - len, n0 = first + len0;
+    knn_wave_sync();
+    if (lane < KNN_ROWS) rows[lane] = make_int4(a0 - first, n0, a1 - n0, 0);
+    knn_wave_sync();
+    int row[KNN_REG] = {};
     for (int t = 0; t < b.nzc; ++t) {
-      const int f = __builtin_amdgcn_readlane(first, t), e = __builtin_amdgcn_readlane(incl, t);
-      const int s0 = __builtin_amdgcn_readlane(a0, t) - f;
-      const int n0 = f + __builtin_amdgcn_readlane(len0, t);
-      const int s1 = wraps ? __builtin_amdgcn_readlane(a1, t) - n0 : 0;
+      const int e = __builtin_amdgcn_readlane(incl, t);
 #pragma unroll
-      for (int u = 0; u < KNN_REG; ++u) {
-        const int k = lane + 64 * u;
-        if (64 * u < total && k >= f && k < e) p[u] = k + (k < n0 ? s0 : s1);
-      }
+      for (int u = 0; u < KNN_REG; ++u)
+        if (64 * u < total) row[u] += lane + 64 * u >= e ? 1 : 0;
     }
     int j[KNN_REG];
     double d[KNN_REG];
 #pragma unroll
-    for (int u = 0; u < KNN_REG; ++u) j[u] = p[u] >= 0 ? cell_nodes[p[u]] : -1;
+    for (int u = 0; u < KNN_REG; ++u) {
+      j[u] = -1;
+      if (64 * u < total) {
+        const int k = lane + 64 * u;
+        const int4 w = rows[min(row[u], KNN_ROWS - 1)];
+        if (k < total) j[u] = cell_nodes[k + (k < w.y ? w.x : w.z)];
+      }
+    }
 #pragma unroll
     for (int u = 0; u < KNN_REG; ++u) {
       d[u] = INFINITY;
-      if (j[u] >= 0) {
+      if (64 * u < total && j[u] >= 0) {
         const double2 v = pt[j[u]];
         d[u] = key_d2(v.x, v.y, xc, zc, g.period);
       }
@@ -376,27 +401,68 @@ __global__ __launch_bounds__(64 * KNN_WAVES) void query_kernel(
     knn_wave_sync();
 #pragma unroll
     for (int u = 0; u < KNN_REG; ++u) {
-      const bool in = j[u] >= 0 && (b.covered || d[u] < lim);
-      const uint64_t m = __ballot(in);
-      if (in) {
-        const int at = cnt + __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(m >> 32),
-                                                       __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(m), 0));
-        keys[at] = Key{d[u], j[u], 0};
+      if (64 * u < total) {
+        const bool in = j[u] >= 0 && (b.covered || d[u] < lim);
+        const uint64_t m = __ballot(in);
+        if (in) {
+          const int at = cnt + __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(m >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(m), 0));
+          S.d[at] = d[u];
+          S.j[at] = j[u];
+        }
+        cnt += __popcll(m);
       }
-      cnt += __popcll(m);
     }
     if (cnt < nq) {
       if (b.covered) return;  // fewer nodes than nq: ruled out by the argument checks
       continue;
     }
+    if (lane == 0) S.d[cnt] = INFINITY;  // pairs: an odd count's last partner
+    knn_wave_sync();
+    // keys lane + 64 u: smaller distances counted
+    int rank[KNN_REG];
+#pragma unroll
+    for (int u = 0; u < KNN_REG; ++u) {
+      rank[u] = 0;
+      const int at = lane + 64 * u;
+      if (64 * u < cnt) {
+        d[u] = at < cnt ? S.d[at] : -1.0;  // (nothing is smaller)
+        j[u] = at < cnt ? S.j[at] : 0;
+      }
+    }
+    const double2 *pairs = reinterpret_cast<const double2 *>(S.d);
+#pragma unroll 4
+    for (int k = 0; k < cnt; k += 2) {
+      const double2 v = pairs[k >> 1];
+#pragma unroll
+      for (int u = 0; u < KNN_REG; ++u)
+        if (64 * u < cnt) {
+          rank[u] += v.x < d[u] ? 1 : 0;
+          rank[u] += v.y < d[u] ? 1 : 0;
+        }
+    }
+    knn_wave_sync();
+    // groups of equal distances: members meet at places rank .. rank + size - 1
+#pragma unroll
+    for (int u = 0; u < KNN_REG; ++u)
+      if (64 * u < cnt) group[lane + 64 * u] = 0;
+    knn_wave_sync();
+#pragma unroll
+    for (int u = 0; u < KNN_REG; ++u)
+      if (lane + 64 * u < cnt) S.j[rank[u] + atomicAdd(&group[rank[u]], 1)] = j[u];
     knn_wave_sync();
     int *out = idx + static_cast<int64_t>(q) * n_max;
-    for (int at = lane; at < cnt; at += 64) {
-      const Key own = keys[at];
-      int rank = 0;
-#pragma unroll 4
-      for (int k = 0; k < cnt; ++k) rank += key_less(keys[k].d, keys[k].j, own.d, own.j) ? 1 : 0;
-      if (rank < nq) out[rank] = own.j;
+#pragma unroll
+    for (int u = 0; u < KNN_REG; ++u) {
+      if (64 * u < cnt) {
+        const bool in = lane + 64 * u < cnt;
+        const int size = in ? group[rank[u]] : 0;
+        int place = rank[u];
+        if (__ballot(size > 1) != 0)
+          for (int t = 0; __ballot(t < size) != 0; ++t)
+            if (t < size) place += S.j[rank[u] + t] < j[u] ? 1 : 0;
+        if (in && place < nq) out[place] = j[u];
+      }
     }
     for (int k = nq + lane; k < n_max; k += 64) out[k] = -1;
     return;
@@ -425,9 +491,7 @@ __global__ __launch_bounds__(KNN_BLOCK) void query_list_kernel(
   const double xc = xy[2 * c], zc = xy[2 * c + 1];
   const int cx = cell_x(g, xc), cz = cell_z(g, zc);
   const double smin = fmin(g.sx, g.sz);
-  // first radius: enough cells for about nq nodes at the mean density
-  int r = static_cast<int>(ceil(sqrt(nq / 3.14159)));
-  if (r < 1) r = 1;
+  int r = first_radius(nq);
   for (;;) {
     const CellBlock b = cell_block(g, cx, cz, r);
     const int ncb = b.nxc * b.nzc;
@@ -519,7 +583,7 @@ __global__ __launch_bounds__(KNN_BLOCK) void query_wide_kernel(
   const double xc = xy[2 * c], zc = xy[2 * c + 1];
   const int cx = cell_x(g, xc), cz = cell_z(g, zc);
   const double smin = fmin(g.sx, g.sz);
-  int r = max(1, static_cast<int>(ceil(sqrt(nq / 3.14159))));
+  int r = first_radius(nq);
   for (;;) {
     const CellBlock b = cell_block(g, cx, cz, r);
     int my = 0;
@@ -643,7 +707,8 @@ int knn_run(rbffd_ctx *ctx, const rbffd_stencils *st, int32_t *idx, Workspace &w
   scan_write_kernel<<<tiles, SCAN_THREADS, 0, s>>>(d_count, ncell, d_tiles, d_start);
   scatter_kernel<<<grid_for(n, 256), 256, 0, s>>>(st->xy, n, g, d_start, d_count, d_nodes);
   query_kernel<<<grid_for(nc, KNN_WAVES), 64 * KNN_WAVES, 0, s>>>(st->xy, g, d_start, d_nodes, st->centers, nc,
-                                                                  st->n_per, st->n_max, idx, d_over, d_nover);
+                                                                  st->n_per, st->n_max, first_radius(st->n_max), idx,
+                                                                  d_over, d_nover);
   RBFFD_HIP(ctx, hipGetLastError());
   int n_over = 0;
   RBFFD_HIP(ctx, hipMemcpyAsync(&n_over, d_nover, sizeof(int), hipMemcpyDeviceToHost, s));
