@@ -99,7 +99,8 @@ __device__ __forceinline__ bf8v gather_block(const float *__restrict__ y, const 
   return x;
 }
 
-// Y[s][0..3] for S samples, T tiles of 16 samples per wavefront; blocks of
+// Y[s][0..3] for S samples (and bad[e] = stamp for members with a value that
+// is not finite, unless bad is NULL), T tiles of 16 samples per wavefront; blocks of
 // W wavefronts share one LDS copy of the weights and loop over contiguous
 // unit ranges (XCD-aware block order); OCC wavefronts per SIMD bound the
 // registers. The launch shapes (T, W, OCC) rbffd_closure_tune chooses from
@@ -112,7 +113,7 @@ __global__ __launch_bounds__(64 * MLP_WAVES) __attribute__((amdgpu_waves_per_eu(
 mlp_forward_kernel(
     const float *__restrict__ y, const int *__restrict__ idx_t, int64_t Na, int E,
     const float *__restrict__ nodef, float4 inv, const __bf16 *__restrict__ frag_g, const float *__restrict__ params,
-    float *__restrict__ Y, int64_t S) {
+    float *__restrict__ Y, int64_t S, int *__restrict__ bad, int stamp) {
   extern __shared__ __attribute__((aligned(16))) unsigned char mlp_lds[];
   const bf8v *s_frag = reinterpret_cast<const bf8v *>(mlp_lds);
   float *s_bias = reinterpret_cast<float *>(mlp_lds + static_cast<size_t>(NFRAG) * 64 * 16);
@@ -211,7 +212,11 @@ mlp_forward_kernel(
 #pragma unroll
       for (int tl = 0; tl < T; ++tl) {
         const int64_t s = base + 16 * tl + r;
-        if (s < S) *reinterpret_cast<float4 *>(Y + s * 4) = make_float4(out[tl][0], out[tl][1], out[tl][2], out[tl][3]);
+        if (s < S) {
+          *reinterpret_cast<float4 *>(Y + s * 4) = make_float4(out[tl][0], out[tl][1], out[tl][2], out[tl][3]);
+          if (bad && !(isfinite(out[tl][0]) && isfinite(out[tl][1]) && isfinite(out[tl][2]) && isfinite(out[tl][3])))
+            bad[se[tl]] = stamp;  // (any such sample of the member writes the same)
+        }
       }
     }
   }
@@ -724,31 +729,25 @@ __global__ void adam_kernel(float *__restrict__ p, const float *__restrict__ g, 
   p[t] -= lr * (a / c1) / (sqrtf(v / c2) + eps);
 }
 
-// Per member: 1 if any correction value of that member is not finite.
-__global__ void check_kernel(const float *__restrict__ Y, int ys, int64_t Na, int E, int *__restrict__ bad) {
+// y_active += dt * Y * out_scale, except for members whose correction is not
+// finite (bad[e] = stamp); each of those counts once in `fallback`.
+__global__ void apply_kernel(float *__restrict__ y, const float *__restrict__ Y, int64_t Na, int E,
+                             const int *__restrict__ bad, int stamp, unsigned long long *__restrict__ fallback,
+                             float4 out_scale, float dt) {
   const int64_t s = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (s >= Na * E) return;
   const int e = static_cast<int>(s % E);
-  for (int c = 0; c < 4; ++c)
-    if (!isfinite(Y[s * ys + c])) {
-      atomicOr(bad + e, 1);
-      return;
-    }
-}
-
-// y_active += dt * Y * out_scale, except for members flagged non-finite.
-__global__ void apply_kernel(float *__restrict__ y, const float *__restrict__ Y, int ys, int64_t Na, int E,
-                             const int *__restrict__ bad, float4 out_scale, float dt) {
-  const int64_t s = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (s >= Na * E) return;
-  const int e = static_cast<int>(s % E);
-  if (bad[e]) return;
-  float *o = y + s * 4;
-  const float *q = Y + s * ys;
-  o[0] += dt * q[0] * out_scale.x;
-  o[1] += dt * q[1] * out_scale.y;
-  o[2] += dt * q[2] * out_scale.z;
-  o[3] += dt * q[3] * out_scale.w;
+  if (bad[e] == stamp) {
+    if (s < E) atomicAdd(fallback, 1ull);
+    return;
+  }
+  float4 o = *reinterpret_cast<const float4 *>(y + s * 4);
+  const float4 q = *reinterpret_cast<const float4 *>(Y + s * 4);
+  o.x += dt * q.x * out_scale.x;
+  o.y += dt * q.y * out_scale.y;
+  o.z += dt * q.z * out_scale.z;
+  o.w += dt * q.w * out_scale.w;
+  *reinterpret_cast<float4 *>(y + s * 4) = o;
 }
 
 __global__ void scale_out_kernel(const float *__restrict__ Y, int ys, int64_t S, float4 sc, float *__restrict__ out) {
@@ -786,7 +785,7 @@ struct rbffd_closure {
   DevBuf w1, w2, w3;                                 // BF16 weights
   DevBuf part, part_loss;                            // training: each block's partial gradient and loss
   DevBuf frag, Yc;                                   // fused forward: packed weights, Y [S][4]
-  DevBuf loss, bad;
+  DevBuf loss, bad, fallback;                        // bad: per member, the step (from 1) of the last bad correction
   int64_t step = 0;
   int act = RBFFD_ACT_TANH;
   int shape = 0;  // fused forward launch shape (rbffd_closure_tune)
@@ -850,7 +849,7 @@ void set_mlp_lds(bool &ok) {
 // compute unit: as many as LDS (160 KB, 77 KB of packed weights each) and the
 // SIMDs' wavefront slots allow; the grid is one wave of them.
 template <int SH>
-void launch_forward(rbffd_ctx *ctx, rbffd_closure *cl, const void *state, int64_t S) {
+void launch_forward(rbffd_ctx *ctx, rbffd_closure *cl, const void *state, int64_t S, int *bad, int stamp) {
   constexpr MlpShape sh = kMlpShapes[SH];
   rbffd_model *m = cl->model;
   constexpr int per_cu = std::min<int>(static_cast<int>((160 * 1024) / MLP_LDS), 4 * sh.occ / sh.waves);
@@ -861,16 +860,16 @@ void launch_forward(rbffd_ctx *ctx, rbffd_closure *cl, const void *state, int64_
   auto kern = cl->act == RBFFD_ACT_RELU ? mlp_kernel<SH, RBFFD_ACT_RELU>() : mlp_kernel<SH, RBFFD_ACT_TANH>();
   kern<<<nb, 64 * sh.waves, MLP_LDS, ctx->stream>>>(static_cast<const float *>(state), cl->idx.as<int>(), m->Na,
                                                     m->E, cl->nodef.as<float>(), cl->inv_in, cl->frag.as<__bf16>(),
-                                                    cl->params.as<float>(), cl->Yc.as<float>(), S);
+                                                    cl->params.as<float>(), cl->Yc.as<float>(), S, bad, stamp);
 }
 
-int forward_fused(rbffd_ctx *ctx, rbffd_closure *cl, const void *state, int64_t S) {
+int forward_fused(rbffd_ctx *ctx, rbffd_closure *cl, const void *state, int64_t S, int *bad = nullptr, int stamp = 0) {
   switch (cl->shape) {
-    case 1: launch_forward<1>(ctx, cl, state, S); break;
-    case 2: launch_forward<2>(ctx, cl, state, S); break;
-    case 3: launch_forward<3>(ctx, cl, state, S); break;
-    case 4: launch_forward<4>(ctx, cl, state, S); break;
-    default: launch_forward<0>(ctx, cl, state, S); break;
+    case 1: launch_forward<1>(ctx, cl, state, S, bad, stamp); break;
+    case 2: launch_forward<2>(ctx, cl, state, S, bad, stamp); break;
+    case 3: launch_forward<3>(ctx, cl, state, S, bad, stamp); break;
+    case 4: launch_forward<4>(ctx, cl, state, S, bad, stamp); break;
+    default: launch_forward<0>(ctx, cl, state, S, bad, stamp); break;
   }
   RBFFD_HIP(ctx, hipGetLastError());
   return RBFFD_OK;
@@ -905,7 +904,7 @@ int closure_create(rbffd_ctx *ctx, rbffd_model *m, const rbffd_closure_desc *d, 
             cl->w1.alloc(b2 * HID * KIN) == hipSuccess && cl->w2.alloc(b2 * HID * HID) == hipSuccess &&
             cl->w3.alloc(b2 * NOUT * HID) == hipSuccess && cl->part.alloc(4 * NPARAM * n_cu) == hipSuccess &&
             cl->part_loss.alloc(8 * n_cu) == hipSuccess && cl->loss.alloc(8) == hipSuccess &&
-            cl->bad.alloc(4 * m->E) == hipSuccess && cl->frag.alloc(b2 * NFRAG * 512) == hipSuccess &&
+            cl->bad.alloc(4 * m->E) == hipSuccess && cl->fallback.alloc(8) == hipSuccess && cl->frag.alloc(b2 * NFRAG * 512) == hipSuccess &&
             cl->Yc.alloc(4 * Sx * 4) == hipSuccess;
   if (!ok) {
     delete cl;
@@ -1025,25 +1024,25 @@ int closure_step(rbffd_ctx *ctx, rbffd_closure *cl, void *state, double *t, doub
   rbffd_model *m = cl->model;
   const int64_t S = m->Na * m->E;
   hipStream_t s = ctx->stream;
-  int64_t fb = 0;
-  std::vector<int> hb(m->E);
+  RBFFD_HIP(ctx, hipMemsetAsync(cl->bad.p, 0, cl->bad.bytes, s));
+  RBFFD_HIP(ctx, hipMemsetAsync(cl->fallback.p, 0, 8, s));
   for (int64_t k = 0; k < n_steps; ++k) {
+    const int stamp = static_cast<int>(k % INT32_MAX) + 1;
     int rc = model_ghost(ctx, m, state);
-    if (!rc) rc = forward_fused(ctx, cl, state, S);  // correction of the state before the step
-    if (!rc) rc = model_step(ctx, m, state, t, dt, 1, tableau);
+    if (!rc) rc = forward_fused(ctx, cl, state, S, cl->bad.as<int>(), stamp);  // correction of the state before the step
+    if (!rc) rc = model_step(ctx, m, state, t, dt, 1, tableau, true);
     if (rc) return rc;
-    RBFFD_HIP(ctx, hipMemsetAsync(cl->bad.p, 0, sizeof(int) * m->E, s));
-    check_kernel<<<grid_for(S, 256), 256, 0, s>>>(cl->Yc.as<float>(), 4, m->Na, m->E, cl->bad.as<int>());
-    apply_kernel<<<grid_for(S, 256), 256, 0, s>>>(static_cast<float *>(state), cl->Yc.as<float>(), 4, m->Na, m->E,
-                                                  cl->bad.as<int>(), cl->out_sc, static_cast<float>(dt));
+    apply_kernel<<<grid_for(S, 256), 256, 0, s>>>(static_cast<float *>(state), cl->Yc.as<float>(), m->Na, m->E,
+                                                  cl->bad.as<int>(), stamp, cl->fallback.as<unsigned long long>(),
+                                                  cl->out_sc, static_cast<float>(dt));
     RBFFD_HIP(ctx, hipGetLastError());
-    if (n_fallback) {
-      RBFFD_HIP(ctx, hipMemcpyAsync(hb.data(), cl->bad.p, sizeof(int) * m->E, hipMemcpyDeviceToHost, s));
-      RBFFD_HIP(ctx, hipStreamSynchronize(s));
-      for (int v : hb) fb += v;
-    }
   }
-  if (n_fallback) *n_fallback = fb;
+  if (n_fallback) {
+    unsigned long long fb = 0;
+    RBFFD_HIP(ctx, hipMemcpyAsync(&fb, cl->fallback.p, 8, hipMemcpyDeviceToHost, s));
+    RBFFD_HIP(ctx, hipStreamSynchronize(s));
+    *n_fallback = static_cast<int64_t>(fb);
+  }
   return RBFFD_OK;
 }
 

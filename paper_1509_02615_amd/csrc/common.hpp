@@ -223,8 +223,9 @@ int model_create_impl(rbffd_ctx *ctx, const rbffd_model_desc *d, rbffd_model **o
 int model_destroy_impl(rbffd_model *m);
 int model_ghost(rbffd_ctx *ctx, rbffd_model *m, void *state);
 int model_rhs(rbffd_ctx *ctx, rbffd_model *m, double t, void *state, void *tendency);
+// `closed`: the state's ghosts have just been closed (model_ghost).
 int model_step(rbffd_ctx *ctx, rbffd_model *m, void *state, double *t, double dt,
-               int64_t n_steps, int tableau);
+               int64_t n_steps, int tableau, bool closed = false);
 int64_t model_bytes_per_node(rbffd_model *m);
 int model_profile(rbffd_model *m, int enable);
 int model_profile_read(rbffd_model *m, double *total_ms, int64_t *launches);

@@ -730,6 +730,8 @@ int model_destroy_impl(rbffd_model *m) {
   if (m->graph) (void)hipGraphDestroy(m->graph);
   if (m->exec_n) (void)hipGraphExecDestroy(m->exec_n);
   if (m->graph_n) (void)hipGraphDestroy(m->graph_n);
+  if (m->exec_c) (void)hipGraphExecDestroy(m->exec_c);
+  if (m->graph_c) (void)hipGraphDestroy(m->graph_c);
   delete m;
   return RBFFD_OK;
 }

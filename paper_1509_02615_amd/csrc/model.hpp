@@ -99,6 +99,8 @@ struct rbffd_model {
   hipGraphExec_t exec = nullptr;
   hipGraph_t graph_n = nullptr;    // GRAPH_STEPS captured steps
   hipGraphExec_t exec_n = nullptr;
+  hipGraph_t graph_c = nullptr;    // one captured step from a state whose ghosts are closed
+  hipGraphExec_t exec_c = nullptr;
   void *graph_state = nullptr;
   double graph_dt = 0.0;
   int graph_tableau = -1;

@@ -1096,8 +1096,9 @@ bool needs_ghost(const rbffd_model *m, const StageSpec &sp, const void *y) {
 }
 
 // One full time step, number `step` after the device's step counter, as a
-// sequence of launches on the context stream.
-int enqueue_step(rbffd_ctx *ctx, rbffd_model *m, void *y, double dt, int tableau, int step) {
+// sequence of launches on the context stream; `closed`: the caller has just
+// closed the state's ghosts.
+int enqueue_step(rbffd_ctx *ctx, rbffd_model *m, void *y, double dt, int tableau, int step, bool closed) {
   int rc;
   void *ya = m->ya.p, *yb = m->yb.p;
   if (tableau == RBFFD_RK4) {
@@ -1109,7 +1110,7 @@ int enqueue_step(rbffd_ctx *ctx, rbffd_model *m, void *y, double dt, int tableau
     };
     for (StageSpec sp : st) {
       sp.step = step;
-      if (needs_ghost(m, sp, y) && (rc = launch_ghost(ctx, m, const_cast<void *>(sp.ys)))) return rc;
+      if (!(closed && sp.ys == y) && needs_ghost(m, sp, y) && (rc = launch_ghost(ctx, m, const_cast<void *>(sp.ys)))) return rc;
       if ((rc = launch_stage(ctx, m, sp, 0.0, true, dt))) return rc;
     }
   } else {
@@ -1120,7 +1121,7 @@ int enqueue_step(rbffd_ctx *ctx, rbffd_model *m, void *y, double dt, int tableau
     };
     for (StageSpec sp : st) {
       sp.step = step;
-      if (needs_ghost(m, sp, y) && (rc = launch_ghost(ctx, m, const_cast<void *>(sp.ys)))) return rc;
+      if (!(closed && sp.ys == y) && needs_ghost(m, sp, y) && (rc = launch_ghost(ctx, m, const_cast<void *>(sp.ys)))) return rc;
       if ((rc = launch_stage(ctx, m, sp, 0.0, true, dt))) return rc;
     }
   }
@@ -1128,9 +1129,9 @@ int enqueue_step(rbffd_ctx *ctx, rbffd_model *m, void *y, double dt, int tableau
 }
 
 // n steps, and the device's step counter past them.
-int enqueue_steps(rbffd_ctx *ctx, rbffd_model *m, void *y, double dt, int tableau, int n) {
+int enqueue_steps(rbffd_ctx *ctx, rbffd_model *m, void *y, double dt, int tableau, int n, bool closed) {
   for (int k = 0; k < n; ++k) {
-    const int rc = enqueue_step(ctx, m, y, dt, tableau, k);
+    const int rc = enqueue_step(ctx, m, y, dt, tableau, k, closed && k == 0);
     if (rc) return rc;
   }
   tick_kernel<<<1, 1, 0, ctx->stream>>>(m->dev_misc.as<DevMisc>(), n);
@@ -1171,13 +1172,15 @@ void drop_graphs(rbffd_model *m) {
   if (m->graph) (void)hipGraphDestroy(m->graph);
   if (m->exec_n) (void)hipGraphExecDestroy(m->exec_n);
   if (m->graph_n) (void)hipGraphDestroy(m->graph_n);
-  m->exec = m->exec_n = nullptr;
-  m->graph = m->graph_n = nullptr;
+  if (m->exec_c) (void)hipGraphExecDestroy(m->exec_c);
+  if (m->graph_c) (void)hipGraphDestroy(m->graph_c);
+  m->exec = m->exec_n = m->exec_c = nullptr;
+  m->graph = m->graph_n = m->graph_c = nullptr;
 }
 
 // Captures k steps into one graph and instantiates it.
-int capture_steps(rbffd_ctx *ctx, rbffd_model *m, void *state, double dt, int tableau, int k, hipGraph_t *graph_out,
-                  hipGraphExec_t *exec_out) {
+int capture_steps(rbffd_ctx *ctx, rbffd_model *m, void *state, double dt, int tableau, int k, bool closed,
+                  hipGraph_t *graph_out, hipGraphExec_t *exec_out) {
   hipStream_t cs = ctx->stream;
   bool own_stream = false;
   if (cs == nullptr) {  // the null stream cannot be captured
@@ -1191,7 +1194,7 @@ int capture_steps(rbffd_ctx *ctx, rbffd_model *m, void *state, double dt, int ta
   hipGraph_t graph = nullptr;
   hipError_t ec = eb;
   if (eb == hipSuccess) {
-    rc = enqueue_steps(ctx, m, state, dt, tableau, k);
+    rc = enqueue_steps(ctx, m, state, dt, tableau, k, closed);
     ec = hipStreamEndCapture(cs, &graph);
   }
   ctx->stream = saved;
@@ -1207,20 +1210,21 @@ int capture_steps(rbffd_ctx *ctx, rbffd_model *m, void *state, double dt, int ta
 
 }  // namespace
 
-int model_step(rbffd_ctx *ctx, rbffd_model *m, void *state, double *t, double dt, int64_t n_steps, int tableau) {
+int model_step(rbffd_ctx *ctx, rbffd_model *m, void *state, double *t, double dt, int64_t n_steps, int tableau,
+               bool closed) {
   if (n_steps == 0) return RBFFD_OK;
   hipStream_t s = ctx->stream;
   misc_init_kernel<<<1, 1, 0, s>>>(m->dev_misc.as<DevMisc>(), *t);
   RBFFD_HIP(ctx, hipGetLastError());
   if (m->profile) {
     for (int64_t k = 0; k < n_steps; ++k) {
-      int rc = enqueue_steps(ctx, m, state, dt, tableau, 1);
+      int rc = enqueue_steps(ctx, m, state, dt, tableau, 1, closed && k == 0);
       if (rc) return rc;
     }
   } else {
     // graphs are captured for one (state, dt, tableau) and only when a call
     // needs them: the eight-step graph for n_steps >= 8, the one-step graph
-    // for a remainder
+    // for a remainder, and the one-step graph that starts from closed ghosts
     if (m->graph_state != state || m->graph_dt != dt || m->graph_tableau != tableau) {
       drop_graphs(m);
       m->graph_state = state;
@@ -1228,16 +1232,22 @@ int model_step(rbffd_ctx *ctx, rbffd_model *m, void *state, double *t, double dt
       m->graph_tableau = tableau;
     }
     int rc = RBFFD_OK;
-    if (n_steps >= GRAPH_STEPS && !m->exec_n)
-      rc = capture_steps(ctx, m, state, dt, tableau, GRAPH_STEPS, &m->graph_n, &m->exec_n);
-    if (rc == RBFFD_OK && n_steps % GRAPH_STEPS != 0 && !m->exec)
-      rc = capture_steps(ctx, m, state, dt, tableau, 1, &m->graph, &m->exec);
+    const int64_t rest = n_steps - (closed ? 1 : 0);
+    if (closed && !m->exec_c) rc = capture_steps(ctx, m, state, dt, tableau, 1, true, &m->graph_c, &m->exec_c);
+    if (rc == RBFFD_OK && rest >= GRAPH_STEPS && !m->exec_n)
+      rc = capture_steps(ctx, m, state, dt, tableau, GRAPH_STEPS, false, &m->graph_n, &m->exec_n);
+    if (rc == RBFFD_OK && rest % GRAPH_STEPS != 0 && !m->exec)
+      rc = capture_steps(ctx, m, state, dt, tableau, 1, false, &m->graph, &m->exec);
     if (rc) {
       drop_graphs(m);
       m->graph_state = nullptr;
       return rc;
     }
     int64_t k = 0;
+    if (closed) {
+      RBFFD_HIP(ctx, hipGraphLaunch(m->exec_c, s));
+      ++k;
+    }
     for (; k + GRAPH_STEPS <= n_steps; k += GRAPH_STEPS) RBFFD_HIP(ctx, hipGraphLaunch(m->exec_n, s));
     for (; k < n_steps; ++k) RBFFD_HIP(ctx, hipGraphLaunch(m->exec, s));
   }
