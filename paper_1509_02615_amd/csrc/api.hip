@@ -124,9 +124,10 @@ int rbffd_knn(rbffd_ctx *ctx, const rbffd_stencils *st, int32_t *idx) {
   ScratchLease mem(ctx, bytes);
   if (!mem.get()) return rbffd_fail(ctx, RBFFD_ENOMEM, "device allocation of %zu bytes failed", bytes);
   Workspace ws(mem.get(), bytes);
-  rc = check_stencils_device(ctx, st, nullptr, 0, false, ws);
+  int *flag;
+  rc = check_launch(ctx, st, nullptr, 0, false, ws, &flag);
   if (rc) return rc;
-  return knn_run(ctx, st, idx, ws);
+  return knn_run(ctx, st, idx, ws, flag);
 }
 
 // Checks of the uniform arguments of a weights call that need no device.
@@ -178,14 +179,21 @@ static size_t weights_call_bytes(const rbffd_stencils *st) {
 static int weights_impl(rbffd_ctx *ctx, const rbffd_stencils *st, const rbffd_op *ops, int n_ops, int precision,
                         int32_t *idx, double *w, int32_t *status, Workspace &ws, bool tune = false,
                         int32_t *shapes = nullptr, double *ms = nullptr) {
-  int rc = check_stencils_device(ctx, st, ops, n_ops, true, ws);
+  int *flag;
+  int rc = check_launch(ctx, st, ops, n_ops, true, ws, &flag);
   if (rc) return rc;
   const int32_t *use_idx = st->idx_in;
   if (!use_idx) {
-    rc = knn_run(ctx, st, idx, ws);
+    rc = knn_run(ctx, st, idx, ws, flag);
     if (rc) return rc;
     use_idx = idx;
-  } else if (idx) {
+  } else {
+    int f[2];
+    RBFFD_HIP(ctx, hipMemcpyAsync(f, flag, sizeof(f), hipMemcpyDeviceToHost, ctx->stream));
+    RBFFD_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    if ((rc = check_result(ctx, st, f)) != RBFFD_OK) return rc;
+  }
+  if (st->idx_in && idx) {
     RBFFD_HIP(ctx, hipMemcpyAsync(idx, st->idx_in, sizeof(int32_t) * st->n_centers * st->n_max,
                                   hipMemcpyDeviceToDevice, ctx->stream));
   }

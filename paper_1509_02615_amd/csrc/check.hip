@@ -31,7 +31,8 @@ struct CheckArgs {
   int k_max;  // largest k of the Laplacian^k operators that take the stencil's own m (0: none)
 };
 
-// flag[0]: OR of the reasons, flag[1]: smallest bad stencil
+// flag[0]: OR of the reasons, flag[1]: n_centers - the smallest bad stencil
+// (both 0 when all is well)
 __global__ void check_params_kernel(CheckArgs a, int *flag) {
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
   int bad = 0;
@@ -57,7 +58,7 @@ __global__ void check_params_kernel(CheckArgs a, int *flag) {
   if (__ballot(bad != 0) == 0) return;  // the usual case: one vote per wavefront
   if (bad) {
     atomicOr(&flag[0], bad);
-    atomicMin(&flag[1], q);
+    atomicMax(&flag[1], a.n_centers - q);
   }
 }
 
@@ -79,14 +80,14 @@ __global__ void check_index_kernel(CheckArgs a, int *flag) {
   if (__ballot(bad) == 0) return;
   if (bad) {
     atomicOr(&flag[0], BAD_INDEX);
-    atomicMin(&flag[1], q);
+    atomicMax(&flag[1], a.n_centers - q);
   }
 }
 
 }  // namespace
 
-int check_stencils_device(rbffd_ctx *ctx, const rbffd_stencils *st, const rbffd_op *ops, int n_ops, bool weights,
-                          Workspace &ws) {
+int check_launch(rbffd_ctx *ctx, const rbffd_stencils *st, const rbffd_op *ops, int n_ops, bool weights, Workspace &ws,
+                 int **flag) {
   CheckArgs a{};
   a.centers = st->centers;
   a.n_per = st->n_per;
@@ -104,17 +105,18 @@ int check_stencils_device(rbffd_ctx *ctx, const rbffd_stencils *st, const rbffd_
   hipStream_t s = ctx->stream;
   int *d_flag;
   RBFFD_WS(ctx, ws, ws.get(2, &d_flag));
-  const int init[2] = {0, a.n_centers};
-  RBFFD_HIP(ctx, hipMemcpyAsync(d_flag, init, sizeof(init), hipMemcpyHostToDevice, s));
+  RBFFD_HIP(ctx, hipMemsetAsync(d_flag, 0, 2 * sizeof(int), s));
   check_params_kernel<<<grid_for(a.n_centers, 256), 256, 0, s>>>(a, d_flag);
   if (a.idx_in) {
     const int64_t total = static_cast<int64_t>(a.n_centers) * a.n_max;
     check_index_kernel<<<grid_for(total, 256), 256, 0, s>>>(a, d_flag);
   }
   RBFFD_HIP(ctx, hipGetLastError());
-  int flag[2];
-  RBFFD_HIP(ctx, hipMemcpyAsync(flag, d_flag, sizeof(flag), hipMemcpyDeviceToHost, s));
-  RBFFD_HIP(ctx, hipStreamSynchronize(s));
+  *flag = d_flag;
+  return RBFFD_OK;
+}
+
+int check_result(rbffd_ctx *ctx, const rbffd_stencils *st, const int (&flag)[2]) {
   if (!flag[0]) return RBFFD_OK;
   const int f = flag[0];
   const char *why = (f & BAD_CENTER) ? "centre index outside the node set"
@@ -125,5 +127,5 @@ int check_stencils_device(rbffd_ctx *ctx, const rbffd_stencils *st, const rbffd_
                     : (f & BAD_SIZE) ? "system size n + M above 128"
                     : (f & BAD_HYPERLAP) ? "Laplacian^k of r^m not continuous (m < 2k + 1)"
                                          : "given stencil index outside the node set";
-  return rbffd_fail(ctx, RBFFD_EINVAL, "stencil %d: %s (nothing written)", flag[1], why);
+  return rbffd_fail(ctx, RBFFD_EINVAL, "stencil %d: %s (nothing written)", static_cast<int>(st->n_centers) - flag[1], why);
 }

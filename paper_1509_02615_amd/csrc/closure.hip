@@ -27,6 +27,7 @@ constexpr int OW1 = 0, OB1 = OW1 + HID * KIN, OW2 = OB1 + HID, OB2 = OW2 + HID *
 static_assert(NPARAM == RBFFD_CLOSURE_NPARAMS, "parameter layout");
 
 typedef __attribute__((ext_vector_type(4))) float f4v;
+typedef f4v f4u __attribute__((aligned(4)));  // a caller's rows of four floats, aligned as floats
 typedef __attribute__((ext_vector_type(8))) __bf16 bf8v;
 
 // ---- fused forward pass -------------------------------------------------
@@ -79,18 +80,17 @@ template <int ACT> __device__ __forceinline__ float act_fn(float v) {
 // Input fragment of contraction block j for one sample: slots 8j + 2g and
 // 8j + 2g + 1 (four fields each). Branch-free: a slot past the stencil
 // re-reads the node itself (difference 0); slot 37 carries the node value.
-__device__ __forceinline__ bf8v gather_block(const float *__restrict__ y, const int *__restrict__ idx_t, int64_t Na,
-                                             int E, float nodev, float4 inv, int64_t i, int e, float4 own,
-                                             int slot0) {
+// `rows`: the sample's entry of row 2g of the neighbour table (place 0 of each
+// node's members), `ye`: the state at this member.
+__device__ __forceinline__ bf8v gather_block(const float4 *__restrict__ ye, const unsigned *__restrict__ rows, int64_t Na,
+                                             float nodev, float4 inv, float4 own, int j, int slot0) {
   bf8v x;
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    const int slot = slot0 + h;
-    const int64_t j = idx_t[static_cast<int64_t>(slot) * Na + i];
-    const float4 f = *reinterpret_cast<const float4 *>(y + (j * E + e) * 4);
-    const float4 b = slot == 0 ? make_float4(0.f, 0.f, 0.f, 0.f) : own;
+    const float4 f = ye[rows[(8 * j + h) * Na]];
+    const float4 b = j == 0 && slot0 + h == 0 ? make_float4(0.f, 0.f, 0.f, 0.f) : own;
     float v0 = (f.x - b.x) * inv.x, v1 = (f.y - b.y) * inv.y, v2 = (f.z - b.z) * inv.z, v3 = (f.w - b.w) * inv.w;
-    if (slot == NSLOT_MAX) v0 = nodev;
+    if (j == 4 && slot0 + 32 + h == NSLOT_MAX) v0 = nodev;
     x[4 * h + 0] = static_cast<__bf16>(v0);
     x[4 * h + 1] = static_cast<__bf16>(v1);
     x[4 * h + 2] = static_cast<__bf16>(v2);
@@ -99,7 +99,7 @@ __device__ __forceinline__ bf8v gather_block(const float *__restrict__ y, const 
   return x;
 }
 
-// Y[s][0..3] for S samples (and bad[e] = stamp for members with a value that
+// Y[s][0..3] times out_scale for S samples (and bad[e] = stamp for members with a value that
 // is not finite, unless bad is NULL), T tiles of 16 samples per wavefront; blocks of
 // W wavefronts share one LDS copy of the weights and loop over contiguous
 // unit ranges (XCD-aware block order); OCC wavefronts per SIMD bound the
@@ -111,9 +111,9 @@ __device__ __forceinline__ bf8v gather_block(const float *__restrict__ y, const 
 template <int T, int MLP_WAVES, int MLP_OCC, int ACT>
 __global__ __launch_bounds__(64 * MLP_WAVES) __attribute__((amdgpu_waves_per_eu(MLP_OCC, MLP_OCC))) void
 mlp_forward_kernel(
-    const float *__restrict__ y, const int *__restrict__ idx_t, int64_t Na, int E,
+    const float *__restrict__ y, const unsigned *__restrict__ idx_t, int64_t Na, int E,
     const float *__restrict__ nodef, float4 inv, const __bf16 *__restrict__ frag_g, const float *__restrict__ params,
-    float *__restrict__ Y, int64_t S, int *__restrict__ bad, int stamp) {
+    float *__restrict__ Y, float4 out_scale, int64_t S, int *__restrict__ bad, int stamp) {
   extern __shared__ __attribute__((aligned(16))) unsigned char mlp_lds[];
   const bf8v *s_frag = reinterpret_cast<const bf8v *>(mlp_lds);
   float *s_bias = reinterpret_cast<float *>(mlp_lds + static_cast<size_t>(NFRAG) * 64 * 16);
@@ -139,16 +139,16 @@ mlp_forward_kernel(
     // keeps the weight fragments' LDS reads inside the loop: hoisted out of
     // it as loop-invariant they would need 304 registers
     asm volatile("" ::: "memory");
-    int64_t si[T];
-    int se[T];
+    unsigned si[T], se[T];
     float4 own[T];
     float nodev[T];
 #pragma unroll
     for (int tl = 0; tl < T; ++tl) {
-      const int64_t s = min(base + 16 * tl + r, S - 1);     // rows past S compute a copy, never stored
-      si[tl] = s / E;
-      se[tl] = static_cast<int>(s - si[tl] * E);
-      own[tl] = *reinterpret_cast<const float4 *>(y + s * 4);
+      // (S < 2^28: 32-bit division)
+      const unsigned s = static_cast<unsigned>(min(base + 16 * tl + r, S - 1));  // rows past S compute a copy, never stored
+      si[tl] = s / static_cast<unsigned>(E);
+      se[tl] = s - si[tl] * static_cast<unsigned>(E);
+      own[tl] = reinterpret_cast<const float4 *>(y)[s];
       nodev[tl] = nodef[si[tl]];
     }
     // output tile outermost: only one tile's accumulators are live, so the
@@ -159,7 +159,8 @@ mlp_forward_kernel(
     for (int j = 0; j < 5; ++j)
 #pragma unroll
       for (int tl = 0; tl < T; ++tl)
-        x[j][tl] = gather_block(y, idx_t, Na, E, nodev[tl], inv, si[tl], se[tl], own[tl], 8 * j + 2 * g);
+        x[j][tl] = gather_block(reinterpret_cast<const float4 *>(y) + se[tl], idx_t + 2 * g * Na + si[tl], Na, nodev[tl],
+                                inv, own[tl], j, 2 * g);
     bf8v hb[4][T];
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
@@ -213,7 +214,8 @@ mlp_forward_kernel(
       for (int tl = 0; tl < T; ++tl) {
         const int64_t s = base + 16 * tl + r;
         if (s < S) {
-          *reinterpret_cast<float4 *>(Y + s * 4) = make_float4(out[tl][0], out[tl][1], out[tl][2], out[tl][3]);
+          *reinterpret_cast<f4u *>(Y + s * 4) = f4v{out[tl][0] * out_scale.x, out[tl][1] * out_scale.y,
+                                                    out[tl][2] * out_scale.z, out[tl][3] * out_scale.w};
           if (bad && !(isfinite(out[tl][0]) && isfinite(out[tl][1]) && isfinite(out[tl][2]) && isfinite(out[tl][3])))
             bad[se[tl]] = stamp;  // (any such sample of the member writes the same)
         }
@@ -363,7 +365,7 @@ template <typename T> __device__ __forceinline__ T half_sum(T v) {
 
 template <int ACT>
 __global__ __launch_bounds__(64 * TR_WAVES) __attribute__((amdgpu_waves_per_eu(2, 2))) void train_kernel(
-    const float *__restrict__ y, const int *__restrict__ idx_t, int Na, int E, const float *__restrict__ nodef,
+    const float *__restrict__ y, const unsigned *__restrict__ idx_t, int Na, int E, const float *__restrict__ nodef,
     float4 inv, const __bf16 *__restrict__ w1, const __bf16 *__restrict__ w2, const __bf16 *__restrict__ w3,
     const float *__restrict__ params, const float *__restrict__ target, int S, float *__restrict__ part,
     double *__restrict__ part_loss) {
@@ -416,7 +418,7 @@ __global__ __launch_bounds__(64 * TR_WAVES) __attribute__((amdgpu_waves_per_eu(2
   // slot differences, 0 past the stencil). Samples past S repeat the last one;
   // their dY is 0.
   const int gs = tid >> 3, g8 = tid & 7;
-  int gj[5], gi = 0, ge = 0;
+  unsigned gj[5], gi = 0, ge = 0;
   auto gather_index = [&](int tile) {
     const unsigned s = min(tile * TR_S + gs, S - 1);
     gi = s / static_cast<unsigned>(E);
@@ -427,9 +429,10 @@ __global__ __launch_bounds__(64 * TR_WAVES) __attribute__((amdgpu_waves_per_eu(2
   float4 gf[5], gown;
   float gnode;
   auto gather_load = [&]() {
-    gown = *reinterpret_cast<const float4 *>(y + (static_cast<int64_t>(gi) * E + ge) * 4);
+    const float4 *ye = reinterpret_cast<const float4 *>(y) + ge;
+    gown = ye[gi * static_cast<unsigned>(E)];
 #pragma unroll
-    for (int j = 0; j < 5; ++j) gf[j] = *reinterpret_cast<const float4 *>(y + (static_cast<int64_t>(gj[j]) * E + ge) * 4);
+    for (int j = 0; j < 5; ++j) gf[j] = ye[gj[j]];
     gnode = nodef[gi];
   };
   unsigned xa_at = L0 + TR_XA + tr_at(gs, g8 >> 1) + 8 * (g8 & 1);      // group g8 + 8 j: chunk g8 / 2 + 4 j
@@ -554,7 +557,7 @@ __global__ __launch_bounds__(64 * TR_WAVES) __attribute__((amdgpu_waves_per_eu(2
     grad_w1(cur ^ 1);
     lds_barrier();
     const int s_own = tile * TR_S + srow;
-    const float4 t_own = *reinterpret_cast<const float4 *>(target + static_cast<int64_t>(min(s_own, S - 1)) * 4);
+    const f4v t_own = *reinterpret_cast<const f4u *>(target + static_cast<int64_t>(min(s_own, S - 1)) * 4);
     opaque();
     // layer 2
     {
@@ -579,11 +582,10 @@ __global__ __launch_bounds__(64 * TR_WAVES) __attribute__((amdgpu_waves_per_eu(2
                                                       lds_get<bf8v>((a_row ^ (32 * kk)) + TR_H2), acc, 0, 0, 0);
       bf8v dy = {};
       if (lh == 0 && s_own < S) {  // outputs 0-3: registers 0-3 of lanes 0-31
-        const float t[4] = {t_own.x, t_own.y, t_own.z, t_own.w};
         const f4v b3 = lds_get<f4v>(L0 + TR_B + 2 * HID * 4);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const float d = acc[i] + b3[i] - t[i];
+          const float d = acc[i] + b3[i] - t_own[i];
           const float g = 2.0f * d * scale;
           dy[i] = static_cast<__bf16>(g);
           if (hg == 0) {
@@ -750,24 +752,17 @@ __global__ void apply_kernel(float *__restrict__ y, const float *__restrict__ Y,
   *reinterpret_cast<float4 *>(y + s * 4) = o;
 }
 
-__global__ void scale_out_kernel(const float *__restrict__ Y, int ys, int64_t S, float4 sc, float *__restrict__ out) {
-  const int64_t s = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (s >= S) return;
-  out[s * 4 + 0] = Y[s * ys + 0] * sc.x;
-  out[s * 4 + 1] = Y[s * ys + 1] * sc.y;
-  out[s * 4 + 2] = Y[s * ys + 2] * sc.z;
-  out[s * 4 + 3] = Y[s * ys + 3] * sc.w;
-}
-
 // The gather's neighbours, one row per group of four input features: row k the
 // node of slot k (1 <= k < n), the node itself in every other row, so that a
-// slot past the stencil gives the difference 0.
+// slot past the stencil gives the difference 0; as the place of the node's
+// first member in the state (node E, below 2^32 for n_active E <= 2^28).
 constexpr int NGROUP = KIN / 4;
-__global__ void gather_rows_fill_kernel(const int *__restrict__ idx_t, int64_t Na, int n, int *__restrict__ out) {
+__global__ void gather_rows_fill_kernel(const int *__restrict__ idx_t, int64_t Na, int n, unsigned E,
+                                        unsigned *__restrict__ out) {
   const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (t >= Na * NGROUP) return;
   const int64_t k = t / Na;
-  out[t] = k >= 1 && k < n ? idx_t[t] : static_cast<int>(t - k * Na);
+  out[t] = E * static_cast<unsigned>(k >= 1 && k < n ? idx_t[t] : static_cast<int>(t - k * Na));
 }
 
 __global__ void f64_to_f32_kernel(const double *__restrict__ a, int64_t n, float *__restrict__ b) {
@@ -800,7 +795,7 @@ int gradient(rbffd_ctx *ctx, rbffd_closure *cl, const void *state, const float *
   rbffd_model *m = cl->model;
   const int nb = static_cast<int>(std::min<int64_t>(ctx->n_cu, (S + TR_S - 1) / TR_S));
   auto kern = cl->act == RBFFD_ACT_RELU ? train_kernel<RBFFD_ACT_RELU> : train_kernel<RBFFD_ACT_TANH>;
-  kern<<<nb, 64 * TR_WAVES, TR_LDS, s>>>(static_cast<const float *>(state), cl->idx.as<int>(), static_cast<int>(m->Na),
+  kern<<<nb, 64 * TR_WAVES, TR_LDS, s>>>(static_cast<const float *>(state), cl->idx.as<unsigned>(), static_cast<int>(m->Na),
                                          m->E, cl->nodef.as<float>(), cl->inv_in, cl->w1.as<__bf16>(),
                                          cl->w2.as<__bf16>(), cl->w3.as<__bf16>(), cl->params.as<float>(), T,
                                          static_cast<int>(S), cl->part.as<float>(), cl->part_loss.as<double>());
@@ -845,11 +840,12 @@ void set_mlp_lds(bool &ok) {
                                  hipFuncAttributeMaxDynamicSharedMemorySize, TR_LDS) == hipSuccess;
 }
 
-// Fused forward pass into cl->Yc [S][4] in launch shape S. Resident blocks per
+// Fused forward pass into Y [S][4], times sc, in launch shape SH. Resident blocks per
 // compute unit: as many as LDS (160 KB, 77 KB of packed weights each) and the
 // SIMDs' wavefront slots allow; the grid is one wave of them.
 template <int SH>
-void launch_forward(rbffd_ctx *ctx, rbffd_closure *cl, const void *state, int64_t S, int *bad, int stamp) {
+void launch_forward(rbffd_ctx *ctx, rbffd_closure *cl, const void *state, int64_t S, float *Y, float4 sc, int *bad,
+                    int stamp) {
   constexpr MlpShape sh = kMlpShapes[SH];
   rbffd_model *m = cl->model;
   constexpr int per_cu = std::min<int>(static_cast<int>((160 * 1024) / MLP_LDS), 4 * sh.occ / sh.waves);
@@ -858,18 +854,21 @@ void launch_forward(rbffd_ctx *ctx, rbffd_closure *cl, const void *state, int64_
   const unsigned nb = static_cast<unsigned>(
       std::max<int64_t>(1, std::min<int64_t>(static_cast<int64_t>(ctx->n_cu) * per_cu, (units + sh.waves - 1) / sh.waves)));
   auto kern = cl->act == RBFFD_ACT_RELU ? mlp_kernel<SH, RBFFD_ACT_RELU>() : mlp_kernel<SH, RBFFD_ACT_TANH>();
-  kern<<<nb, 64 * sh.waves, MLP_LDS, ctx->stream>>>(static_cast<const float *>(state), cl->idx.as<int>(), m->Na,
+  kern<<<nb, 64 * sh.waves, MLP_LDS, ctx->stream>>>(static_cast<const float *>(state), cl->idx.as<unsigned>(), m->Na,
                                                     m->E, cl->nodef.as<float>(), cl->inv_in, cl->frag.as<__bf16>(),
-                                                    cl->params.as<float>(), cl->Yc.as<float>(), S, bad, stamp);
+                                                    cl->params.as<float>(), Y, sc, S, bad, stamp);
 }
 
-int forward_fused(rbffd_ctx *ctx, rbffd_closure *cl, const void *state, int64_t S, int *bad = nullptr, int stamp = 0) {
+const float4 kOne = make_float4(1.0f, 1.0f, 1.0f, 1.0f);
+
+int forward_fused(rbffd_ctx *ctx, rbffd_closure *cl, const void *state, int64_t S, float *Y, float4 sc,
+                  int *bad = nullptr, int stamp = 0) {
   switch (cl->shape) {
-    case 1: launch_forward<1>(ctx, cl, state, S, bad, stamp); break;
-    case 2: launch_forward<2>(ctx, cl, state, S, bad, stamp); break;
-    case 3: launch_forward<3>(ctx, cl, state, S, bad, stamp); break;
-    case 4: launch_forward<4>(ctx, cl, state, S, bad, stamp); break;
-    default: launch_forward<0>(ctx, cl, state, S, bad, stamp); break;
+    case 1: launch_forward<1>(ctx, cl, state, S, Y, sc, bad, stamp); break;
+    case 2: launch_forward<2>(ctx, cl, state, S, Y, sc, bad, stamp); break;
+    case 3: launch_forward<3>(ctx, cl, state, S, Y, sc, bad, stamp); break;
+    case 4: launch_forward<4>(ctx, cl, state, S, Y, sc, bad, stamp); break;
+    default: launch_forward<0>(ctx, cl, state, S, Y, sc, bad, stamp); break;
   }
   RBFFD_HIP(ctx, hipGetLastError());
   return RBFFD_OK;
@@ -925,7 +924,8 @@ int closure_create(rbffd_ctx *ctx, rbffd_model *m, const rbffd_closure_desc *d, 
     return rbffd_fail(ctx, RBFFD_EDEVICE, "closure set-up copies");
   }
   f64_to_f32_kernel<<<grid_for(m->Na, 256), 256, 0, s>>>(d->node_feature, m->Na, cl->nodef.as<float>());
-  gather_rows_fill_kernel<<<grid_for(m->Na * NGROUP, 256), 256, 0, s>>>(m->idx_t.as<int>(), m->Na, m->n, cl->idx.as<int>());
+  gather_rows_fill_kernel<<<grid_for(m->Na * NGROUP, 256), 256, 0, s>>>(m->idx_t.as<int>(), m->Na, m->n,
+                                                                      static_cast<unsigned>(m->E), cl->idx.as<unsigned>());
   repack(cl, s);
   const hipError_t e_launch = hipGetLastError();
   const hipError_t e_sync = hipStreamSynchronize(s);
@@ -947,11 +947,7 @@ float *closure_params(rbffd_closure *cl) { return cl->params.as<float>(); }
 
 int closure_forward(rbffd_ctx *ctx, rbffd_closure *cl, const void *state, float *out) {
   const int64_t S = cl->model->Na * cl->model->E;
-  int rc = forward_fused(ctx, cl, state, S);
-  if (rc) return rc;
-  scale_out_kernel<<<grid_for(S, 256), 256, 0, ctx->stream>>>(cl->Yc.as<float>(), 4, S, cl->out_sc, out);
-  RBFFD_HIP(ctx, hipGetLastError());
-  return RBFFD_OK;
+  return forward_fused(ctx, cl, state, S, out, cl->out_sc);
 }
 
 // Time every launch shape of the fused forward kernel on `state` (one
@@ -970,10 +966,10 @@ int closure_tune(rbffd_ctx *ctx, rbffd_closure *cl, const void *state, int *chos
   int rc = RBFFD_OK;
   for (int sh = first; sh <= last && rc == RBFFD_OK; ++sh) {
     cl->shape = sh;
-    rc = forward_fused(ctx, cl, state, S);
+    rc = forward_fused(ctx, cl, state, S, cl->Yc.as<float>(), kOne);
     if (rc) break;
     if (hipEventRecord(e0, ctx->stream) != hipSuccess) rc = RBFFD_EDEVICE;
-    for (int r = 0; r < 3 && rc == RBFFD_OK; ++r) rc = forward_fused(ctx, cl, state, S);
+    for (int r = 0; r < 3 && rc == RBFFD_OK; ++r) rc = forward_fused(ctx, cl, state, S, cl->Yc.as<float>(), kOne);
     float ms = 0.0f;
     if (rc == RBFFD_OK && (hipEventRecord(e1, ctx->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
                            hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
@@ -1029,7 +1025,7 @@ int closure_step(rbffd_ctx *ctx, rbffd_closure *cl, void *state, double *t, doub
   for (int64_t k = 0; k < n_steps; ++k) {
     const int stamp = static_cast<int>(k % INT32_MAX) + 1;
     int rc = model_ghost(ctx, m, state);
-    if (!rc) rc = forward_fused(ctx, cl, state, S, cl->bad.as<int>(), stamp);  // correction of the state before the step
+    if (!rc) rc = forward_fused(ctx, cl, state, S, cl->Yc.as<float>(), kOne, cl->bad.as<int>(), stamp);  // correction of the state before the step
     if (!rc) rc = model_step(ctx, m, state, t, dt, 1, tableau, true);
     if (rc) return rc;
     apply_kernel<<<grid_for(S, 256), 256, 0, s>>>(static_cast<float *>(state), cl->Yc.as<float>(), m->Na, m->E,

@@ -173,15 +173,16 @@ class ScratchLease {
 // the weights' count array.
 constexpr int KNN_BOX_BLOCKS = 512;
 constexpr int KNN_SCAN_TILE = 4096;
+constexpr size_t KNN_HEAD_BYTES = 256;
 constexpr int WEIGHTS_COUNTS = 40;
 constexpr size_t round256(size_t b) { return (b + 255) & ~size_t(255); }
 constexpr size_t knn_scratch_bytes(int64_t n_nodes, int64_t n_centers) {
-  // box partials, box + overflow count, cell counts, cell starts, scan tile
+  // box partials, box, grid and findings, cell counts, cell starts, scan tile
   // sums, nodes by cell, centres left to the dense-cluster kernel
   const size_t n = static_cast<size_t>(n_nodes), cells = n + 16;
   const size_t tiles = (cells + KNN_SCAN_TILE - 1) / KNN_SCAN_TILE;
   const size_t nc = static_cast<size_t>(n_centers > 1 ? n_centers : 1);
-  return round256(sizeof(double) * 4 * KNN_BOX_BLOCKS) + round256(sizeof(double) * 8) +
+  return round256(sizeof(double) * 4 * KNN_BOX_BLOCKS) + round256(KNN_HEAD_BYTES) +
          round256(sizeof(int) * cells) + round256(sizeof(int) * (cells + 1)) + round256(sizeof(int) * tiles) +
          round256(sizeof(int) * n) + round256(sizeof(int) * nc);
 }
@@ -199,13 +200,16 @@ constexpr size_t weights_scratch_bytes(int64_t n_centers) {
 // Every per-stencil parameter and index of a search (`weights` false) or a
 // weights call is checked before anything is written: centre indices, n, and
 // for weights m, l, n >= M(l), n + M <= 128, Laplacian^k continuity and the
-// given stencils' indices. Synchronises; RBFFD_EINVAL names the first bad
-// stencil.
-int check_stencils_device(rbffd_ctx *ctx, const rbffd_stencils *st, const rbffd_op *ops, int n_ops, bool weights,
-                          Workspace &ws);
+// given stencils' indices. check_launch runs the checks into flag[2] (device;
+// the search reads it, writes nothing when it is set, and reports it with its
+// own findings); check_result turns a copy of it into RBFFD_EINVAL, naming the
+// first bad stencil.
+int check_launch(rbffd_ctx *ctx, const rbffd_stencils *st, const rbffd_op *ops, int n_ops, bool weights, Workspace &ws,
+                 int **flag);
+int check_result(rbffd_ctx *ctx, const rbffd_stencils *st, const int (&flag)[2]);
 
 // ---- stencil search (knn.hip) ----
-int knn_run(rbffd_ctx *ctx, const rbffd_stencils *st, int32_t *idx, Workspace &ws);
+int knn_run(rbffd_ctx *ctx, const rbffd_stencils *st, int32_t *idx, Workspace &ws, const int *flag);
 
 // ---- weights (weights.hip) ----
 // `shapes`: launch shape per size bucket (NULL: the context's tuned ones);

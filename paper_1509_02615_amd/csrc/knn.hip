@@ -32,6 +32,17 @@ struct Grid {
   int ncx, ncz;
 };
 
+// What the launches of one search share in device memory, read back once at
+// its end. `go`: the arguments and the box are good; without it no launch
+// after the box touches anything.
+enum : int { BOX_OK = 0, BOX_NONFINITE = 1, BOX_PERIOD = 2 };
+struct Head {
+  Grid g;
+  double extent;  // of x
+  int go, box, flag[2], n_over;
+};
+static_assert(sizeof(Head) <= KNN_HEAD_BYTES, "scratch size formula");
+
 __device__ __forceinline__ int cell_x(const Grid &g, double x) {
   int ix = static_cast<int>(floor((x - g.x0) / g.sx));
   if (g.period > 0.0) {  // nodes lie within one period of x0
@@ -99,8 +110,33 @@ __global__ __launch_bounds__(BOX_THREADS) void bbox_partial_kernel(const double 
   if (threadIdx.x < 4) part[4 * blockIdx.x + threadIdx.x] = (nan && threadIdx.x == 0) ? NAN : s[threadIdx.x][0];
 }
 
-__global__ __launch_bounds__(BOX_BLOCKS) void bbox_final_kernel(const double *__restrict__ part, int nb,
-                                                                double *__restrict__ out) {
+// grid of cells about one mean spacing wide over the box, at most n + 16 cells
+__device__ Grid make_grid(const double (&box)[4], double period, int n) {
+  Grid g{};
+  g.period = period;
+  const double lx = period > 0.0 ? period : box[1] - box[0];
+  const double lz = box[3] - box[2];
+  double ext = fmax(lx, lz);
+  if (!(ext > 0.0)) ext = 1.0;
+  const double area = fmax(lx, 1e-12 * ext) * fmax(lz, 1e-12 * ext);
+  const double sc = sqrt(area / n);
+  g.x0 = box[0];
+  g.z0 = box[2];
+  g.ncx = lx > 0.0 ? static_cast<int>(fmin(fmax(floor(lx / sc), 1.0), 1 << 20)) : 1;
+  g.ncz = lz > 0.0 ? static_cast<int>(fmin(fmax(floor(lz / sc), 1.0), 1 << 20)) : 1;
+  while (static_cast<int64_t>(g.ncx) * g.ncz > static_cast<int64_t>(n) + 16) {
+    g.ncx = max(1, g.ncx / 2);
+    g.ncz = max(1, g.ncz / 2);
+  }
+  g.sx = lx > 0.0 ? lx / g.ncx : 1.0;
+  g.sz = lz > 0.0 ? lz / g.ncz : 1.0;
+  return g;
+}
+
+// The whole box, the grid on it and the findings so far.
+__global__ __launch_bounds__(BOX_BLOCKS) void bbox_final_kernel(const double *__restrict__ part, int nb, double period,
+                                                                int n, const int *__restrict__ flag,
+                                                                Head *__restrict__ head) {
   __shared__ double s[4][BOX_BLOCKS];
   const int t = threadIdx.x;
   const bool nan = __syncthreads_or(t < nb && isnan(part[4 * t]));
@@ -118,19 +154,35 @@ __global__ __launch_bounds__(BOX_BLOCKS) void bbox_final_kernel(const double *__
     }
     __syncthreads();
   }
-  if (t < 4) out[t] = (nan && t == 0) ? NAN : s[t][0];
+  if (t == 0) {
+    const double box[4] = {s[0][0], s[1][0], s[2][0], s[3][0]};
+    Head h{};
+    h.extent = box[1] - box[0];
+    h.flag[0] = flag[0];
+    h.flag[1] = flag[1];
+    if (nan || !(isfinite(box[0]) && isfinite(box[1]) && isfinite(box[2]) && isfinite(box[3])))
+      h.box = BOX_NONFINITE;
+    else if (period > 0.0 && h.extent >= period)
+      h.box = BOX_PERIOD;
+    else
+      h.g = make_grid(box, period, n);
+    h.go = h.box == BOX_OK && h.flag[0] == 0 ? 1 : 0;
+    *head = h;
+  }
 }
 
-__global__ void count_kernel(const double *__restrict__ xy, int n, Grid g, int *__restrict__ count) {
+__global__ void count_kernel(const double *__restrict__ xy, int n, const Head *__restrict__ head, int *__restrict__ count) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+  if (i >= n || !head->go) return;
+  const Grid g = head->g;
   int c = cell_z(g, xy[2 * i + 1]) * g.ncx + cell_x(g, xy[2 * i]);
   atomicAdd(&count[c], 1);
 }
 
 // Exclusive scan of count[0..n) into start[0..n] in three launches: each
 // 1024-thread block sums SCAN_ITEMS consecutive counts per thread, one block
-// scans the block sums, and each block then writes its own range's starts.
+// scans the block sums, and each block then writes its own range's starts. n is
+// the grid's cell count; the launches cover the largest it can be.
 constexpr int SCAN_THREADS = 1024, SCAN_ITEMS = 4, SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
 static_assert(SCAN_TILE == KNN_SCAN_TILE, "scratch size formula");
 
@@ -150,9 +202,13 @@ __device__ __forceinline__ int block_excl_scan(int v, int *s, int &total) {
   return r;
 }
 
-__global__ __launch_bounds__(SCAN_THREADS) void scan_tile_sum_kernel(const int *__restrict__ count, int n,
+__device__ __forceinline__ int cell_count(const Head *head) { return head->go ? head->g.ncx * head->g.ncz : 0; }
+
+__global__ __launch_bounds__(SCAN_THREADS) void scan_tile_sum_kernel(const int *__restrict__ count,
+                                                                     const Head *__restrict__ head,
                                                                      int *__restrict__ tile_sum) {
   __shared__ int s[SCAN_THREADS];
+  const int n = cell_count(head);
   const int base = blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
   int v = 0;
 #pragma unroll
@@ -165,8 +221,10 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_tile_sum_kernel(const int *
 // Exclusive scan of the nt tile sums in place (each thread a contiguous
 // chunk of them), and the grand total into start[n].
 __global__ __launch_bounds__(SCAN_THREADS) void scan_tiles_kernel(int *__restrict__ tile_sum, int nt,
-                                                                  int *__restrict__ start, int n) {
+                                                                  int *__restrict__ start,
+                                                                  const Head *__restrict__ head) {
   __shared__ int s[SCAN_THREADS];
+  const int n = cell_count(head);
   const int chunk = (nt + SCAN_THREADS - 1) / SCAN_THREADS;
   const int b = threadIdx.x * chunk, e = min(nt, b + chunk);
   int v = 0;
@@ -181,10 +239,12 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_tiles_kernel(int *__restric
   if (threadIdx.x == 0) start[n] = total;
 }
 
-__global__ __launch_bounds__(SCAN_THREADS) void scan_write_kernel(const int *__restrict__ count, int n,
+__global__ __launch_bounds__(SCAN_THREADS) void scan_write_kernel(const int *__restrict__ count,
+                                                                  const Head *__restrict__ head,
                                                                   const int *__restrict__ tile_off,
                                                                   int *__restrict__ start) {
   __shared__ int s[SCAN_THREADS];
+  const int n = cell_count(head);
   const int base = blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
   int c[SCAN_ITEMS], v = 0;
 #pragma unroll
@@ -204,10 +264,11 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_write_kernel(const int *__r
 // Node i goes to its cell's range of `nodes`; count[c] (the cell's size)
 // is consumed as the cursor, so the order within a cell is arbitrary (the
 // query orders candidates by their keys).
-__global__ void scatter_kernel(const double *__restrict__ xy, int n, Grid g, const int *__restrict__ start,
-                               int *__restrict__ count, int *__restrict__ nodes) {
+__global__ void scatter_kernel(const double *__restrict__ xy, int n, const Head *__restrict__ head,
+                               const int *__restrict__ start, int *__restrict__ count, int *__restrict__ nodes) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+  if (i >= n || !head->go) return;
+  const Grid g = head->g;
   int c = cell_z(g, xy[2 * i + 1]) * g.ncx + cell_x(g, xy[2 * i]);
   nodes[start[c] + atomicSub(&count[c], 1) - 1] = i;
 }
@@ -327,9 +388,9 @@ __device__ __forceinline__ void knn_wave_sync() {
 }
 
 __global__ __launch_bounds__(64 * KNN_WAVES) void query_kernel(
-    const double *__restrict__ xy, Grid g, const int *__restrict__ start, const int *__restrict__ cell_nodes,
-    const int *__restrict__ centers, int n_centers, const int *__restrict__ n_per, int n_max, int r_uniform,
-    int *__restrict__ idx, int *__restrict__ over, int *__restrict__ n_over) {
+    const double *__restrict__ xy, Head *__restrict__ head, const int *__restrict__ start,
+    const int *__restrict__ cell_nodes, const int *__restrict__ centers, int n_centers, const int *__restrict__ n_per,
+    int n_max, int r_uniform, int *__restrict__ idx, int *__restrict__ over) {
   __shared__ __attribute__((aligned(16))) KnnShared s_all[KNN_WAVES];
   static_assert(sizeof(KnnShared) % 16 == 0 && KNN_ROWS * 16 <= sizeof(double) * KNN_KEYS, "aligned views of LDS");
   // block ids go round-robin over the 8 XCDs: each XCD takes a contiguous
@@ -339,7 +400,8 @@ __global__ __launch_bounds__(64 * KNN_WAVES) void query_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   const int lane = threadIdx.x & 63;
   const int q = lb * KNN_WAVES + wave;
-  if (q >= n_centers) return;
+  if (q >= n_centers || !head->go) return;
+  const Grid g = head->g;
   KnnShared &S = s_all[wave];
   int4 *rows = reinterpret_cast<int4 *>(S.d);
   int *group = reinterpret_cast<int *>(S.d);
@@ -359,7 +421,7 @@ __global__ __launch_bounds__(64 * KNN_WAVES) void query_kernel(
     const int incl = scan32(len);
     const int total = __builtin_amdgcn_readlane(incl, KNN_ROWS - 1);
     if (b.nzc > KNN_ROWS || total > KNN_KEYS) {
-      if (lane == 0) over[atomicAdd(n_over, 1)] = q;
+      if (lane == 0) over[atomicAdd(&head->n_over, 1)] = q;
       return;
     }
     // candidate k = lane + 64 u, in row order: its row is the number of rows
@@ -645,79 +707,54 @@ __global__ __launch_bounds__(KNN_BLOCK) void query_wide_kernel(
   }
 }
 
-// grid of cells about one mean spacing wide over the box, at most n + 16 cells
-Grid make_grid(const double box[4], double period, int n) {
-  Grid g{};
-  g.period = period;
-  const double lx = period > 0.0 ? period : box[1] - box[0];
-  const double lz = box[3] - box[2];
-  double ext = fmax(lx, lz);
-  if (!(ext > 0.0)) ext = 1.0;
-  const double area = fmax(lx, 1e-12 * ext) * fmax(lz, 1e-12 * ext);
-  const double sc = sqrt(area / n);
-  g.x0 = box[0];
-  g.z0 = box[2];
-  g.ncx = lx > 0.0 ? static_cast<int>(fmin(fmax(floor(lx / sc), 1.0), 1 << 20)) : 1;
-  g.ncz = lz > 0.0 ? static_cast<int>(fmin(fmax(floor(lz / sc), 1.0), 1 << 20)) : 1;
-  while (static_cast<int64_t>(g.ncx) * g.ncz > static_cast<int64_t>(n) + 16) {
-    g.ncx = max(1, g.ncx / 2);
-    g.ncz = max(1, g.ncz / 2);
-  }
-  g.sx = lx > 0.0 ? lx / g.ncx : 1.0;
-  g.sz = lz > 0.0 ? lz / g.ncz : 1.0;
-  return g;
-}
-
 }  // namespace
 
 
-int knn_run(rbffd_ctx *ctx, const rbffd_stencils *st, int32_t *idx, Workspace &ws) {
+// The search, in one stream of launches: the box, the grid and the findings
+// stay on the device, so the only wait is for the last launch.
+int knn_run(rbffd_ctx *ctx, const rbffd_stencils *st, int32_t *idx, Workspace &ws, const int *flag) {
   const int n = static_cast<int>(st->n_nodes);
   const int nc = static_cast<int>(st->n_centers);
   hipStream_t s = ctx->stream;
-  double *d_part, *d_small;  // box partials; box[4] then two ints (overflow count, spare)
-  RBFFD_WS(ctx, ws, ws.get(4 * BOX_BLOCKS, &d_part));
-  RBFFD_WS(ctx, ws, ws.get(8, &d_small));
-  int *d_nover = reinterpret_cast<int *>(d_small + 4);
-  const int nb = std::min(BOX_BLOCKS, static_cast<int>(grid_for(n, BOX_THREADS)));
-  bbox_partial_kernel<<<nb, BOX_THREADS, 0, s>>>(st->xy, n, d_part);
-  bbox_final_kernel<<<1, BOX_BLOCKS, 0, s>>>(d_part, nb, d_small);
-  RBFFD_HIP(ctx, hipGetLastError());
-  double box[4];
-  RBFFD_HIP(ctx, hipMemcpyAsync(box, d_small, sizeof(box), hipMemcpyDeviceToHost, s));
-  RBFFD_HIP(ctx, hipStreamSynchronize(s));
-  if (!(std::isfinite(box[0]) && std::isfinite(box[1]) && std::isfinite(box[2]) && std::isfinite(box[3])))
-    return rbffd_fail(ctx, RBFFD_EINVAL, "non-finite node coordinates");
-  if (st->period_x > 0.0 && box[1] - box[0] >= st->period_x)
-    return rbffd_fail(ctx, RBFFD_EINVAL, "x extent %g not inside one period %g", box[1] - box[0], st->period_x);
-  const Grid g = make_grid(box, st->period_x, n);
-  const int ncell = g.ncx * g.ncz;
-  const int tiles = static_cast<int>(grid_for(ncell, SCAN_TILE));
+  const int max_cells = n + 16;
+  const int tiles = static_cast<int>(grid_for(max_cells, SCAN_TILE));
+  double *d_part;
+  void *d_head;
   int *d_count, *d_start, *d_tiles, *d_nodes, *d_over;
-  RBFFD_WS(ctx, ws, ws.get(ncell, &d_count));
-  RBFFD_WS(ctx, ws, ws.get(ncell + 1, &d_start));
+  RBFFD_WS(ctx, ws, ws.get(4 * BOX_BLOCKS, &d_part));
+  RBFFD_WS(ctx, ws, ws.get(KNN_HEAD_BYTES, &d_head));
+  RBFFD_WS(ctx, ws, ws.get(max_cells, &d_count));
+  RBFFD_WS(ctx, ws, ws.get(max_cells + 1, &d_start));
   RBFFD_WS(ctx, ws, ws.get(tiles, &d_tiles));
   RBFFD_WS(ctx, ws, ws.get(n, &d_nodes));
   RBFFD_WS(ctx, ws, ws.get(std::max(nc, 1), &d_over));
-  RBFFD_HIP(ctx, hipMemsetAsync(d_count, 0, sizeof(int) * ncell, s));
-  RBFFD_HIP(ctx, hipMemsetAsync(d_nover, 0, sizeof(int), s));
-  count_kernel<<<grid_for(n, 256), 256, 0, s>>>(st->xy, n, g, d_count);
-  scan_tile_sum_kernel<<<tiles, SCAN_THREADS, 0, s>>>(d_count, ncell, d_tiles);
-  scan_tiles_kernel<<<1, SCAN_THREADS, 0, s>>>(d_tiles, tiles, d_start, ncell);
-  scan_write_kernel<<<tiles, SCAN_THREADS, 0, s>>>(d_count, ncell, d_tiles, d_start);
-  scatter_kernel<<<grid_for(n, 256), 256, 0, s>>>(st->xy, n, g, d_start, d_count, d_nodes);
-  query_kernel<<<grid_for(nc, KNN_WAVES), 64 * KNN_WAVES, 0, s>>>(st->xy, g, d_start, d_nodes, st->centers, nc,
+  Head *head = static_cast<Head *>(d_head);
+  const int nb = std::min(BOX_BLOCKS, static_cast<int>(grid_for(n, BOX_THREADS)));
+  bbox_partial_kernel<<<nb, BOX_THREADS, 0, s>>>(st->xy, n, d_part);
+  bbox_final_kernel<<<1, BOX_BLOCKS, 0, s>>>(d_part, nb, st->period_x, n, flag, head);
+  RBFFD_HIP(ctx, hipMemsetAsync(d_count, 0, sizeof(int) * max_cells, s));
+  count_kernel<<<grid_for(n, 256), 256, 0, s>>>(st->xy, n, head, d_count);
+  scan_tile_sum_kernel<<<tiles, SCAN_THREADS, 0, s>>>(d_count, head, d_tiles);
+  scan_tiles_kernel<<<1, SCAN_THREADS, 0, s>>>(d_tiles, tiles, d_start, head);
+  scan_write_kernel<<<tiles, SCAN_THREADS, 0, s>>>(d_count, head, d_tiles, d_start);
+  scatter_kernel<<<grid_for(n, 256), 256, 0, s>>>(st->xy, n, head, d_start, d_count, d_nodes);
+  query_kernel<<<grid_for(nc, KNN_WAVES), 64 * KNN_WAVES, 0, s>>>(st->xy, head, d_start, d_nodes, st->centers, nc,
                                                                   st->n_per, st->n_max, first_radius(st->n_max), idx,
-                                                                  d_over, d_nover);
+                                                                  d_over);
   RBFFD_HIP(ctx, hipGetLastError());
-  int n_over = 0;
-  RBFFD_HIP(ctx, hipMemcpyAsync(&n_over, d_nover, sizeof(int), hipMemcpyDeviceToHost, s));
+  Head h;
+  RBFFD_HIP(ctx, hipMemcpyAsync(&h, head, sizeof(h), hipMemcpyDeviceToHost, s));
   RBFFD_HIP(ctx, hipStreamSynchronize(s));
-  if (n_over > 0) {
-    query_list_kernel<<<n_over, KNN_BLOCK, 0, s>>>(st->xy, n, g, d_start, d_nodes, st->centers, nc, st->n_per, st->n_max,
-                                                   idx, d_over);
-    query_wide_kernel<<<n_over, KNN_BLOCK, 0, s>>>(st->xy, g, d_start, d_nodes, st->centers, st->n_per, st->n_max,
-                                                   d_over, idx);
+  const int rc = check_result(ctx, st, h.flag);
+  if (rc) return rc;
+  if (h.box == BOX_NONFINITE) return rbffd_fail(ctx, RBFFD_EINVAL, "non-finite node coordinates");
+  if (h.box == BOX_PERIOD)
+    return rbffd_fail(ctx, RBFFD_EINVAL, "x extent %g not inside one period %g", h.extent, st->period_x);
+  if (h.n_over > 0) {
+    query_list_kernel<<<h.n_over, KNN_BLOCK, 0, s>>>(st->xy, n, h.g, d_start, d_nodes, st->centers, nc, st->n_per,
+                                                     st->n_max, idx, d_over);
+    query_wide_kernel<<<h.n_over, KNN_BLOCK, 0, s>>>(st->xy, h.g, d_start, d_nodes, st->centers, st->n_per, st->n_max,
+                                                     d_over, idx);
     RBFFD_HIP(ctx, hipGetLastError());
     RBFFD_HIP(ctx, hipStreamSynchronize(s));  // results are complete on return, as after query_kernel
   }

@@ -1194,7 +1194,9 @@ int capture_steps(rbffd_ctx *ctx, rbffd_model *m, void *state, double dt, int ta
   hipGraph_t graph = nullptr;
   hipError_t ec = eb;
   if (eb == hipSuccess) {
-    rc = enqueue_steps(ctx, m, state, dt, tableau, k, closed);
+    // (the step from closed ghosts leaves the counter to model_step: it is
+    // mostly the only step of a call)
+    rc = closed ? enqueue_step(ctx, m, state, dt, tableau, 0, true) : enqueue_steps(ctx, m, state, dt, tableau, k, false);
     ec = hipStreamEndCapture(cs, &graph);
   }
   ctx->stream = saved;
@@ -1246,7 +1248,7 @@ int model_step(rbffd_ctx *ctx, rbffd_model *m, void *state, double *t, double dt
     int64_t k = 0;
     if (closed) {
       RBFFD_HIP(ctx, hipGraphLaunch(m->exec_c, s));
-      ++k;
+      if (++k < n_steps) tick_kernel<<<1, 1, 0, s>>>(m->dev_misc.as<DevMisc>(), 1);
     }
     for (; k + GRAPH_STEPS <= n_steps; k += GRAPH_STEPS) RBFFD_HIP(ctx, hipGraphLaunch(m->exec_n, s));
     for (; k < n_steps; ++k) RBFFD_HIP(ctx, hipGraphLaunch(m->exec, s));

@@ -80,9 +80,9 @@ struct WArgs {
   int max_iter;
   const int *list;    // the launch's queue of stencils, list[base .. base + count)
                       // (NULL: the stencils base .. base + count - 1 themselves)
-  const int2 *qinfo;  // device {base, count} of the queue (NULL: {0, n_centers}); a
-                      // negative base: the queue fills `list` from its end, so its
-                      // entries are list[n_centers - count .. n_centers)
+  const int2 *qinfo;  // device {base, count} of the queue (NULL: {0, n_centers})
+  int from_end;       // the queue fills `list` from its end: its entries are
+                      // list[n_centers - count .. n_centers)
   int *defer;         // two systems per wavefront: stencils left to the one-system kernel
   int *n_defer;       // their count (the deferred queue's count, device)
 };
@@ -100,12 +100,12 @@ __device__ __forceinline__ QueueView queue_view(const WArgs &a) {
   if (a.qinfo) {
     const int2 qi = *a.qinfo;
     v.count = qi.y;
-    v.base = qi.x >= 0 ? qi.x : a.n_centers - qi.y;
+    v.base = a.from_end ? a.n_centers - qi.y : qi.x;
   }
   return v;
 }
 
-__device__ __forceinline__ int n_terms(int l) { return (l + 1) * (l + 2) / 2; }
+__host__ __device__ __forceinline__ int n_terms(int l) { return (l + 1) * (l + 2) / 2; }
 
 // Graded monomial order: q -> (a, b) of x^a z^b, degree d = a + b.
 __device__ __forceinline__ void mono(int q, int &a, int &b) {
@@ -1571,7 +1571,7 @@ constexpr int NBUCKET = 6;
 __host__ __device__ constexpr int bucket_cap(int b) {
   return b == 0 ? 32 : b == 1 ? 48 : b == 2 ? 64 : b == 3 ? 80 : b == 4 ? 96 : 128;
 }
-__device__ __forceinline__ int bucket_of(int K) {
+__host__ __device__ __forceinline__ int bucket_of(int K) {
   int b = 0;
   while (b < NBUCKET - 1 && K > bucket_cap(b)) ++b;
   return b;
@@ -1792,17 +1792,28 @@ int weights_run(rbffd_ctx *ctx, const rbffd_stencils *st, const rbffd_op *ops, i
   const int nc = static_cast<int>(st->n_centers);
   const int n_cu = ctx->n_cu;
   if (!shapes) shapes = ctx->wshape;
+  // One size for all stencils (the checks have passed it): one bucket, whose
+  // queue is the stencils themselves, and no counting, waiting for the counts
+  // and filling (60 us of a 2,176-stencil call's 390). Systems of up to 32
+  // unknowns of several orders stay out: their pairs need the filling's order.
+  const bool uniform = !st->n_per && !st->l_per && (!st->m_per || st->n_max + n_terms(st->l_uniform) > bucket_cap(0));
   int *d_cnt, *d_list;
   RBFFD_WS(ctx, ws, ws.get(C_ALL, &d_cnt));
   RBFFD_WS(ctx, ws, ws.get(std::max(nc, 1), &d_list));
   RBFFD_HIP(ctx, hipMemsetAsync(d_cnt, 0, C_ALL * sizeof(int), s));
-  // stencils bucketed by K (and the invalid ones counted)
-  bucket_count_kernel<<<grid_for(nc, BK_BLOCK), BK_BLOCK, 0, s>>>(st->n_per, st->n_max, st->l_per, st->l_uniform,
-                                                                  nc, d_cnt, d_cnt + C_KMAX);
-  RBFFD_HIP(ctx, hipGetLastError());
-  int cnt[C_ALL];  // counts (and the invalid count), largest K per bucket, cursors, queues
-  RBFFD_HIP(ctx, hipMemcpyAsync(cnt, d_cnt, C_CURSOR * sizeof(int), hipMemcpyDeviceToHost, s));
-  RBFFD_HIP(ctx, hipStreamSynchronize(s));
+  int cnt[C_ALL] = {};  // counts (and the invalid count), largest K per bucket, cursors, queues
+  if (uniform) {
+    const int K = st->n_max + n_terms(st->l_uniform), b = bucket_of(K);
+    cnt[b] = nc;
+    cnt[C_KMAX + b] = K;
+  } else {
+    // stencils bucketed by K (and the invalid ones counted)
+    bucket_count_kernel<<<grid_for(nc, BK_BLOCK), BK_BLOCK, 0, s>>>(st->n_per, st->n_max, st->l_per, st->l_uniform,
+                                                                    nc, d_cnt, d_cnt + C_KMAX);
+    RBFFD_HIP(ctx, hipGetLastError());
+    RBFFD_HIP(ctx, hipMemcpyAsync(cnt, d_cnt, C_CURSOR * sizeof(int), hipMemcpyDeviceToHost, s));
+    RBFFD_HIP(ctx, hipStreamSynchronize(s));
+  }
   // n and l were checked before anything was written; this is a safeguard
   if (cnt[NBUCKET] > 0) return rbffd_fail(ctx, RBFFD_EINVAL, "%d stencils with invalid n or l", cnt[NBUCKET]);
   int kc = 0, n_small = 0, n_large = 0;
@@ -1814,24 +1825,26 @@ int weights_run(rbffd_ctx *ctx, const rbffd_stencils *st, const rbffd_op *ops, i
 
   int32_t *st_out = status;
   if (!st_out) RBFFD_WS(ctx, ws, ws.get(nc, &st_out));
-  // queues: bucket b at its prefix offset in the list (its fill cursor starts
-  // there), the deferred and stalled queues empty
-  for (int b = 0, off = 0; b < NBUCKET; ++b) {
-    cnt[C_CURSOR + b] = off;
-    cnt[C_Q + 2 * b] = off;
-    cnt[C_Q + 2 * b + 1] = cnt[b];
-    off += cnt[b];
+  if (!uniform) {
+    // queues: bucket b at its prefix offset in the list (its fill cursor starts
+    // there), the deferred and stalled queues empty
+    for (int b = 0, off = 0; b < NBUCKET; ++b) {
+      cnt[C_CURSOR + b] = off;
+      cnt[C_Q + 2 * b] = off;
+      cnt[C_Q + 2 * b + 1] = cnt[b];
+      off += cnt[b];
+    }
+    for (int q = NBUCKET; q < NQUEUE; ++q) {
+      cnt[C_Q + 2 * q] = 0;
+      cnt[C_Q + 2 * q + 1] = 0;
+    }
+    RBFFD_HIP(ctx, hipMemcpyAsync(d_cnt + C_CURSOR, cnt + C_CURSOR, (C_STATUS - C_CURSOR) * sizeof(int),
+                                  hipMemcpyHostToDevice, s));
+    bucket_fill_kernel<<<grid_for(nc, BK_BLOCK), BK_BLOCK, 0, s>>>(st->n_per, st->n_max, st->m_per, st->m_uniform,
+                                                                   st->l_per, st->l_uniform, nc, d_cnt + C_CURSOR,
+                                                                   d_list);
+    RBFFD_HIP(ctx, hipGetLastError());
   }
-  for (int q = NBUCKET; q < NQUEUE; ++q) {
-    cnt[C_Q + 2 * q] = q == Q_STALL_HI ? -1 : 0;
-    cnt[C_Q + 2 * q + 1] = 0;
-  }
-  RBFFD_HIP(ctx, hipMemcpyAsync(d_cnt + C_CURSOR, cnt + C_CURSOR, (C_STATUS - C_CURSOR) * sizeof(int),
-                                hipMemcpyHostToDevice, s));
-  bucket_fill_kernel<<<grid_for(nc, BK_BLOCK), BK_BLOCK, 0, s>>>(st->n_per, st->n_max, st->m_per, st->m_uniform,
-                                                                 st->l_per, st->l_uniform, nc, d_cnt + C_CURSOR,
-                                                                 d_list);
-  RBFFD_HIP(ctx, hipGetLastError());
   int2 *queue = reinterpret_cast<int2 *>(d_cnt + C_Q);
 
   WArgs a{};
@@ -1852,14 +1865,14 @@ int weights_run(rbffd_ctx *ctx, const rbffd_stencils *st, const rbffd_op *ops, i
   a.w = w;
   a.status = st_out;
   a.max_iter = precision == RBFFD_SOLVE_FP64 ? 3 : 30;
-  a.list = d_list;
+  a.list = uniform ? nullptr : d_list;
   const bool f64 = precision == RBFFD_SOLVE_FP64;
   int *d_def = nullptr;
   if (cnt[0] > 0) RBFFD_WS(ctx, ws, ws.get(cnt[0], &d_def));
   for (int b = 0; b < NBUCKET; ++b) {
     if (bucket_ev) RBFFD_HIP(ctx, hipEventRecord(bucket_ev[2 * b], s));
     if (cnt[b] > 0) {
-      a.qinfo = queue + b;
+      a.qinfo = uniform ? nullptr : queue + b;
       a.k_cap = cnt[C_KMAX + b];  // the bucket's largest K
       if (b == 0) {
         // systems of up to 32 unknowns: two per wavefront, then the stencils
@@ -1915,6 +1928,7 @@ int weights_run(rbffd_ctx *ctx, const rbffd_stencils *st, const rbffd_op *ops, i
     }
     if (n_large > 0) {
       f.qinfo = queue + Q_STALL_HI;
+      f.from_end = 1;
       f.k_cap = kc;
       const int rc = launch_block<double>(ctx, f, grid_of(n_large, 2, n_cu));
       if (rc) return rc;
