@@ -1090,13 +1090,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(wave_occ<KC,
 //
 // Bound by the chain of a step (LDS read, update, pivot search, reciprocal,
 // LDS write, barrier). The 4,700 K = 82 systems of the mixed 1M batch take
-// 1.04 ms (FP64) against 2.84 ms, and the 500 of a 128 x 128 batch with FP32
-// factors 0.45 ms against 2.42 ms, with the matrix in LDS, rows interchanged
+// 0.98 ms (FP64) against 2.84 ms, and the 500 of a 128 x 128 batch with FP32
+// factors 0.41 ms against 2.42 ms, with the matrix in LDS, rows interchanged
 // there and a barrier per step of every substitution.
 template <typename T> struct BlockShared {
   T l[2][128];           // multipliers of the step in flight and the next
   T rp[128];             // 1 / pivot of each step
   int pv[128];           // pivot row of each step
+  int mono[28];          // exponents of each monomial: a | b << 8
   double red[4][2];      // per wavefront: maxima
   int gl[MAX_OPS], kg[MAX_OPS];  // operators of the current group, their k
   int flag;
@@ -1147,13 +1148,18 @@ __device__ __forceinline__ bool block_refine(const WArgs &a, BlockShared<T> &S, 
   const int NP = K <= 84 ? 3 : 2, RW = 64 / NP;
   const int part = ln / RW, row = wv * RW + (ln - part * RW);
   const bool act = part < NP && row < K, is_node = row < n;
+  auto exps = [&](int q, int &ea, int &eb) {
+    const int v = S.mono[q];
+    ea = v & 255;
+    eb = v >> 8;
+  };
   double own[4] = {0.0, 0.0, 0.0, 0.0};
   int pa = 0, pb = 0;
   if (act && is_node) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) own[u] = Y.off[4 * row + u];
   } else if (act) {
-    mono(row - n, pa, pb);
+    exps(row - n, pa, pb);
   }
   dd bc[G];  // the right-hand sides
 #pragma unroll
@@ -1172,23 +1178,30 @@ __device__ __forceinline__ bool block_refine(const WArgs &a, BlockShared<T> &S, 
     dd acc[G] = {};
     if (act && plain_pass) {
       const int e = (Y.mg - 1) / 2;
-      for (int j = part; j < K; j += NP) {
-        double ev = 0.0;
-        if (j < n && is_node) {
+      int j = part;
+      for (; j < n; j += NP) {
+        double ev;
+        if (is_node) {
           const double ddx = own[0] - Y.off[4 * j], ddz = own[2] - Y.off[4 * j + 2];
           const double s2 = ddx * ddx + ddz * ddz;
           const bool pos = s2 > 0.0;
           double r = sqrt_pos(pos ? s2 : 1.0);
           for (int t = 0; t < e; ++t) r *= s2;
           ev = pos ? r : 0.0;
-        } else if (j < n || is_node) {
-          int qa = pa, qb = pb;
-          if (j >= n) mono(j - n, qa, qb);
-          ev = block_mono<PW>(Y, j < n ? j : row, qa, qb).hi;
+        } else {
+          ev = block_mono<PW>(Y, j, pa, pb).hi;
         }
 #pragma unroll
         for (int g = 0; g < G; ++g) acc[g].hi = fma(ev, Y.xs[4 * j + g], acc[g].hi);
       }
+      if (is_node)
+        for (; j < K; j += NP) {
+          int qa, qb;
+          exps(j - n, qa, qb);
+          const double ev = block_mono<PW>(Y, row, qa, qb).hi;
+#pragma unroll
+          for (int g = 0; g < G; ++g) acc[g].hi = fma(ev, Y.xs[4 * j + g], acc[g].hi);
+        }
     } else if (act && it > 0) {
       // node columns: Phi for node rows, the monomials of node j for
       // polynomial rows; then the polynomial columns of node rows
@@ -1207,7 +1220,7 @@ __device__ __forceinline__ bool block_refine(const WArgs &a, BlockShared<T> &S, 
         if (is_node)
           for (; j < K; j += NP) {
             int qa, qb;
-            mono(j - n, qa, qb);
+            exps(j - n, qa, qb);
             const dd e = block_mono<PW>(Y, row, qa, qb);
 #pragma unroll
             for (int g = 0; g < G; ++g) acc[g] = dd_acc(acc[g], e, Y.xs[4 * j + g]);
@@ -1350,6 +1363,11 @@ __device__ __forceinline__ void block_solve(const WArgs &a, BlockShared<T> &S, d
     reject(1);
     return;
   }
+  if (tid >= 128 && tid < 128 + K - n) {  // (n <= 120: other threads than the nodes')
+    int ea, eb;
+    mono(tid - 128, ea, eb);
+    S.mono[tid - 128] = ea | (eb << 8);
+  }
   if (tid < n) {
     const dd ex = dd_div(dx, dd{rho, 0.0}), ez = dd_div(dz, dd{rho, 0.0});
     double *o = Y.off + 4 * tid;
@@ -1420,9 +1438,8 @@ __device__ __forceinline__ void block_solve(const WArgs &a, BlockShared<T> &S, d
           for (int t = 0; t < e; ++t) r *= s2;
           v = pos ? r : 0.0;
         } else if (i < n || j < n) {
-          int qa, qb;
-          mono((i < n ? j : i) - n, qa, qb);
-          v = block_mono<PW>(Y, i < n ? i : j, qa, qb).hi;
+          const int q2 = S.mono[(i < n ? j : i) - n];
+          v = block_mono<PW>(Y, i < n ? i : j, q2 & 255, q2 >> 8).hi;
         }
         Y.F[j * kc + i] = static_cast<T>(v);
         amax = fmax(amax, fabs(v));
