@@ -530,3 +530,45 @@ def test_weights_tuner_shapes_are_bit_identical(R, ctx):
     with pytest.raises(R.RbffdError) as e:
         R.rbffd_weights_tune(ctx, xy, ops, cfg["n_max"], shapes=[10, 0, 0, 0, 0, 0], **kw)
     assert e.value.code == R.EINVAL
+
+
+def test_scratch_large_and_parallel_calls(R):
+    """The context keeps its scratch between calls up to 64 MB: a search that
+    needs more (6 million nodes, 72 MB) takes a block of its own, and so does a
+    call beside another thread's on the same context. Both give the exact
+    search; the small one is the same alone, after and beside others."""
+    import threading
+    import torch
+    ctx = R.Context(0)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    xy = torch.rand((6_000_000, 2), generator=g, device="cuda", dtype=torch.float64)
+    cen = torch.arange(0, 6_000_000, 1_000_003, device="cuda", dtype=torch.int32)
+    small = dev(jittered_square(40, seed=4).xy, torch.float64)
+    want = host(R.rbffd_knn(ctx, small, 21))
+    got = host(R.rbffd_knn(ctx, xy, 13, centers=cen))
+    for k, c in enumerate(cen.tolist()):
+        d = (xy[:, 0] - xy[c, 0]) ** 2 + (xy[:, 1] - xy[c, 1]) ** 2
+        near = torch.topk(d, 14, largest=False, sorted=True)
+        assert np.all(np.diff(host(near.values)) > 0)          # no ties: the order is the distances'
+        assert np.array_equal(got[k], host(near.indices)[:13])
+    assert np.array_equal(host(R.rbffd_knn(ctx, small, 21)), want)
+    ops = [(R.DX, 0, 0), (R.DZ, 0, 0)]
+    w_want = host(R.rbffd_weights(ctx, small, ops, 21, 5, 3)[1])
+    bad = []
+
+    def work(kind):
+        torch.cuda.set_device(0)
+        for _ in range(20):
+            if kind:
+                ok = np.array_equal(host(R.rbffd_weights(ctx, small, ops, 21, 5, 3)[1]), w_want)
+            else:
+                ok = np.array_equal(host(R.rbffd_knn(ctx, small, 21)), want)
+            if not ok:
+                bad.append(kind)
+    ts = [threading.Thread(target=work, args=(k,)) for k in (0, 1, 0)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not bad
