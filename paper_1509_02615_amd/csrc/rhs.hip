@@ -744,7 +744,7 @@ __global__ __launch_bounds__(RHS_BLOCK) void ghost_apply_kernel(GArgs a) {
 // entries; the ranges' sums meet in LDS. A closure has few rows (256 of the
 // 400 m channel at 64 members: 256 units), so one wavefront per unit left most
 // of the chip idle in a chain of 37 and 243 loads: 10.9 and 16.4 us against
-// 5.8 and 7.8. Sums run in slot / entry order per range, so such members
+// 5.8 and 7.4. Sums run in slot / entry order per range, so such members
 // agree with single-member runs to rounding rather than bit for bit.
 constexpr int GHOST_MEMBER_LANES = 16;
 constexpr int GHOST_PARTS = 4;
@@ -788,13 +788,19 @@ __device__ __forceinline__ void part_range(int part, int len, int &qb, int &qe) 
   qe = min(len, qb + per);
 }
 
-template <class FT>
+// UNI: a multiple of 64 members, so a wavefront's row is one row, and its
+// inverse entries are scalar loads (64 members: 66 -> 52 us for 4,096 rows, 8.2
+// -> 7.4 us for 256). The residuals stay together by row: a plane per field,
+// which halves what the windows read, took 76 and 13 us (three loads an entry
+// for one).
+template <class FT, bool UNI>
 __global__ __launch_bounds__(64 * GHOST_PARTS) void ghost_apply_members_kernel(GArgs a) {
   const int part = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   const int64_t total = static_cast<int64_t>(a.R) * a.E;
   const int64_t u = static_cast<int64_t>(blockIdx.x) * 64 + (threadIdx.x & 63), t = min(u, total - 1);
-  const int64_t row = t / a.E;
+  int64_t row = t / a.E;
   const int e = static_cast<int>(t - row * a.E);
+  if constexpr (UNI) row = __builtin_amdgcn_readfirstlane(static_cast<int>(row));
   double v[4] = {0.0, 0.0, 0.0, 0.0};
   int qb, qe;
   if (!a.u_shared) {
@@ -899,10 +905,12 @@ int launch_ghost(rbffd_ctx *ctx, rbffd_model *m, void *y, void *zero = nullptr) 
     const unsigned grid = grid_for(cnt, 64), block = 64 * GHOST_PARTS;
     if (m->fdt == RBFFD_F64) {
       ghost_resid_members_kernel<double><<<grid, block, 0, ctx->stream>>>(g);
-      ghost_apply_members_kernel<double><<<grid, block, 0, ctx->stream>>>(g);
+      (m->E % 64 == 0 ? ghost_apply_members_kernel<double, true> : ghost_apply_members_kernel<double, false>)
+          <<<grid, block, 0, ctx->stream>>>(g);
     } else {
       ghost_resid_members_kernel<float><<<grid, block, 0, ctx->stream>>>(g);
-      ghost_apply_members_kernel<float><<<grid, block, 0, ctx->stream>>>(g);
+      (m->E % 64 == 0 ? ghost_apply_members_kernel<float, true> : ghost_apply_members_kernel<float, false>)
+          <<<grid, block, 0, ctx->stream>>>(g);
     }
   } else {
     const unsigned grid = grid_for(cnt, RHS_BLOCK / 64);                 // one wavefront each
