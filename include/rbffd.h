@@ -126,7 +126,9 @@ int rbffd_knn(rbffd_ctx *ctx, const rbffd_stencils *st, int32_t *idx);
  * and keep w. The system is formed in a frame centred at x_c and scaled by
  * the largest centre-to-node distance, solved by LU with partial pivoting in
  * FP64 (or an FP32 factorisation when precision = RBFFD_SOLVE_FP32_IR) plus
- * iterative refinement with double-double residuals, then rescaled.
+ * iterative refinement with double-double residuals, then rescaled. With an
+ * FP32 factorisation the substitutions run in FP32 as well for K = n + M up to
+ * 64 (in FP64 above), and the first refinement passes take FP64 residuals.
  * Runs the A1 search first unless st->idx_in is given (then idx is a copy).
  * Outputs: idx [Nc][n_max] (may be NULL when idx_in is given),
  *          w [n_ops][Nc][n_max] FP64 (zero past n_c),

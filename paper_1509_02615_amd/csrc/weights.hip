@@ -35,8 +35,8 @@
 //     stencils differs by ~5e-10), correction through the same factors,
 //     until the correction is at rounding level (with FP32 factors the
 //     first passes take plain FP64 residuals of the FP64 matrix, and
-//     double-double ones from there on, and the corrections are solved for
-//     in FP32);
+//     double-double ones from there on; the wavefront kernels then solve for
+//     the corrections in FP32, the workgroup kernel in FP64);
 //  5. rescaling by rho^-q (q = derivative order) and the padded row write.
 //
 // FP64 matrix cores on gfx950 have the same peak as the FP64 vector ALUs,
@@ -1079,14 +1079,20 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(wave_occ<KC,
 // Four wavefronts; lane i holds rows i and i + 64 of A in registers, wavefront
 // w the columns 4 c + w. A step of the elimination takes one barrier: the
 // wavefront that owns the next column updates that column first, picks its
-// pivot row (data-parallel maximum, as in the wavefront kernels), and leaves
-// the multipliers in LDS while the others update the rest; nobody moves rows,
-// and the pivot row's entries come from the pivot lane's registers. The
-// factors, each row scaled by its own 1 / pivot, then go to LDS for the
+// pivot row (data-parallel maximum) and leaves the multipliers in LDS while the
+// others update the rest; nobody moves rows, and the pivot row's entries come
+// from the pivot lane's registers. The factors then go to LDS for the
 // substitutions: one wavefront per right-hand side, the unknowns in registers,
 // the column of a step an independent LDS read, no barriers. The residual
 // takes three lanes per row (K <= 84) or two, with the same |x_i - x_j|^m and
 // power tables as the wavefront kernels.
+//
+// Pivots are compared in full, multipliers are rounded quotients and the
+// substitutions run in FP64, also on FP32 factors: whether a refinement with
+// FP32 factors converges (status 0 or 3) hangs on them at condition numbers of
+// 1e9. With pivots compared on 16 bits, products with reciprocals and FP32
+// substitutions a quarter of such systems went the other way, for 2-4% (FP64
+// factors) and 4-12% (FP32) less time.
 //
 // Bound by the chain of a step (LDS read, update, pivot search, reciprocal,
 // LDS write, barrier). The 4,700 K = 82 systems of the mixed 1M batch take
@@ -1095,7 +1101,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(wave_occ<KC,
 // there and a barrier per step of every substitution.
 template <typename T> struct BlockShared {
   T l[2][128];           // multipliers of the step in flight and the next
-  T rp[128];             // 1 / pivot of each step
+  T piv[128];            // pivot of each step
   int pv[128];           // pivot row of each step
   int mono[28];          // exponents of each monomial: a | b << 8
   double red[4][2];      // per wavefront: maxima
@@ -1117,7 +1123,7 @@ template <typename T> struct BlockSys {
   double *off;   // [kc][4] scaled node offsets: x hi, x lo, z hi, z lo
   double *xs;    // [kc][4] current solution of the right-hand sides in flight
   double *vs;    // [4][kc] residuals
-  T *F;          // [K columns][kc] scaled factors
+  T *F;          // [K columns][kc] factors: multipliers up to a row's own step, then its U entries
   double *pw;    // node t, power e at t (l + 1) + e: x^e (hi, lo), z^e (hi, lo)
   int kc, n, K, mg, P;
 };
@@ -1132,6 +1138,11 @@ template <bool PW, typename T> __device__ __forceinline__ dd block_mono(const Bl
     return dd_mulr(dd_ipow(dd{o[0], o[1]}, a), dd_ipow(dd{o[2], o[3]}, b));
   }
 }
+
+// |v| as unsigned words in its order
+__device__ __forceinline__ unsigned mag_hi(double v) { return __double2hiint(v) & 0x7fffffff; }
+__device__ __forceinline__ unsigned mag_lo(double v) { return __double2loint(v); }
+__device__ __forceinline__ unsigned mag_hi(float v) { return __float_as_uint(v) & 0x7fffffff; }
 
 // Solve for the G right-hand sides of operators S.gl[g0 ..], then refine with
 // double-double residuals until the stopping rule holds (with FP32 factors the
@@ -1169,7 +1180,8 @@ __device__ __forceinline__ bool block_refine(const WArgs &a, BlockShared<T> &S, 
                                          dd{own[0], own[1]}, dd{own[2], own[3]})
                              : dd{0.0, 0.0};
   }
-  const T rdg0 = st0 < K ? S.rp[st0] : T(0), rdg1 = st1 < K ? S.rp[st1] : T(0);
+  const double rdg0 = st0 < K ? 1.0 / static_cast<double>(S.piv[st0]) : 0.0,
+               rdg1 = st1 < K ? 1.0 / static_cast<double>(S.piv[st1]) : 0.0;
   const int pv0 = S.pv[min(ln, K - 1)], pv1 = S.pv[min(ln + 64, K - 1)];  // lane k: pivot rows of steps k, k + 64
   double dprev = 0.0;
   bool plain = F32, converged = false;
@@ -1248,30 +1260,35 @@ __device__ __forceinline__ bool block_refine(const WArgs &a, BlockShared<T> &S, 
       }
     }
     __syncthreads();
-    // substitutions of right-hand side wv, in the factors' precision
+    // substitutions of right-hand side wv, in FP64 whatever the factors' type
     double dm = 0.0, xm = 0.0;
     if (wv < G) {
       const bool r0 = ln < K, r1 = ln + 64 < K;
-      T w0 = r0 ? static_cast<T>(Y.vs[wv * kc + ln] * static_cast<double>(rdg0)) : T(0);
-      T w1 = r1 ? static_cast<T>(Y.vs[wv * kc + ln + 64] * static_cast<double>(rdg1)) : T(0);
+      double w0 = r0 ? Y.vs[wv * kc + ln] : 0.0, w1 = r1 ? Y.vs[wv * kc + ln + 64] : 0.0;
       auto step = [&](int k, int p, bool fwd) {
-        const T y = rl(p >= 64 ? w1 : w0, p & 63);
-        const T f0 = Y.F[k * kc + ln], f1 = Y.F[k * kc + ln + 64];
+        const double y = rl(p >= 64 ? w1 : w0, p & 63);
+        double f0 = static_cast<double>(Y.F[k * kc + ln]), f1 = static_cast<double>(Y.F[k * kc + ln + 64]);
+        if (!fwd) {  // (beside the chain: no product waits for y)
+          f0 *= rdg0;
+          f1 *= rdg1;
+        }
         const bool u0 = r0 && (fwd ? st0 > k : st0 < k), u1 = r1 && (fwd ? st1 > k : st1 < k);
-        w0 = fma(-(u0 ? f0 : T(0)), y, w0);
-        w1 = fma(-(u1 ? f1 : T(0)), y, w1);
+        w0 = fma(-(u0 ? f0 : 0.0), y, w0);
+        w1 = fma(-(u1 ? f1 : 0.0), y, w1);
       };
 #pragma unroll 4
       for (int k = 0; k < k64; ++k) step(k, __builtin_amdgcn_readlane(pv0, k), true);
 #pragma unroll 4
       for (int k = 64; k < K; ++k) step(k, __builtin_amdgcn_readlane(pv1, k - 64), true);
+      w0 *= rdg0;
+      w1 *= rdg1;
 #pragma unroll 4
       for (int k = K - 1; k >= 64; --k) step(k, __builtin_amdgcn_readlane(pv1, k - 64), false);
 #pragma unroll 4
       for (int k = k64 - 1; k >= 0; --k) step(k, __builtin_amdgcn_readlane(pv0, k), false);
       // row p_k holds the correction of unknown k
-      auto add = [&](int st, T w) {
-        const double d = static_cast<double>(w), x = Y.xs[4 * st + wv] + d;
+      auto add = [&](int st, double d) {
+        const double x = Y.xs[4 * st + wv] + d;
         Y.xs[4 * st + wv] = x;
         dm = fmax(dm, fabs(d));
         xm = fmax(xm, fabs(x));
@@ -1464,24 +1481,32 @@ __device__ __forceinline__ void block_solve(const WArgs &a, BlockShared<T> &S, d
     bool f0 = ln < K, f1 = ln + 64 < K;  // rows not yet chosen as pivot rows
     int st0 = KC, st1 = KC;              // elimination step of each row
     double pmin = INFINITY;
-    // pivot row of step k among the free rows of its column (a0, a1): compared
-    // on 16 mantissa bits, ties to the highest row; + 128 keeps free rows above
-    // the others
-    auto search = [&](T a0, T a1, int k) {
-      auto key = [](T v, int row) {
-        return ((__float_as_uint(static_cast<float>(fabs(static_cast<double>(v)))) & ~127u) + 128u) |
-               static_cast<unsigned>(row);
-      };
-      const unsigned m0 = f0 ? key(a0, ln) : 0u, m1 = f1 ? key(a1, ln + 64) : 0u;
-      const int p = static_cast<int>(wave_max_u32(max(m0, m1)) & 127u);
+    // pivot row of step k, the largest entry among the free rows of its column
+    // (a0, a1; the lowest row of equal ones); the column's other free rows
+    // become their multipliers
+    auto search = [&](T &a0, T &a1, int k) {
+      const unsigned h0 = f0 ? mag_hi(a0) + 1 : 0u, h1 = f1 ? mag_hi(a1) + 1 : 0u;  // (0: not free)
+      const unsigned hm = wave_max_u32(max(h0, h1));
+      uint64_t b0 = __ballot(h0 == hm), b1 = __ballot(h1 == hm);
+      if constexpr (!std::is_same<T, float>::value) {
+        if (__popcll(b0) + __popcll(b1) > 1) {  // equal upper words: by the lower ones
+          const unsigned g0 = h0 == hm ? mag_lo(a0) : 0u, g1 = h1 == hm ? mag_lo(a1) : 0u;
+          const unsigned gm = wave_max_u32(max(g0, g1));
+          b0 &= __ballot(g0 == gm);
+          b1 &= __ballot(g1 == gm);
+        }
+      }
+      const int p = b0 ? __builtin_ctzll(b0) : 64 + __builtin_ctzll(b1);
       const T piv = rl(p >= 64 ? a1 : a0, p & 63);
       pmin = fmin(pmin, fabs(static_cast<double>(piv)));
-      const T rp = recip(piv);
-      S.l[k & 1][ln] = f0 && ln != p ? a0 * rp : T(0);
-      S.l[k & 1][ln + 64] = f1 && ln + 64 != p ? a1 * rp : T(0);
+      const bool e0 = f0 && ln != p, e1 = f1 && ln + 64 != p;
+      a0 = e0 ? a0 / piv : a0;
+      a1 = e1 ? a1 / piv : a1;
+      S.l[k & 1][ln] = e0 ? a0 : T(0);
+      S.l[k & 1][ln + 64] = e1 ? a1 : T(0);
       if (ln == 0) {
         S.pv[k] = p;
-        S.rp[k] = rp;
+        S.piv[k] = piv;
       }
     };
     if (wv == 0) search(r0[0], r1[0], 0);
@@ -1526,15 +1551,12 @@ __device__ __forceinline__ void block_solve(const WArgs &a, BlockShared<T> &S, d
     }
     __syncthreads();
     if (ln == 0) S.red[wv][1] = pmin;
-    // each row scaled by its own 1 / pivot, to LDS for the substitutions
-    {
-      const T d0 = ln < K ? S.rp[st0] : T(0), d1 = ln + 64 < K ? S.rp[st1] : T(0);
+    // the factors to LDS for the substitutions
 #pragma unroll
-      for (int cc = 0; cc < CL; ++cc) {
-        const int j = 4 * cc + wv;
-        if (j < K && ln < K) Y.F[j * kc + ln] = r0[cc] * d0;
-        if (j < K && ln + 64 < K) Y.F[j * kc + ln + 64] = r1[cc] * d1;
-      }
+    for (int cc = 0; cc < CL; ++cc) {
+      const int j = 4 * cc + wv;
+      if (j < K && ln < K) Y.F[j * kc + ln] = r0[cc];
+      if (j < K && ln + 64 < K) Y.F[j * kc + ln + 64] = r1[cc];
     }
     __syncthreads();
     pmin = fmin(fmin(S.red[0][1], S.red[1][1]), fmin(S.red[2][1], S.red[3][1]));

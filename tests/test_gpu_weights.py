@@ -572,3 +572,101 @@ def test_scratch_large_and_parallel_calls(R):
     for t in ts:
         t.join()
     assert not bad
+
+
+def _two_sum(a, b):
+    s = a + b
+    t = s - a
+    return s, (a - (s - t)) + (b - t)
+
+
+def _dd_residual(A, B, X):
+    """B - A X for (high, low) pairs A and B, products split exactly (Dekker)
+    and the high parts summed error-free."""
+    def split(v):
+        t = v * 134217729.0
+        return t - (t - v), v - (t - (t - v))
+    hi, lo = B[0].copy(), B[1].copy()
+    (a1, a2), (x1, x2) = split(A[0]), split(X)
+    for j in range(len(X)):
+        p = A[0][:, j, None] * X[j]
+        e = ((a1[:, j, None] * x1[j] - p) + a1[:, j, None] * x2[j] + a2[:, j, None] * x1[j]) + a2[:, j, None] * x2[j]
+        hi, t = _two_sum(hi, -p)
+        lo += t - (e + A[1][:, j, None] * X[j])
+    return hi + lo
+
+
+def _fp32_factors_stall(xy, st, c, m, l, ops):
+    """Whether the refinement of one system with FP32 factors stalls: the FP32
+    elimination entry by entry (largest pivot, one rounding per multiplier and
+    per fused multiply-add), substitutions in FP64, the passes and the stopping
+    rule of include/rbffd.h."""
+    import scipy.linalg as sl
+    from oracle.weights import local_frame, saddle_matrix, saddle_rhs
+    x, z, _ = local_frame(xy, st, c, 0.0, np.longdouble)
+    A, B = [(v.astype(np.float64), (v - v.astype(np.float64)).astype(np.float64))
+            for v in (saddle_matrix(x, z, m, l), saddle_rhs(x, z, m, l, ops))]
+
+    def f32(v):
+        return v.astype(np.float32).astype(np.float64)
+    F = f32(A[0])
+    K = len(F)
+    piv = np.arange(K)
+    for k in range(K):
+        q = piv[k] = k + np.argmax(np.abs(F[k:, k]))
+        F[[k, q]] = F[[q, k]]
+        F[k + 1:, k] = f32(F[k + 1:, k] / F[k, k])
+        F[k + 1:, k + 1:] = f32(F[k + 1:, k + 1:] - np.outer(F[k + 1:, k], F[k, k + 1:]))
+    X = sl.lu_solve((F, piv), B[0])
+    dprev, plain = np.abs(X).max(), True
+    for _ in range(30):
+        D = sl.lu_solve((F, piv), B[0] - A[0] @ X if plain else _dd_residual(A, B, X))
+        X = X + D
+        dm, xm = np.abs(D).max(), np.abs(X).max()
+        if plain:
+            plain = not (dm <= 2.0 ** -24 * xm or dm > 0.5 * dprev)
+        elif dm <= 2.0 ** -48 * xm or (dm <= 0.5 * dprev and dm * dm <= 2.0 ** -52 * xm * dprev):
+            return False
+        dprev = dm
+    return True
+
+
+def _squeezed_lattice(sq, seed):
+    g = np.random.default_rng(seed)
+    X, Z = np.meshgrid(np.arange(40), np.arange(40))
+    return np.stack([X.ravel(), Z.ravel() * sq], 1) + g.uniform(-0.25, 0.25, (1600, 2)) * np.array([1.0, sq])
+
+
+@pytest.mark.parametrize("m, l, n, sq, seed", [(9, 4, 60, 0.3, 2), (7, 6, 75, 0.25, 1), (9, 6, 60, 0.3, 1)])
+def test_fp32_factors_fall_back_where_their_refinement_stalls(R, ctx, m, l, n, sq, seed):
+    """K > 64 systems at condition numbers of 1e9 to 1e10, where the refinement
+    with FP32 factors converges for about half of them: status 3 exactly where
+    the emulated elimination (pivots compared in full, multipliers rounded once,
+    substitutions in FP64) stalls. Only the residuals' sums differ from the
+    emulation's, at 2^-53 against the factors' 2^-24, so few systems can lie
+    close enough to the rule's edge to go the other way: 1 in 20 is allowed."""
+    import torch
+    xy = _squeezed_lattice(sq, seed)
+    centers = np.arange(0, 1600, 27, dtype=np.int32)
+    ops = [(O.DX, 0, 0), (O.DZ, 0, 0), (O.LAP, 0, 0)]
+    status = host(R.rbffd_weights(ctx, dev(xy, torch.float64), ops, n, m, l, centers=dev(centers, torch.int32),
+                                  precision=R.SOLVE_FP32_IR)[2])
+    want = np.array([_fp32_factors_stall(xy, O.knn(xy, [int(c)], n, 0.0)[0], int(c), m, l, [(k, kk) for k, kk, _ in ops])
+                     for c in centers])
+    off = int(np.count_nonzero((status == 3) != want))
+    say(f"weights: K = {n + (l + 1) * (l + 2) // 2}, FP32 factors: {int(want.sum())} of {len(centers)} stall, {off} differ")
+    assert 0.1 * len(centers) < want.sum() < 0.9 * len(centers)
+    assert np.all((status == 0) | (status == 3)) and off <= len(centers) // 20
+
+
+@pytest.mark.parametrize("m, l, n", [(3, 4, 60), (3, 5, 100), (5, 4, 60), (5, 5, 80), (5, 5, 100)])
+def test_fp32_factors_solve_well_conditioned_workgroup_systems(R, ctx, m, l, n):
+    """K > 64 systems of low order on a jittered lattice: FP32 factors are good
+    enough, so no stencil may need the FP64 solve (status 3) that would hide a
+    broken FP32 one."""
+    import torch
+    xy = _squeezed_lattice(1.0, 3)
+    ops = [(O.DX, 0, 0), (O.DZ, 0, 0), (O.LAP, 0, 0), (O.DZZ, 0, 0), (O.DXX, 0, 0)]
+    status = host(R.rbffd_weights(ctx, dev(xy, torch.float64), ops, n, m, l, precision=R.SOLVE_FP32_IR)[2])
+    say(f"weights: K = {n + (l + 1) * (l + 2) // 2}, r^{m}, FP32 factors: {int(np.count_nonzero(status))} not solved by them")
+    assert np.all(status == 0)
