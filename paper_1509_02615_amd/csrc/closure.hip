@@ -337,16 +337,19 @@ __device__ __forceinline__ bf8v read_tr2(unsigned p0, unsigned p1) {
 }
 
 // Back through the activation: d a'(h), rounded to BF16, from the BF16 values
-// h. relu: h is 0 or above, so the value is kept where h's bits are not 0.
+// h. relu: h is 0 or above, or NaN, and the value is kept where h > 0: where
+// h's bits lie in 1 .. 0x7f80, so that both h and 0x7f81 - h (saturating) are
+// at least 1. (A NaN activation has derivative 0, as in a comparison.)
 template <int ACT> __device__ __forceinline__ bf4v act_back(f4v d, bf4v h) {
   bf4v o;
   if constexpr (ACT == RBFFD_ACT_RELU) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) o[i] = static_cast<__bf16>(d[i]);
     typedef __attribute__((ext_vector_type(4))) unsigned short u4s;
-    const u4s hb = __builtin_bit_cast(u4s, h);
-    return __builtin_bit_cast(bf4v, static_cast<u4s>(__builtin_bit_cast(u4s, o) *
-                                                     __builtin_elementwise_min(hb, u4s{1, 1, 1, 1})));
+    const u4s hb = __builtin_bit_cast(u4s, h), top = {0x7f81, 0x7f81, 0x7f81, 0x7f81};
+    const u4s keep = __builtin_elementwise_min(__builtin_elementwise_min(hb, __builtin_elementwise_sub_sat(top, hb)),
+                                               u4s{1, 1, 1, 1});
+    return __builtin_bit_cast(bf4v, static_cast<u4s>(__builtin_bit_cast(u4s, o) * keep));
   } else {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {

@@ -244,3 +244,26 @@ def test_closure_gradient_tile_edges(nx, nz, n, E, act):
     assert np.all(g[OC.OW3 + 4 * OC.HID:OC.OB3] == 0.0) and np.all(g[OC.OB3 + 4:] == 0.0)
     g2, loss2 = cl.gradient(dev(state), dev(T.reshape(na, E, 4)))
     assert loss2 == loss and np.array_equal(g2.cpu().numpy().astype(np.float64), g)   # fixed summation order
+
+
+def test_closure_gradient_of_nan_activations(setup):
+    """relu's derivative is 0 where the activation is not above 0, and a NaN is
+    not: with one NaN hidden unit in layer 1, which makes all of layer 2 and the
+    outputs NaN, nothing flows back through either layer. The loss and the
+    output layer's gradient are NaN; the biases and weights below get exactly 0
+    (but for the W2 column that multiplies the NaN unit itself)."""
+    import torch
+    st = setup
+    p = OC.init_params(seed=5)
+    p[OC.OB1 + 5] = np.nan
+    cl, _ = _closure(st, p, IN_SCALE, OUT_SCALE, OC.RELU)
+    s = torch.from_numpy(st["closed"].astype(np.float32)).cuda().contiguous()
+    T = torch.zeros((st["nd"].n_active, st["E"], 4), dtype=torch.float32, device="cuda")
+    g, loss = cl.gradient(s, T)
+    g = g.cpu().numpy()
+    assert np.isnan(loss)
+    assert np.all(np.isnan(g[OC.OB3:OC.OB3 + 4])) and np.all(np.isnan(g[OC.OW3:OC.OW3 + 4 * OC.HID]))
+    W2 = g[OC.OW2:OC.OB2].reshape(OC.HID, OC.HID)
+    assert np.all(np.isnan(W2[:, 5])) and np.all(np.delete(W2, 5, 1) == 0.0)
+    assert np.all(g[OC.OB2:OC.OW3] == 0.0)
+    assert np.all(g[OC.OW1:OC.OW2] == 0.0)
