@@ -179,7 +179,7 @@ struct NSArgs {
 // P > 1: the slots of a unit of 64 (node, member) pairs are split over P
 // wavefronts of one block, whose sums meet in LDS; the first one applies the
 // stage. For launches of few wavefronts, where a wavefront's chain of loads
-// over all slots is what takes the time (split_of). Parts are ranges of
+// over all slots is what takes the time (split_ns). Parts are ranges of
 // stencil slots, whether or not the centre slot is streamed.
 template <class FT, int WDT, int S, bool MW = false, int P = 1>
 __global__ __launch_bounds__(P == 1 ? StageShape<S>::block : 64 * P) void ns_stage_kernel(NSArgs a) {
@@ -941,26 +941,51 @@ hipError_t launch_timed(void (*k)(A), unsigned grid, unsigned block, hipStream_t
   return hipGetLastError();
 }
 
-// Wavefronts per unit of 64 (node, member) pairs. One wavefront walks its
-// slots in a chain of loads; with fewer units than fill the chip (1,024 SIMDs)
-// that latency is the launch's time, so the slots are split. Small ensembles
-// go by the node count alone, so that members agree with a single run bit for
-// bit. Measured on hexagonal channels, us per right-hand side unsplit | split
-// (with the closure, 9 us of each): FP32 600 units 29.2 | 18.7, 2,064 39.7 |
-// 30.6, 3,600 43.6 | 41.2, 4,096 45.1 | 45.8, 8,192 78.6 | 92.8 (the weight
-// stream is then at the HBM rate, and the sums' exchange only costs); FP64 600
-// 26.0 | 18.3, 3,600 67.5 | 67.2, 4,096 72.5 | 79.2; BF16 2,064 39.7 | 29.7;
-// 64 members a unit 2,176 27.2 | 26.5, 6,528 48.7 | 59.4. Transport 625 7.1 |
-// 5.4, 1,024 9.2 | 10.4.
+// Whether a launch splits the slots of its units of 64 (node, member) pairs over
+// the wavefronts of a block. One wavefront walks its slots in a chain of loads:
+// where the units leave the chip part empty, that latency is the launch's time.
+//
+// Without splitting, R units are resident at once (eight wavefronts on each of
+// 1,024 SIMDs, five with FP64 fields), and a launch takes rounds of them. Up to
+// 0.7 R a split launch is faster; from there the sums' exchange only costs, until
+// ensembles pass R: an unsplit second round that is mostly empty costs more, up
+// to 1.35 R. us per launch, hexagonal channels, each side in its best shape,
+// unsplit | split:
+//   FP32, R = 8,192   1 member:   512 units 17.5 | 8.8, 1,024 24.4 | 12.2, 2,048 28.9 | 21.7,
+//                                 4,032 35.2 | 34.9, 5,120 41.3 | 40.0, 6,144 54.1 | 58.3
+//                     2-15:       2,048 27.8 | 18.6, 4,096 32.2 | 27.6, 5,632 36.4 | 33.9,
+//                                 6,144 36.9 | 37.5, 8,000 41.7 | 46.2, 9,600 57.9 | 54.9,
+//                                 11,200 60.1 | 60.9, 12,800 64.7 | 70.5
+//   BF16 weights      as FP32 within 2 us
+//   FP64, R = 5,120   1 member:   512 17.4 | 9.3, 2,048 26.5 | 27.1, 3,072 38.5 | 41.0,
+//                                 3,328 47.1 | 44.2, 4,032 59.8 | 65.0
+//                     2-15:       2,048 19.5 | 16.1, 3,584 24.0 | 23.7, 4,096 25.1 | 29.1,
+//                                 5,120 29.3 | 33.1, 6,144 45.3 | 39.1, 7,680 45.8 | 46.8
+// A wavefront of 64 members of one node loads its records once for all of them,
+// and splitting pays up to fewer units: FP32 2,176 17.8 | 14.8, 2,816 18.5 | 17.8,
+// 3,072 18.8 | 19.3, 4,096 19.8 | 22.7; FP64 3,328 21.7 | 21.0, 3,840 22.4 | 22.8;
+// BF16 3,840 20.2 | 19.8, 4,096 20.6 | 20.8. Transport (eight wavefronts a unit):
+// 512 5.0 | 4.3, 723 7.2 | 5.4, 827 8.1 | 7.5, 900 8.4 | 9.0, and with 8 or 15
+// members 960 5.1 | 5.3, 5,000 15.1 | 19.8, 9,375 26.6 | 34.8.
+//
+// The price: a split node's sums are added in another order, so members agree
+// with a run of their own to rounding, and bit for bit (fewer than 16 members)
+// only where both launches are split or neither is. Parts taken one after the
+// other by one wavefront would keep the bits, but need 30 registers more: 8,192
+// units in FP32 50.5 | 60.0, and 74.3 that way.
 constexpr int SPLIT = 4, ADV_SPLIT = 8;
-constexpr int64_t SPLIT_UNITS = 4096, ADV_SPLIT_UNITS = 768;
-inline bool split_of(int64_t na, int E, int64_t limit) {
-  return (na * (E < 16 ? 1 : E) + 63) / 64 < limit;
+inline int64_t units_of(int64_t na, int E) { return (na * E + 63) / 64; }
+inline bool split_adv(int64_t na, int E) { return units_of(na, E) < 768; }
+inline bool split_ns(int64_t na, int E, int wdt, bool mw) {
+  const int64_t u = units_of(na, E);
+  if (mw) return u < (wdt == RBFFD_F32 ? 2944 : wdt == RBFFD_F64 ? 3584 : 4096);
+  const int64_t R = wdt == RBFFD_F64 ? 5120 : 8192;
+  return 10 * u < 7 * R || (E > 1 && E < 16 && u > R && 20 * u <= 27 * R);
 }
 
 template <class FT, int WDT, int S, bool MW>
 hipError_t launch_ns_one(int64_t cnt, hipStream_t st, const NSArgs &a, hipEvent_t e0, hipEvent_t e1) {
-  if (split_of(a.Na, a.E, SPLIT_UNITS)) {
+  if (split_ns(a.Na, a.E, WDT, MW)) {
     // (block sizes do not apply: one instance per unrolling and load kind)
     constexpr int C = kShapes[S].unroll == 1 ? 0 : kShapes[S].unroll == 2 ? 1 : 5;
     return launch_timed(ns_stage_kernel<FT, WDT, C, MW, SPLIT>, grid_for(cnt, 64), 64 * SPLIT, st, a, e0, e1);
@@ -988,7 +1013,7 @@ hipError_t launch_ns_shape(int shape, int64_t cnt, hipStream_t st, const NSArgs 
 }
 
 template <class FT> hipError_t launch_adv(int64_t cnt, hipStream_t st, const AdvArgs &a, hipEvent_t e0, hipEvent_t e1) {
-  if (split_of(a.Na, a.E, ADV_SPLIT_UNITS))
+  if (split_adv(a.Na, a.E))
     return launch_timed(adv_stage_kernel<FT, ADV_SPLIT>, grid_for(cnt, 64), 64 * ADV_SPLIT, st, a, e0, e1);
   return launch_timed(adv_stage_kernel<FT, 1>, grid_for(cnt, RHS_BLOCK), RHS_BLOCK, st, a, e0, e1);
 }

@@ -790,3 +790,96 @@ def test_split_slots(R, ctx, na, E, n):
         err = np.abs(host(f)[..., 0] - want)
         say(f"   transport: {(err / np.maximum(mag, 1e-300)).max() / eps:.2f} eps")
         assert np.all(err <= (n + 8) * eps * mag)
+
+
+CONSTS = dict(c_p=1004.0, c_v=717.0, R_d=287.0, g=9.81, theta_bar=300.0, mu=0.7, u_bar=0.3)
+NS_TYPES = {"f64": (0, 0), "f32": (1, 1), "bf16": (1, 2)}
+
+
+def _random_ns(R, ctx, kind, na, E, n, seed=0):
+    """A model of arbitrary stencils and weights without walls (the centre in
+    slot 0 of every stencil, so that it is left out of the stream), its state,
+    stencils, weights and nodes, all on the device."""
+    import torch
+    fdt, wdt = NS_TYPES[kind]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1000 * n + seed)
+    idx = torch.randint(0, na, (na, n), generator=g, device="cuda", dtype=torch.int32)
+    idx[:, 0] = torch.arange(na, device="cuda", dtype=torch.int32)
+    W = torch.randn((4, na, n), generator=g, device="cuda", dtype=torch.float64)
+    xy = torch.rand((na, 2), generator=g, device="cuda", dtype=torch.float64)
+    y = torch.randn((na, E, 4), generator=g, device="cuda", dtype=torch.float64 if fdt == 0 else torch.float32)
+    m = R.Model(ctx, R.PHYS_NS, idx, W, xy, na, field_dtype=fdt, weight_dtype=wdt, ensemble=E, hv_coeff=0.4,
+                consts=CONSTS)
+    return m, y, idx.long(), W, xy
+
+
+def _tendency64(y, idx, W, xy):
+    """The Navier-Stokes tendency of _random_ns in FP64, and the magnitude of
+    what it sums."""
+    import torch
+    c, y = CONSTS, y.double()
+    d = y[idx] - y[:, None]                                            # [na][n][E][4]
+    D = [(w[:, :, None, None] * d).sum(1) for w in W]
+    A = [(w.abs()[:, :, None, None] * d.abs()).sum(1) + x.abs() for w, x in zip(W, D)]
+    u, w, th, pi = y.unbind(-1)
+    pib = (1.0 - c["g"] * xy[:, 1] / (c["c_p"] * c["theta_bar"]))[:, None]
+    ua, cpt = u + c["u_bar"], c["c_p"] * (c["theta_bar"] + th)
+    rcv, dpb = c["R_d"] / c["c_v"], -c["g"] / (c["c_p"] * c["theta_bar"])
+
+    def tend(X, a, s):
+        x, z, lp, hv = X
+        r = torch.stack([s * (a(ua) * x[..., 0] + a(w) * z[..., 0] + a(cpt) * x[..., 3]) + c["mu"] * lp[..., 0],
+                         s * (a(ua) * x[..., 1] + a(w) * z[..., 1] + a(cpt) * z[..., 3])
+                         + a(c["g"] * th / c["theta_bar"]) + c["mu"] * lp[..., 1],
+                         s * (a(ua) * x[..., 2] + a(w) * z[..., 2]) + c["mu"] * lp[..., 2],
+                         s * (a(ua) * x[..., 3] + a(w) * (abs(dpb) if s > 0 else dpb) + a(w) * z[..., 3]
+                              + a(rcv * (pib + pi)) * (x[..., 0] + z[..., 1]))], -1)
+        return r + 0.4 * hv
+    return tend(D, lambda v: v, -1.0), tend(A, torch.abs, 1.0)
+
+
+def _rhs(R, ctx, m, y):
+    import torch
+    f = torch.empty_like(y)
+    R.rbffd_rhs(ctx, m, 0.25, y.clone(), f)
+    return f
+
+
+def _random_transport(R, ctx, na, E, n, ng=0, fdt=0):
+    """A transport model of arbitrary stencils and weights (and ng mirror
+    ghosts), its state and, for the reference, stencils, the folded velocity
+    weights, the Lap^k weights and the ghosts' sources."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7 * n + na)
+    idx = torch.randint(0, na + ng, (na, n), generator=g, device="cuda", dtype=torch.int32)
+    W = torch.randn((3, na, n), generator=g, device="cuda", dtype=torch.float64)
+    xy = torch.rand((na + ng, 2), generator=g, device="cuda", dtype=torch.float64)
+    U, V = torch.randn((2, na + ng), generator=g, device="cuda", dtype=torch.float64)
+    src = torch.randint(0, na, (ng,), generator=g, device="cuda", dtype=torch.int32)
+    y = torch.randn((na + ng, E, 1), generator=g, device="cuda", dtype=torch.float64 if fdt == 0 else torch.float32)
+    m = R.Model(ctx, R.PHYS_ADVECTION, idx, W, xy, na, field_dtype=fdt, ensemble=E, hv_coeff=0.4, vel_u=U.contiguous(),
+                vel_v=V.contiguous(), vel_period=5.0, mirror_src=src if ng else None)
+    j = idx.long()
+    return m, y, j, W[0] * U[j] + W[1] * V[j], W[2], src.long()
+
+
+@pytest.mark.parametrize("kind", ["f64", "f32", "bf16"])
+def test_members_of_full_launches_are_not_split(R, ctx, kind):
+    """Whether slots are split goes by all units of a launch, members included:
+    15 members of 30,000 nodes fill the chip as 16 do, and each member has the
+    same bits in both (fewer than 16 members went by their nodes alone, and a
+    chip full of split units takes up to a third longer). Transport as well."""
+    import torch
+    na, n = 30000, 13
+    m16, y, *_ = _random_ns(R, ctx, kind, na, 16, n)
+    f16 = _rhs(R, ctx, m16, y)
+    m15, _, *_ = _random_ns(R, ctx, kind, na, 15, n)
+    f15 = _rhs(R, ctx, m15, y[:, :15].contiguous())
+    assert torch.equal(f15, f16[:, :15])
+    fdt = NS_TYPES[kind][0]
+    m16, y, *_ = _random_transport(R, ctx, na, 16, n, fdt=fdt)
+    f16 = _rhs(R, ctx, m16, y)
+    m15, _, *_ = _random_transport(R, ctx, na, 15, n, fdt=fdt)
+    assert torch.equal(_rhs(R, ctx, m15, y[:, :15].contiguous()), f16[:, :15])
