@@ -883,3 +883,80 @@ def test_members_of_full_launches_are_not_split(R, ctx, kind):
     f16 = _rhs(R, ctx, m16, y)
     m15, _, *_ = _random_transport(R, ctx, na, 15, n, fdt=fdt)
     assert torch.equal(_rhs(R, ctx, m15, y[:, :15].contiguous()), f16[:, :15])
+
+
+@pytest.mark.parametrize("kind, E, units", [
+    ("f64", 1, 3583), ("f64", 1, 3584), ("f64", 3, 5120), ("f64", 3, 5121), ("f64", 3, 6912), ("f64", 3, 6913),
+    ("f32", 1, 5734), ("f32", 1, 5735), ("f32", 5, 8192), ("f32", 5, 8193), ("f32", 5, 11059), ("f32", 5, 11060),
+    ("bf16", 1, 5734), ("bf16", 1, 5735), ("bf16", 2, 8193), ("bf16", 17, 8193),
+    ("f64", 64, 3583), ("f64", 64, 3584), ("f32", 64, 2943), ("f32", 64, 2944), ("bf16", 64, 4095), ("bf16", 64, 4096)])
+def test_split_limits(R, ctx, kind, E, units):
+    """Launches just below and just above each limit of slot splitting, with
+    FP64, FP32 and BF16 weights and members in lanes or by wavefront, against
+    plain FP64 sums. Bars: each sum's rounding, (n + 8) 2^-53 of the summed
+    magnitudes (FP32 fields: 2^-23), and BF16 weights' own 2^-16."""
+    n = 9
+    na = (64 * units - 63) // E + 1 if E < 64 else units              # the last unit holds a few pairs
+    assert (na * E + 63) // 64 == units
+    m, y, idx, W, xy = _random_ns(R, ctx, kind, na, E, n, units)
+    want, mag = _tendency64(y, idx, W, xy)
+    got = _rhs(R, ctx, m, y).double()
+    bar = (n + 8) * 2.0 ** (-53 if kind == "f64" else -23) + (2.0 ** -16 if kind == "bf16" else 0.0)
+    worst = float(((got - want).abs() / mag).max())
+    say(f"split limits: {kind}, E {E}, {units} units ({na} nodes): {worst / bar:.3f} of the bar")
+    assert worst <= bar
+
+
+@pytest.mark.parametrize("kind, E", [("f64", 1), ("f32", 1), ("bf16", 1), ("f64", 64), ("f32", 64), ("bf16", 64)])
+def test_forced_shapes_of_full_launches_identical(R, ctx, kind, E):
+    """Every launch shape of the unsplit stage kernels (for 64 members in row
+    and in Morton order) gives the same tendency bit for bit, and the tuner
+    keeps one of them."""
+    import torch
+    na = 64 * 5800 - 9 if E == 1 else 4200
+    m, y, *_ = _random_ns(R, ctx, kind, na, E, 9)
+    ref = _rhs(R, ctx, m, y)
+    for shape in range(12 if E == 64 else 6):
+        got, us = R.rbffd_model_tune(ctx, m, y.clone(), shape)
+        assert got == shape and us > 0
+        assert torch.equal(_rhs(R, ctx, m, y), ref), shape
+    R.rbffd_model_tune(ctx, m, y.clone())
+    assert torch.equal(_rhs(R, ctx, m, y), ref)
+
+
+@pytest.mark.parametrize("E, units", [(1, 767), (1, 768), (15, 767), (15, 768), (3, 2310)])
+def test_transport_split_limit(R, ctx, E, units):
+    """Transport right-hand sides and RK4 steps with mirror ghosts just below
+    and above the limit of slot splitting, against plain FP64 sums (13 slots).
+    Bars: (n + 8) 2^-53 of the summed magnitudes for one right-hand side; three
+    steps sum 12 of them, each in a state a few 2^-53 off, at |dt f| << |y|:
+    1e-13 relative l2."""
+    import torch
+    n, ng = 13, 500
+    na = (64 * units - 63) // E + 1
+    m, y, idx, adv, hv, src = _random_transport(R, ctx, na, E, n, ng)
+
+    def f(t, v, mag=False):
+        v = torch.cat([v, v[src]])[idx]                                # [na][n][E]
+        a = torch.abs if mag else (lambda x: x)
+        cs = np.cos(np.pi * t / 5.0)
+        return (-a(torch.tensor(cs)) * (-1.0 if mag else 1.0) * (a(adv)[..., None] * a(v)).sum(1)
+                + 0.4 * (a(hv)[..., None] * a(v)).sum(1))
+    v0 = y[:na, :, 0].clone()
+    got = _rhs(R, ctx, m, y)[..., 0]
+    err, mag = (got[:na] - f(0.25, v0)).abs(), f(0.25, v0, True)
+    say(f"transport split limit: E {E}, {units} units: {float((err / mag).max()) * 2.0 ** 53:.2f} eps")
+    assert bool((err <= (n + 8) * 2.0 ** -53 * mag).all()) and bool((got[na:] == 0.0).all())
+    dt, v = 1e-3, v0
+    s = y.clone()
+    R.rbffd_step(ctx, m, s, 0.1, dt, 3, R.RK4)
+    for k in range(3):
+        t = 0.1 + k * dt
+        k1 = f(t, v)
+        k2 = f(t + dt / 2, v + dt / 2 * k1)
+        k3 = f(t + dt / 2, v + dt / 2 * k2)
+        v = v + dt / 6 * (k1 + 2 * k2 + 2 * k3 + f(t + dt, v + dt * k3))
+    off = float(torch.linalg.norm(s[:na, :, 0] - v) / torch.linalg.norm(v))
+    say(f"   three RK4 steps: {off:.1e}")
+    assert off <= 1e-13
+    assert torch.equal(s[na:, :, 0], s[src, :, 0])
