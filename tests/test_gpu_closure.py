@@ -267,3 +267,54 @@ def test_closure_gradient_of_nan_activations(setup):
     assert np.all(np.isnan(W2[:, 5])) and np.all(np.delete(W2, 5, 1) == 0.0)
     assert np.all(g[OC.OB2:OC.OW3] == 0.0)
     assert np.all(g[OC.OW1:OC.OW2] == 0.0)
+
+
+def test_closure_fallback_of_one_member_in_one_step(setup):
+    """A member whose correction is not finite keeps the plain step, the others
+    are corrected, and a member that was bad in one step is corrected again in
+    the next: member 1 carries a spike of theta' whose input overflows before
+    the first step and, smoothed by it, no longer before the second (the
+    network's theta' weights are 0, so a finite input does nothing and an
+    infinite one makes NaN). The corrected states are dt times the forward pass
+    added to plain steps, to a few FP32 roundings."""
+    import torch
+    st = setup
+    R, na, E, dt = st["R"], st["nd"].n_active, st["E"], 1.0
+    p = OC.init_params(seed=2)
+    p[OC.OW1:OC.OB1].reshape(OC.HID, OC.KIN)[:, 2:4 * OC.NSLOT:4] = 0.0
+    y0 = torch.from_numpy(st["closed"].astype(np.float32)).cuda().contiguous()
+    spike = na // 2 + 40
+    y0[spike, 1, 2] += 60.0
+    R.rbffd_ghost(st["ctx"], st["gm"], y0)
+    y1 = y0.clone()
+    R.rbffd_step(st["ctx"], st["gm"], y1, 0.0, dt, 1, R.RK4)
+
+    def largest(y):                                        # largest theta' input of each member
+        th = y[..., 2].double()
+        d = th[torch.from_numpy(st["o_idx"]).cuda().long()] - th[:na, None]
+        return torch.maximum(d.abs().amax((0, 1)), th[:na].abs().amax(0)).cpu().numpy()
+    f0, f1 = largest(y0), largest(y1)
+    say(f"closure: one bad member, largest theta' inputs {f0} then {f1}")
+    # (the threshold lies between them, further from both than BF16's spacing of 2^-8)
+    assert f1[1] < 0.98 * f0[1] and max(f0[0], f0[2], f1[0], f1[2]) < 0.98 * f1[1]
+    scale = list(IN_SCALE)
+    scale[2] = float(np.sqrt(f0[1] * f1[1]) / np.finfo(np.float32).max)
+    cl, _ = _closure(st, p, scale, OUT_SCALE, OC.RELU)
+    want, fallbacks = y0.clone(), []
+    for k in range(2):
+        R.rbffd_ghost(st["ctx"], st["gm"], want)
+        corr = cl.forward(want)
+        good = torch.isfinite(corr).all(dim=2).all(dim=0)
+        fallbacks.append([int(e) for e in torch.nonzero(~good)])
+        R.rbffd_step(st["ctx"], st["gm"], want, 0.0, dt, 1, R.RK4)
+        want[:na, good] += dt * corr[:, good]
+    assert fallbacks == [[1], []]
+    got = y0.clone()
+    assert cl.step(got, 0.0, dt, 1, R.RK4)[1] == 1
+    assert torch.equal(got[:na, 1], y1[:na, 1])
+    assert not torch.equal(got[:na, 0], y1[:na, 0]) and not torch.equal(got[:na, 2], y1[:na, 2])
+    got = y0.clone()
+    assert cl.step(got, 0.0, dt, 2, R.RK4)[1] == 1
+    for f in range(4):
+        size = want[:na, :, f].abs().amax()
+        assert float((got[:na, :, f] - want[:na, :, f]).abs().amax() / size) < 1e-5, f
