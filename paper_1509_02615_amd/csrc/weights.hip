@@ -49,10 +49,7 @@
 
 namespace {
 
-#ifndef RBFFD_W_THREADS
-#define RBFFD_W_THREADS 256
-#endif
-constexpr int W_THREADS = RBFFD_W_THREADS;
+constexpr int W_THREADS = 256;  // of the workgroup kernel, which is written for four wavefronts
 constexpr int MAX_OPS = 8;
 
 struct WOp {
