@@ -95,7 +95,10 @@ enum { RBFFD_RK4 = 0, RBFFD_WSRK3 = 1 };
 /* ---- context ------------------------------------------------------------ */
 
 /* Create a context on HIP device `device`; `hip_stream` is a hipStream_t
- * (NULL = the null stream) that every call of this context is ordered on. */
+ * (NULL = the null stream) that every call of this context is ordered on.
+ * The context keeps the device scratch of its searches and weights between
+ * calls, up to 64 MiB (larger calls allocate and free their own), until
+ * rbffd_destroy gives it back. */
 int rbffd_create(rbffd_ctx **out, int device, void *hip_stream);
 int rbffd_destroy(rbffd_ctx *ctx);
 /* Message of the last failing call on this context (never NULL). */
@@ -307,7 +310,9 @@ int rbffd_model_profile_read(rbffd_model *model, double *total_ms, int64_t *laun
  * (its ghost entries are overwritten), time every compiled launch shape of
  * the kernel (block size, slot unrolling, cached or non-temporal weight
  * loads) on a few evaluations of this model's data, and keep the fastest
- * for all later calls. Models of a multiple of 64 members also try
+ * for all later calls. Small models, whose nodes' slots are split over the
+ * wavefronts of a block, have no block size to choose: shapes that differ by it
+ * alone are one launch, and the first of them stands for it. Models of a multiple of 64 members also try
  * traversing the nodes in Morton order of their coordinates (shape index + 6).
  * *chosen on entry: -1 to time every shape, or one shape index to time and
  * keep that one alone (EINVAL, nothing changed, if it is out of range); on
@@ -358,7 +363,7 @@ int rbffd_closure_forward(rbffd_ctx *ctx, rbffd_closure *cl, const void *state, 
 /* Autotuning of the fused forward pass: times each compiled launch shape
  * (16-sample tiles per wavefront 1 or 2, wavefronts per block 4, 8 or 16,
  * wavefronts per SIMD 2 or 4: shapes 0-4) on `state` and keeps the fastest for
- * later forward, step and training calls; every shape computes the same
+ * later forward and step calls; every shape computes the same
  * correction bit for bit. *chosen (host, in/out): -1 on entry tunes, a shape
  * 0-4 is timed and kept as given; on return the shape kept and its time per
  * call (us). Synchronises. EINVAL for a shape above 4. */

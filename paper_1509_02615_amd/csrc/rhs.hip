@@ -983,13 +983,14 @@ inline bool split_ns(int64_t na, int E, int wdt, bool mw) {
   return 10 * u < 7 * R || (E > 1 && E < 16 && u > R && 20 * u <= 27 * R);
 }
 
+// The shape whose split kernel shape s uses: block sizes do not apply to split
+// launches, which leaves one per unrolling (and its kind of load).
+constexpr int split_shape(int s) { return kShapes[s].unroll == 1 ? 0 : kShapes[s].unroll == 2 ? 1 : 5; }
+
 template <class FT, int WDT, int S, bool MW>
 hipError_t launch_ns_one(int64_t cnt, hipStream_t st, const NSArgs &a, hipEvent_t e0, hipEvent_t e1) {
-  if (split_ns(a.Na, a.E, WDT, MW)) {
-    // (block sizes do not apply: one instance per unrolling and load kind)
-    constexpr int C = kShapes[S].unroll == 1 ? 0 : kShapes[S].unroll == 2 ? 1 : 5;
-    return launch_timed(ns_stage_kernel<FT, WDT, C, MW, SPLIT>, grid_for(cnt, 64), 64 * SPLIT, st, a, e0, e1);
-  }
+  if (split_ns(a.Na, a.E, WDT, MW))
+    return launch_timed(ns_stage_kernel<FT, WDT, split_shape(S), MW, SPLIT>, grid_for(cnt, 64), 64 * SPLIT, st, a, e0, e1);
   constexpr int B = StageShape<S>::block;
   return launch_timed(ns_stage_kernel<FT, WDT, S, MW>, grid_for(cnt, B), B, st, a, e0, e1);
 }
@@ -1352,6 +1353,7 @@ int model_tune(rbffd_ctx *ctx, rbffd_model *m, void *state, int *chosen, double 
   if (forced < -1 || forced >= kNumShapes * n_orders)
     return rbffd_fail(ctx, RBFFD_EINVAL, "model_tune: shape %d is not -1 or in [0, %d)", forced,
                       kNumShapes * n_orders);
+  const bool split = split_ns(m->Na, m->E, m->wdt, m->E % 64 == 0);
   const int saved_profile = m->profile;
   m->profile = 0;
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1365,7 +1367,7 @@ int model_tune(rbffd_ctx *ctx, rbffd_model *m, void *state, int *chosen, double 
   for (int o = 0; o < n_orders && rc == RBFFD_OK; ++o) {
     m->use_order = o;
     for (int sh = 0; sh < kNumShapes && rc == RBFFD_OK; ++sh) {
-      if (forced >= 0 && forced != sh + kNumShapes * o) continue;
+      if (forced >= 0 ? forced != sh + kNumShapes * o : split && sh != split_shape(sh)) continue;
       m->shape = sh;
       rc = launch_stage(ctx, m, sp, 0.0, false, 0.0);  // warm-up
       if (rc) break;

@@ -960,3 +960,16 @@ def test_transport_split_limit(R, ctx, E, units):
     say(f"   three RK4 steps: {off:.1e}")
     assert off <= 1e-13
     assert torch.equal(s[na:, :, 0], s[src, :, 0])
+
+
+@pytest.mark.parametrize("kind, E", [("f64", 1), ("f32", 1), ("bf16", 3), ("f32", 64)])
+def test_tuner_names_a_split_launch_once(R, ctx, kind, E):
+    """Split launches have no block size, so shapes 0, 3 and 4 are one launch, and
+    1 and 2: the tuner times each launch once and returns the first shape of its
+    kind; every shape can still be forced."""
+    m, y, *_ = _random_ns(R, ctx, kind, 900, E, 9)
+    for _ in range(12):
+        shape, us = R.rbffd_model_tune(ctx, m, y)
+        assert shape % 6 in (0, 1, 5) and us > 0
+    for shape in range(6):
+        assert R.rbffd_model_tune(ctx, m, y, shape)[0] == shape
