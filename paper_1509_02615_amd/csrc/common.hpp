@@ -173,18 +173,19 @@ class ScratchLease {
 // the weights' count array.
 constexpr int KNN_BOX_BLOCKS = 512;
 constexpr int KNN_SCAN_TILE = 4096;
-constexpr size_t KNN_HEAD_BYTES = 256;
+constexpr size_t KNN_HEAD_BYTES = 256 + 32 * 128;
+constexpr int KNN_OVER_PAD = 128;
 constexpr int WEIGHTS_COUNTS = 40;
 constexpr size_t round256(size_t b) { return (b + 255) & ~size_t(255); }
 constexpr size_t knn_scratch_bytes(int64_t n_nodes, int64_t n_centers) {
-  // box partials, box, grid and findings, cell counts, cell starts, scan tile
-  // sums, nodes by cell, centres left to the dense-cluster kernel
+  // box partials, box, grid, findings and list counts, cell counts, cell starts,
+  // scan tile sums, nodes by cell, lists of the centres left over
   const size_t n = static_cast<size_t>(n_nodes), cells = n + 16;
   const size_t tiles = (cells + KNN_SCAN_TILE - 1) / KNN_SCAN_TILE;
   const size_t nc = static_cast<size_t>(n_centers > 1 ? n_centers : 1);
   return round256(sizeof(double) * 4 * KNN_BOX_BLOCKS) + round256(KNN_HEAD_BYTES) +
          round256(sizeof(int) * cells) + round256(sizeof(int) * (cells + 1)) + round256(sizeof(int) * tiles) +
-         round256(sizeof(int) * n) + round256(sizeof(int) * nc);
+         round256(sizeof(int) * n) + round256(sizeof(int) * (nc + KNN_OVER_PAD));
 }
 constexpr size_t CHECK_SCRATCH_BYTES = 256;
 constexpr size_t weights_scratch_bytes(int64_t n_centers) {

@@ -35,11 +35,19 @@ struct Grid {
 // What the launches of one search share in device memory, read back once at
 // its end. `go`: the arguments and the box are good; without it no launch
 // after the box touches anything.
+// The centres query_kernel leaves over are counted in OVER_LISTS lists, each
+// counter in a cache line of its own.
+constexpr int OVER_LISTS = 32;
 enum : int { BOX_OK = 0, BOX_NONFINITE = 1, BOX_PERIOD = 2 };
-struct Head {
+struct Findings {
   Grid g;
   double extent;  // of x
-  int go, box, flag[2], n_over;
+  int go, box, flag[2];
+};
+struct Head : Findings {
+  struct alignas(128) Count {
+    int n;
+  } over[OVER_LISTS];
 };
 static_assert(sizeof(Head) <= KNN_HEAD_BYTES, "scratch size formula");
 
@@ -156,7 +164,7 @@ __global__ __launch_bounds__(BOX_BLOCKS) void bbox_final_kernel(const double *__
   }
   if (t == 0) {
     const double box[4] = {s[0][0], s[1][0], s[2][0], s[3][0]};
-    Head h{};
+    Findings h{};
     h.extent = box[1] - box[0];
     h.flag[0] = flag[0];
     h.flag[1] = flag[1];
@@ -167,8 +175,9 @@ __global__ __launch_bounds__(BOX_BLOCKS) void bbox_final_kernel(const double *__
     else
       h.g = make_grid(box, period, n);
     h.go = h.box == BOX_OK && h.flag[0] == 0 ? 1 : 0;
-    *head = h;
+    static_cast<Findings &>(*head) = h;
   }
+  if (t < OVER_LISTS) head->over[t].n = 0;
 }
 
 __global__ void count_kernel(const double *__restrict__ xy, int n, const Head *__restrict__ head, int *__restrict__ count) {
@@ -368,11 +377,21 @@ __device__ __forceinline__ int scan32(int v) {
 // instructions) with whole (d, j) keys compared and each candidate's row found
 // by a test per row. A centre whose block holds more than KNN_KEYS candidates
 // (denser than about 2.5 nodes per cell there) or more than KNN_ROWS rows (a
-// sparse one) goes to `over`, for query_list_kernel.
+// sparse one) goes to a list of `over`, for query_list_kernel. Blocks share the
+// lists by XCD and in turns, because atomics on one counter take 10 ns each: with
+// one list, 200,000 of 300,000 centres left over made this kernel 1.97 ms, with
+// these 0.24 (the whole search 23.7 -> 21.0 ms, 22.5 with every centre sorted in LDS).
 constexpr int KNN_WAVES = 4;
 constexpr int KNN_REG = 4;
 constexpr int KNN_KEYS = 64 * KNN_REG;
 constexpr int KNN_ROWS = 32;
+
+// Most centres that one list can receive: the blocks that share it take
+// KNN_WAVES each.
+__host__ __device__ constexpr int over_cap(int n_centers) {
+  return KNN_WAVES * (((n_centers + KNN_WAVES - 1) / KNN_WAVES + OVER_LISTS - 1) / OVER_LISTS);
+}
+static_assert(KNN_WAVES * OVER_LISTS <= KNN_OVER_PAD, "scratch size formula");
 
 struct KnnShared {
   // distances of the candidates (then the sizes of the groups of equal ones);
@@ -421,7 +440,10 @@ __global__ __launch_bounds__(64 * KNN_WAVES) void query_kernel(
     const int incl = scan32(len);
     const int total = __builtin_amdgcn_readlane(incl, KNN_ROWS - 1);
     if (b.nzc > KNN_ROWS || total > KNN_KEYS) {
-      if (lane == 0) over[atomicAdd(&head->n_over, 1)] = q;
+      if (lane == 0) {
+        const int list = (bid % 8) * (OVER_LISTS / 8) + bid / 8 % (OVER_LISTS / 8);
+        over[static_cast<int64_t>(list) * over_cap(n_centers) + atomicAdd(&head->over[list].n, 1)] = q;
+      }
       return;
     }
     // candidate k = lane + 64 u, in row order: its row is the number of rows
@@ -534,17 +556,27 @@ __global__ __launch_bounds__(64 * KNN_WAVES) void query_kernel(
 // The centres query_kernel leaves over (uneven node sets): the same widening
 // blocks with up to KNN_CAP candidates sorted in LDS, one wavefront per
 // block. A centre of a still denser block is marked (KNN_DENSE in its first
-// entry) for query_wide_kernel, which runs over the same list.
+// entry) for query_wide_kernel, which runs over the same lists.
 constexpr int KNN_DENSE = -2;
+// The lists one after the other: item b of them all.
+struct OverLists {
+  int end[OVER_LISTS];  // items up to and with each list
+  int cap;
+  __device__ __forceinline__ int item(const int *over, int b) const {
+    int list = 0;
+    for (int t = 0; t < OVER_LISTS - 1; ++t) list += b >= end[t] ? 1 : 0;
+    return over[static_cast<int64_t>(list) * cap + b - (list ? end[list - 1] : 0)];
+  }
+};
 __global__ __launch_bounds__(KNN_BLOCK) void query_list_kernel(
     const double *__restrict__ xy, int n_nodes, Grid g, const int *__restrict__ start,
     const int *__restrict__ cell_nodes, const int *__restrict__ centers, int n_centers,
     const int *__restrict__ n_per, int n_max, int *__restrict__ idx,
-    const int *__restrict__ over) {
+    const int *__restrict__ over, OverLists lists) {
   __shared__ double sd[KNN_CAP];
   __shared__ int sj[KNN_CAP];
   __shared__ int s_scan[KNN_BLOCK];
-  const int q = over[blockIdx.x];
+  const int q = lists.item(over, blockIdx.x);
   const int lane = threadIdx.x;
   const int c = centers ? centers[q] : q;
   const int nq = n_per ? n_per[q] : n_max;
@@ -634,10 +666,10 @@ __global__ __launch_bounds__(KNN_BLOCK) void query_list_kernel(
 // by row range. O(n x candidates) per centre, for the few such centres.
 __global__ __launch_bounds__(KNN_BLOCK) void query_wide_kernel(
     const double *__restrict__ xy, Grid g, const int *__restrict__ start, const int *__restrict__ cell_nodes,
-    const int *__restrict__ centers, const int *__restrict__ n_per, int n_max, const int *__restrict__ list,
-    int *__restrict__ idx) {
+    const int *__restrict__ centers, const int *__restrict__ n_per, int n_max, const int *__restrict__ over,
+    OverLists lists, int *__restrict__ idx) {
   __shared__ int s_out[128];
-  const int q = list[blockIdx.x];
+  const int q = lists.item(over, blockIdx.x);
   const int lane = threadIdx.x;
   if (idx[static_cast<int64_t>(q) * n_max] != KNN_DENSE) return;  // the list kernel finished it
   const int c = centers ? centers[q] : q;
@@ -727,7 +759,7 @@ int knn_run(rbffd_ctx *ctx, const rbffd_stencils *st, int32_t *idx, Workspace &w
   RBFFD_WS(ctx, ws, ws.get(max_cells + 1, &d_start));
   RBFFD_WS(ctx, ws, ws.get(tiles, &d_tiles));
   RBFFD_WS(ctx, ws, ws.get(n, &d_nodes));
-  RBFFD_WS(ctx, ws, ws.get(std::max(nc, 1), &d_over));
+  RBFFD_WS(ctx, ws, ws.get(std::max(nc, 1) + KNN_OVER_PAD, &d_over));
   Head *head = static_cast<Head *>(d_head);
   const int nb = std::min(BOX_BLOCKS, static_cast<int>(grid_for(n, BOX_THREADS)));
   bbox_partial_kernel<<<nb, BOX_THREADS, 0, s>>>(st->xy, n, d_part);
@@ -750,11 +782,15 @@ int knn_run(rbffd_ctx *ctx, const rbffd_stencils *st, int32_t *idx, Workspace &w
   if (h.box == BOX_NONFINITE) return rbffd_fail(ctx, RBFFD_EINVAL, "non-finite node coordinates");
   if (h.box == BOX_PERIOD)
     return rbffd_fail(ctx, RBFFD_EINVAL, "x extent %g not inside one period %g", h.extent, st->period_x);
-  if (h.n_over > 0) {
-    query_list_kernel<<<h.n_over, KNN_BLOCK, 0, s>>>(st->xy, n, h.g, d_start, d_nodes, st->centers, nc, st->n_per,
-                                                     st->n_max, idx, d_over);
-    query_wide_kernel<<<h.n_over, KNN_BLOCK, 0, s>>>(st->xy, h.g, d_start, d_nodes, st->centers, st->n_per, st->n_max,
-                                                     d_over, idx);
+  OverLists lists{};
+  lists.cap = over_cap(nc);
+  int n_over = 0;
+  for (int t = 0; t < OVER_LISTS; ++t) lists.end[t] = n_over += h.over[t].n;
+  if (n_over > 0) {
+    query_list_kernel<<<n_over, KNN_BLOCK, 0, s>>>(st->xy, n, h.g, d_start, d_nodes, st->centers, nc, st->n_per, st->n_max,
+                                                   idx, d_over, lists);
+    query_wide_kernel<<<n_over, KNN_BLOCK, 0, s>>>(st->xy, h.g, d_start, d_nodes, st->centers, st->n_per, st->n_max, d_over,
+                                                   lists, idx);
     RBFFD_HIP(ctx, hipGetLastError());
     RBFFD_HIP(ctx, hipStreamSynchronize(s));  // results are complete on return, as after query_kernel
   }

@@ -670,3 +670,29 @@ def test_fp32_factors_solve_well_conditioned_workgroup_systems(R, ctx, m, l, n):
     status = host(R.rbffd_weights(ctx, dev(xy, torch.float64), ops, n, m, l, precision=R.SOLVE_FP32_IR)[2])
     say(f"weights: K = {n + (l + 1) * (l + 2) // 2}, r^{m}, FP32 factors: {int(np.count_nonzero(status))} not solved by them")
     assert np.all(status == 0)
+
+
+@pytest.mark.parametrize("count", [1, 3, 127, 128, 129, 1000, 3001])
+def test_knn_left_over_centres(R, ctx, count):
+    """Centres that the usual search leaves over (inside a dense patch), all of
+    them or in runs beside others, in numbers that fill the 32 lists of four
+    centres a block unevenly; bit-exact against the oracle."""
+    say(f"knn: {count} centres, inside and outside a dense patch")
+    rng = np.random.default_rng(count)
+    xy = np.concatenate([rng.uniform(0.0, 1.0, (800, 2)), np.array([0.5, 0.5]) + rng.uniform(-0.03, 0.03, (700, 2))])
+    inside, outside = 800 + rng.integers(0, 700, count), rng.integers(0, 800, count)
+    k = np.arange(count)
+    for some in (False, True):
+        pick = ((k // 32) % 3 == 0) | (((k // 32) % 3 == 1) & (k % 2 == 0)) if some else k >= 0
+        cen = np.where(pick, inside, outside).astype(np.int32)
+        for n in (13, 37):
+            _knn_case(R, ctx, xy, n, 0.0, centers=cen, sample=k[::max(1, count // 100)])
+
+
+def test_knn_mostly_left_over(R, ctx):
+    """40,000 of 50,000 centres left over: 400 of them and 100 others against the
+    oracle."""
+    rng = np.random.default_rng(8)
+    xy = np.concatenate([rng.uniform(0.0, 1.0, (10000, 2)), 0.5 + rng.uniform(-0.03, 0.03, (40000, 2))])
+    sample = np.concatenate([np.arange(0, 10000, 100), 10000 + rng.choice(40000, 400, replace=False)])
+    _knn_case(R, ctx, xy, 13, 0.0, sample=sample)
