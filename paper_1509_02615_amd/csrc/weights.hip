@@ -1079,8 +1079,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(wave_occ<KC,
 // pivot row (data-parallel maximum) and leaves the multipliers in LDS while the
 // others update the rest; nobody moves rows, and the pivot row's entries come
 // from the pivot lane's registers. The factors then go to LDS for the
-// substitutions: one wavefront per right-hand side, the unknowns in registers,
-// the column of a step an independent LDS read, no barriers. The residual
+// substitutions, rows in the order of their steps: one wavefront per right-hand
+// side, the unknowns in registers, the column of a step an independent LDS read,
+// no barriers. The residual
 // takes three lanes per row (K <= 84) or two, with the same |x_i - x_j|^m and
 // power tables as the wavefront kernels.
 //
@@ -1088,8 +1089,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(wave_occ<KC,
 // substitutions run in FP64, also on FP32 factors: whether a refinement with
 // FP32 factors converges (status 0 or 3) hangs on them at condition numbers of
 // 1e9. With pivots compared on 16 bits, products with reciprocals and FP32
-// substitutions a quarter of such systems went the other way, for 2-4% (FP64
-// factors) and 4-12% (FP32) less time.
+// substitutions a quarter of such systems went the other way, for 0-4% (FP64
+// factors) and 4-9% (FP32) less time.
 //
 // Bound by the chain of a step (LDS read, update, pivot search, reciprocal,
 // LDS write, barrier). The 4,700 K = 82 systems of the mixed 1M batch take
@@ -1120,7 +1121,7 @@ template <typename T> struct BlockSys {
   double *off;   // [kc][4] scaled node offsets: x hi, x lo, z hi, z lo
   double *xs;    // [kc][4] current solution of the right-hand sides in flight
   double *vs;    // [4][kc] residuals
-  T *F;          // [K columns][kc] factors: multipliers up to a row's own step, then its U entries
+  T *F;          // [K columns][kc] A, then the factors by step of their rows: multipliers, then U
   double *pw;    // node t, power e at t (l + 1) + e: x^e (hi, lo), z^e (hi, lo)
   int kc, n, K, mg, P;
 };
@@ -1144,14 +1145,12 @@ __device__ __forceinline__ unsigned mag_hi(float v) { return __float_as_uint(v) 
 // Solve for the G right-hand sides of operators S.gl[g0 ..], then refine with
 // double-double residuals until the stopping rule holds (with FP32 factors the
 // first passes take plain FP64 residuals, as in the wavefront kernels).
-// st0, st1: elimination step of this lane's two rows. The solution is left in
-// Y.xs; returns whether it converged.
+// The solution is left in Y.xs; returns whether it converged.
 template <int G, typename T, bool PW>
-__device__ __forceinline__ bool block_refine(const WArgs &a, BlockShared<T> &S, const BlockSys<T> &Y, int st0, int st1,
-                                             int g0) {
+__device__ __forceinline__ bool block_refine(const WArgs &a, BlockShared<T> &S, const BlockSys<T> &Y, int g0) {
   constexpr bool F32 = std::is_same<T, float>::value;
   const int tid = threadIdx.x, ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n = Y.n, K = Y.K, kc = Y.kc, k64 = min(K, 64);
+  const int n = Y.n, K = Y.K, kc = Y.kc;
   // residual rows: RW rows per wavefront, NP lanes (parts) per row
   const int NP = K <= 84 ? 3 : 2, RW = 64 / NP;
   const int part = ln / RW, row = wv * RW + (ln - part * RW);
@@ -1177,9 +1176,10 @@ __device__ __forceinline__ bool block_refine(const WArgs &a, BlockShared<T> &S, 
                                          dd{own[0], own[1]}, dd{own[2], own[3]})
                              : dd{0.0, 0.0};
   }
-  const double rdg0 = st0 < K ? 1.0 / static_cast<double>(S.piv[st0]) : 0.0,
-               rdg1 = st1 < K ? 1.0 / static_cast<double>(S.piv[st1]) : 0.0;
-  const int pv0 = S.pv[min(ln, K - 1)], pv1 = S.pv[min(ln + 64, K - 1)];  // lane k: pivot rows of steps k, k + 64
+  // lane r: the reciprocal pivots and the pivot rows of steps r and r + 64
+  const double rdg0 = 1.0 / static_cast<double>(S.piv[ln]),
+               rdg1 = ln + 64 < K ? 1.0 / static_cast<double>(S.piv[ln + 64]) : 0.0;
+  const int pv0 = S.pv[ln], pv1 = S.pv[min(ln + 64, K - 1)];
   double dprev = 0.0;
   bool plain = F32, converged = false;
   for (int it = 0; it <= a.max_iter && !converged; ++it) {
@@ -1260,38 +1260,37 @@ __device__ __forceinline__ bool block_refine(const WArgs &a, BlockShared<T> &S, 
     // substitutions of right-hand side wv, in FP64 whatever the factors' type
     double dm = 0.0, xm = 0.0;
     if (wv < G) {
-      const bool r0 = ln < K, r1 = ln + 64 < K;
-      double w0 = r0 ? Y.vs[wv * kc + ln] : 0.0, w1 = r1 ? Y.vs[wv * kc + ln + 64] : 0.0;
-      auto step = [&](int k, int p, bool fwd) {
-        const double y = rl(p >= 64 ? w1 : w0, p & 63);
-        double f0 = static_cast<double>(Y.F[k * kc + ln]), f1 = static_cast<double>(Y.F[k * kc + ln + 64]);
-        if (!fwd) {  // (beside the chain: no product waits for y)
-          f0 *= rdg0;
-          f1 *= rdg1;
-        }
-        const bool u0 = r0 && (fwd ? st0 > k : st0 < k), u1 = r1 && (fwd ? st1 > k : st1 < k);
-        w0 = fma(-(u0 ? f0 : 0.0), y, w0);
-        w1 = fma(-(u1 ? f1 : 0.0), y, w1);
-      };
+      // lane r holds the rows of steps r and r + 64, so a step's value comes from
+      // a fixed lane and only one of the two rows needs a mask, or takes part
+      double w0 = Y.vs[wv * kc + pv0], w1 = ln + 64 < K ? Y.vs[wv * kc + pv1] : 0.0;
+      const T *F0 = Y.F + ln, *F1 = F0 + 64;
 #pragma unroll 4
-      for (int k = 0; k < k64; ++k) step(k, __builtin_amdgcn_readlane(pv0, k), true);
+      for (int k = 0; k < 64; ++k) {
+        const double y = rl(w0, k);
+        w0 = fma(-static_cast<double>(ln > k ? F0[k * kc] : T(0)), y, w0);
+        w1 = fma(-static_cast<double>(F1[k * kc]), y, w1);
+      }
 #pragma unroll 4
-      for (int k = 64; k < K; ++k) step(k, __builtin_amdgcn_readlane(pv1, k - 64), true);
+      for (int k = 64; k < K; ++k) w1 = fma(-static_cast<double>(ln + 64 > k ? F1[k * kc] : T(0)), rl(w1, k - 64), w1);
       w0 *= rdg0;
       w1 *= rdg1;
 #pragma unroll 4
-      for (int k = K - 1; k >= 64; --k) step(k, __builtin_amdgcn_readlane(pv1, k - 64), false);
+      for (int k = K - 1; k >= 64; --k) {
+        const double y = rl(w1, k - 64);
+        w0 = fma(-(static_cast<double>(F0[k * kc]) * rdg0), y, w0);
+        w1 = fma(-(static_cast<double>(ln + 64 < k ? F1[k * kc] : T(0)) * rdg1), y, w1);
+      }
 #pragma unroll 4
-      for (int k = k64 - 1; k >= 0; --k) step(k, __builtin_amdgcn_readlane(pv0, k), false);
-      // row p_k holds the correction of unknown k
-      auto add = [&](int st, double d) {
-        const double x = Y.xs[4 * st + wv] + d;
-        Y.xs[4 * st + wv] = x;
+      for (int k = 63; k >= 0; --k) w0 = fma(-(static_cast<double>(ln < k ? F0[k * kc] : T(0)) * rdg0), rl(w0, k), w0);
+      // the row of step k holds the correction of unknown k
+      auto add = [&](int k, double d) {
+        const double x = Y.xs[4 * k + wv] + d;
+        Y.xs[4 * k + wv] = x;
         dm = fmax(dm, fabs(d));
         xm = fmax(xm, fabs(x));
       };
-      if (r0) add(st0, w0);
-      if (r1) add(st1, w1);
+      add(ln, w0);
+      if (ln + 64 < K) add(ln + 64, w1);
       dm = wave_max(dm);
       xm = wave_max(xm);
     }
@@ -1334,7 +1333,7 @@ __device__ __forceinline__ void block_solve(const WArgs &a, BlockShared<T> &S, d
     if (tid == 0 && a.status) a.status[q] = code;
   };
   const bool bad = (c < 0 || c >= a.n_nodes || n < 1 || n > a.n_max || m < 1 || m > 15 || (m & 1) == 0 || l < 0 ||
-                    l > 6 || n < n_terms(l) || K > kc || K > KC);
+                    l > 6 || n < n_terms(l) || K <= 64 || K > kc || K > KC);
   if (bad) {
     reject(2);
     return;
@@ -1548,12 +1547,12 @@ __device__ __forceinline__ void block_solve(const WArgs &a, BlockShared<T> &S, d
     }
     __syncthreads();
     if (ln == 0) S.red[wv][1] = pmin;
-    // the factors to LDS for the substitutions
+    // the factors to LDS for the substitutions, each row at the place of its step
 #pragma unroll
     for (int cc = 0; cc < CL; ++cc) {
       const int j = 4 * cc + wv;
-      if (j < K && ln < K) Y.F[j * kc + ln] = r0[cc];
-      if (j < K && ln + 64 < K) Y.F[j * kc + ln + 64] = r1[cc];
+      if (j < K) Y.F[j * kc + st0] = r0[cc];
+      if (j < K && ln + 64 < K) Y.F[j * kc + st1] = r1[cc];
     }
     __syncthreads();
     pmin = fmin(fmin(S.red[0][1], S.red[1][1]), fmin(S.red[2][1], S.red[3][1]));
@@ -1566,10 +1565,10 @@ __device__ __forceinline__ void block_solve(const WArgs &a, BlockShared<T> &S, d
       __syncthreads();
       bool converged;
       switch (G) {
-        case 1: converged = block_refine<1, T, PW>(a, S, Y, st0, st1, g0); break;
-        case 2: converged = block_refine<2, T, PW>(a, S, Y, st0, st1, g0); break;
-        case 3: converged = block_refine<3, T, PW>(a, S, Y, st0, st1, g0); break;
-        default: converged = block_refine<4, T, PW>(a, S, Y, st0, st1, g0); break;
+        case 1: converged = block_refine<1, T, PW>(a, S, Y, g0); break;
+        case 2: converged = block_refine<2, T, PW>(a, S, Y, g0); break;
+        case 3: converged = block_refine<3, T, PW>(a, S, Y, g0); break;
+        default: converged = block_refine<4, T, PW>(a, S, Y, g0); break;
       }
       // 5. status and rescaled output
       bool fin = true;
