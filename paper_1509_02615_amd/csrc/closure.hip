@@ -101,13 +101,17 @@ __device__ __forceinline__ bf8v gather_block(const float4 *__restrict__ ye, cons
 
 // Y[s][0..3] times out_scale for S samples (and bad[e] = stamp for members with a value that
 // is not finite, unless bad is NULL), T tiles of 16 samples per wavefront; blocks of
-// W wavefronts share one LDS copy of the weights and loop over contiguous
-// unit ranges (XCD-aware block order); OCC wavefronts per SIMD bound the
-// registers. The launch shapes (T, W, OCC) rbffd_closure_tune chooses from
+// W wavefronts share one LDS copy of the weights; each XCD has a contiguous
+// range of the units (tiles), which its blocks take in turns; OCC wavefronts
+// per SIMD bound the registers. The launch shapes (T, W, OCC) rbffd_closure_tune chooses from
 // are kMlpShapes; a sample's arithmetic is the same in every shape. Measured
 // on 557,056 samples: one 16-wavefront block per compute unit at four
 // wavefronts per SIMD and T = 1 is fastest (more wavefronts hide the gather
 // latency better than larger tiles save LDS reads of the weight fragments).
+// Bound by the chain gather - products - activations of each tile at four
+// wavefronts per SIMD: of this launch's 50 us the matrix pipe is busy 37%, the
+// vector unit 43% and LDS 46%, without bank conflicts (50%, 57% and 62% of the
+// cycles in which a compute unit has a wavefront).
 template <int T, int MLP_WAVES, int MLP_OCC, int ACT>
 __global__ __launch_bounds__(64 * MLP_WAVES) __attribute__((amdgpu_waves_per_eu(MLP_OCC, MLP_OCC))) void
 mlp_forward_kernel(
@@ -275,8 +279,11 @@ template <int SHAPE> __global__ __launch_bounds__(256) void mfma_probe_kernel(fl
 // reads rows (16 bytes a lane) and the weight gradients, which contract over
 // the samples, read columns with the transposing LDS load; so do the
 // products with W2 transposed, from the one copy of W2. Rows are 256 bytes;
-// their 16-byte chunks are permuted by row (tr_sw) so that both kinds of
-// read touch every bank once. Most of W1 stays in registers.
+// their 16-byte chunks are permuted by row (tr_sw) so that the reads of rows
+// and of columns touch every bank once. The 8-byte stores of the activations,
+// the 8-byte accesses of the back-propagation and the columns of dY meet
+// others in a bank (two-way): 15% of the cycles in which LDS is active. Most of
+// W1 stays in registers.
 //
 // Feature 150 (padding of the input row, where the network's W1 sees 0) is
 // set to 1: its column of the W1 gradient is the gradient of b1. Likewise
@@ -284,10 +291,11 @@ template <int SHAPE> __global__ __launch_bounds__(256) void mfma_probe_kernel(fl
 // gradient of b2.
 //
 // Bound by the matrix and LDS pipes at two wavefronts per SIMD. 417,792
-// samples (192 members x 2,176 nodes): 161 us per call (146 us this kernel,
+// samples (192 members x 2,176 nodes): 164 us per call (150 us this kernel,
 // 9 us the sum of the blocks' gradients), against 1,471 us with one launch per
 // product and the activations, their transposes and atomic weight gradients in
-// HBM. The matrix pipe is busy 32% of the kernel, the vector unit 38%, LDS 45%:
+// HBM. The matrix pipe is busy 27% of the launch, the vector unit 35%, LDS 38%
+// (32%, 40% and 44% of the cycles in which a compute unit has a wavefront):
 // what is left is the latency of the four phases between barriers.
 constexpr int TR_S = 64, TR_WAVES = 8, TR_ONE = 150, TR_ONE_DY = 4;
 constexpr int TR_W1_REG = 6;                          // W1 fragments in registers (of 10); the others in LDS

@@ -369,10 +369,10 @@ __device__ __forceinline__ int scan32(int v) {
 // distance (broadcast reads, two keys each); keys of equal distance (lattices
 // have many) meet in LDS and count the smaller node numbers among themselves.
 // So nothing is sorted and only about n / 0.75 keys are compared. Bound by
-// vector issue (the vector unit is busy throughout); 3 KB of LDS per wavefront,
+// vector issue (the vector unit is busy 96% of the kernel); 3 KB of LDS per wavefront,
 // where the LDS sort below needs 25 KB and runs six wavefronts per compute
 // unit. The whole search of the 524,288 centres of the 2048 x 256 channel
-// (n = 37) takes 0.57 ms (this kernel 0.46 ms, 495 vector instructions per
+// (n = 37) takes 0.53 ms (this kernel 0.47 ms, 495 vector instructions per
 // centre), against 6.06 ms with every centre sorted in LDS and 0.86 ms (917
 // instructions) with whole (d, j) keys compared and each candidate's row found
 // by a test per row. A centre whose block holds more than KNN_KEYS candidates

@@ -1080,10 +1080,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(wave_occ<KC,
 // others update the rest; nobody moves rows, and the pivot row's entries come
 // from the pivot lane's registers. The factors then go to LDS for the
 // substitutions, rows in the order of their steps: one wavefront per right-hand
-// side, the unknowns in registers, the column of a step an independent LDS read,
-// no barriers. The residual
-// takes three lanes per row (K <= 84) or two, with the same |x_i - x_j|^m and
-// power tables as the wavefront kernels.
+// side, the unknowns in registers, the column of a step an independent LDS
+// read, no barriers. The residual takes three lanes per row (K <= 84) or two,
+// with the same |x_i - x_j|^m and power tables as the wavefront kernels.
 //
 // Pivots are compared in full, multipliers are rounded quotients and the
 // substitutions run in FP64, also on FP32 factors: whether a refinement with
@@ -1092,11 +1091,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(wave_occ<KC,
 // substitutions a quarter of such systems went the other way, for 0-4% (FP64
 // factors) and 4-9% (FP32) less time.
 //
-// Bound by the chain of a step (LDS read, update, pivot search, reciprocal,
-// LDS write, barrier). The 4,700 K = 82 systems of the mixed 1M batch take
-// 0.98 ms (FP64) against 2.84 ms, and the 500 of a 128 x 128 batch with FP32
-// factors 0.41 ms against 2.42 ms, with the matrix in LDS, rows interchanged
-// there and a barrier per step of every substitution.
+// Bound by the chain of a step (LDS read, update, pivot search, quotient, LDS
+// write, barrier). The 4,700 K = 82 systems of the mixed 1M batch take 0.98 ms
+// (FP64) against 2.84 ms with the matrix in LDS, rows interchanged there and a
+// barrier per step of every substitution. The 500 of a 128 x 128 batch with
+// FP32 factors take 0.45-0.60 ms against 1.71-2.29 ms (eight seeds): the time
+// of the slowest system's refinement passes.
 template <typename T> struct BlockShared {
   T l[2][128];           // multipliers of the step in flight and the next
   T piv[128];            // pivot of each step
